@@ -19,6 +19,7 @@
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 #include "tn_buffer.h"
+#include "tn_lanes.h"
 
 namespace tn {
 
@@ -227,6 +228,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_mfma2(const GateDesc *descs, in
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x / ksplit, kc = blockIdx.x % ksplit;
   if (!d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2) return;
+  if (round > 0 && !d.fullOrder) return;  // k_gram_cross
   int I, J;
   rr_pair(round, pairIdx, d.nblk, I, J);
   if (pair_known_orthogonal(d, I, J)) return;
@@ -285,12 +287,594 @@ __global__ __launch_bounds__(256, 2) void k_gram_mfma2(const GateDesc *descs, in
   }
 }
 
+// The cross block G_IJ = X_I^H X_J alone (rounds after a sweep's first: the
+// pair solves hand the blocks' own Grams on, see k_eig).  Four 16x16 tiles,
+// (column groups 0, 1 of block I) x (2, 3: block J); every wavefront holds
+// all four and takes each fourth 16-row tile, so that a k-step's four loads
+// feed twelve MFMAs; the four partials are added in LDS in a fixed order.
+// Reading X bounds it: 16 x 64 bytes per row against 12 MFMAs per 4 rows,
+// so the loads run three k-steps ahead.
+__global__ __launch_bounds__(256, 2) void k_gram_cross(const GateDesc *descs, int round,
+                                                       int ksplit) {
+  const GateDesc &d = descs[blockIdx.y];
+  const int pairIdx = blockIdx.x / ksplit, kc = blockIdx.x % ksplit;
+  if (d.fullOrder || !d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2) return;
+  int I, J;
+  rr_pair(round, pairIdx, d.nblk, I, J);
+  if (pair_known_orthogonal(d, I, J)) return;
+  int chunk = (d.rows + ksplit - 1) / ksplit;
+  chunk = (chunk + 15) / 16 * 16;
+  const int rbeg = kc * chunk;
+  const int rend = min(d.rows, rbeg + chunk);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar)
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int ld = d.ldx;
+  const BufRes rI = make_res(d.X + (size_t)I * BW * ld, BW * ld);
+  const BufRes rJ = make_res(d.X + (size_t)J * BW * ld, BW * ld);
+  d4_t p1[4], p2[4], p3[4];  // tile u: column groups (u >> 1, 2 + (u & 1))
+#pragma unroll
+  for (int u = 0; u < 4; u++) {
+    p1[u] = d4_t{0.0, 0.0, 0.0, 0.0};
+    p2[u] = d4_t{0.0, 0.0, 0.0, 0.0};
+    p3[u] = d4_t{0.0, 0.0, 0.0, 0.0};
+  }
+  auto load_step = [&](double2 *x, int r) {
+#pragma unroll
+    for (int t = 0; t < 4; t++) x[t] = bload(t < 2 ? rI : rJ, (16 * (t & 1) + l16) * ld + r);
+  };
+  auto mfma_step = [&](const double2 *xin, int r) {
+    __builtin_amdgcn_sched_barrier(0);  // later steps' loads stay in flight
+    double2 x[4];
+#pragma unroll
+    for (int t = 0; t < 4; t++) x[t] = r < rend ? xin[t] : make_double2(0.0, 0.0);
+    double dm[2], sp[2];  // a - b of the A operands, c + d of the B operands
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+      dm[t] = x[t].x - x[t].y;
+      sp[t] = x[2 + t].x + x[2 + t].y;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const double2 a = x[u >> 1], b = x[2 + (u & 1)];
+      p1[u] = mfma64(a.x, b.x, p1[u]);
+      p2[u] = mfma64(a.y, b.y, p2[u]);
+      p3[u] = mfma64(dm[u >> 1], sp[u & 1], p3[u]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int base = rbeg + wave * 16;
+  const int nstep = base < rend ? (rend - base + 63) / 64 * 4 : 0;
+  auto row_of = [&](int n) { return base + 64 * (n >> 2) + 4 * (n & 3) + lg; };
+  if (nstep) {
+    double2 x0[4], x1[4], x2[4], x3[4];
+    load_step(x0, row_of(0));
+    load_step(x1, row_of(1));
+    load_step(x2, row_of(2));
+    for (int n = 0; n < nstep; n += 4) {
+      load_step(x3, row_of(n + 3));
+      mfma_step(x0, row_of(n));
+      load_step(x0, row_of(n + 4));
+      mfma_step(x1, row_of(n + 1));
+      load_step(x1, row_of(n + 5));
+      mfma_step(x2, row_of(n + 2));
+      load_step(x2, row_of(n + 6));
+      mfma_step(x3, row_of(n + 3));
+    }
+  }
+  __shared__ double2 red[4][4][64];
+  for (int w = 0; w < 4; w++) {
+    if (wave == w) {
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+          const double gr = p1[u][v] + p2[u][v], gi = p3[u][v] - p1[u][v] + p2[u][v];
+          double2 *o = &red[u][v][lane];
+          *o = w == 0 ? make_double2(gr, gi) : make_double2(o->x + gr, o->y + gi);
+        }
+    }
+    __syncthreads();
+  }
+  if (tid == 0 && d.ctr && rend > rbeg) {
+    atomicAdd(&d.ctr[CTR_GRAM_FLOP], 8ull * (rend - rbeg) * (BW * BW));
+    atomicAdd(&d.ctr[CTR_GRAM_BYTE], 16ull * (rend - rbeg) * PW + 16ull * BW * BW);
+  }
+  double2 *G = d.Gp + ((size_t)kc * d.gpStride + pairIdx) * (PW * PW);
+  for (int e = tid; e < BW * BW; e += 256) {
+    const int p = e / BW, q = e % BW;  // tile entry v of lane l: row l / 16 + 4 v, column l % 16
+    const int u = (p >> 4) * 2 + (q >> 4), v = (p & 15) >> 2, l = (p & 3) * 16 + (q & 15);
+    G[p * PW + BW + q] = red[u][v][l];
+  }
+}
+
 // ---------------------------------------------------------------- 64x64 Hermitian Jacobi
 
 constexpr int LDG = PW + 1;
-constexpr int EIG_THREADS = 512;  // 8 wavefronts; two pair solves share a CU
-constexpr int EIG_VROWS = PW / (EIG_THREADS / 64);  // rows of V held by each wavefront
-constexpr int EIG_OFFD = (PW / 2) * (PW / 2 - 1) / 2;  // off-diagonal 2x2 blocks (i < j)
+
+// The upper triangle of a pair's Gram, put(r, c, G(r, c)) for r <= c, by
+// THREADS threads.  In a sweep's first round everything comes from the Gram
+// partials; later only the cross block does, and the blocks' own Grams are as
+// their last pair solves left them (a sweep that rotates nothing has seen all
+// of them computed afresh, so convergence is decided on fresh Grams).  Four
+// entries at a time, so that the loads of the K-split's partials overlap (one
+// entry at a time, 16 partials took longer than the solve's rounds).
+template <int THREADS, class F>
+__device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int round, int pairIdx,
+                                          int ksplit, F put) {
+  const int tid = threadIdx.x;
+  const size_t step = (size_t)d.gpStride * (PW * PW);
+  const double2 *G = d.Gp + (size_t)pairIdx * (PW * PW);
+  auto sums = [&](const int (&o)[4], double2 (&x)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; k++) x[k] = G[o[k]];
+#pragma unroll 4
+    for (int kc = 1; kc < ksplit; kc++)
+#pragma unroll
+      for (int k = 0; k < 4; k++) x[k] = cadd(x[k], G[kc * step + o[k]]);
+  };
+  if (round == 0) {
+    for (int e0 = tid; e0 < PW * PW; e0 += 4 * THREADS) {
+      int o[4];
+      double2 x[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) o[k] = e0 + k * THREADS;
+      sums(o, x);  // entries below the stored tiles are read and dropped
+#pragma unroll
+      for (int k = 0; k < 4; k++)
+        if (o[k] / PW <= o[k] % PW) put(o[k] / PW, o[k] % PW, x[k]);
+    }
+    return;
+  }
+  static_assert(BW * BW % THREADS == 0 && PW * PW % (4 * THREADS) == 0, "whole entries per thread");
+  constexpr int CE = BW * BW / THREADS;  // entries of a 32x32 block per thread
+  double2 dI[CE], dJ[CE];
+#pragma unroll
+  for (int k = 0; k < CE; k++) {
+    dI[k] = d.Dg[(size_t)I * (BW * BW) + tid + k * THREADS];
+    dJ[k] = d.Dg[(size_t)J * (BW * BW) + tid + k * THREADS];
+  }
+  int o[4];
+  double2 x[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const int e = tid + (k % CE) * THREADS;
+    o[k] = e / BW * PW + BW + e % BW;
+  }
+  sums(o, x);
+#pragma unroll
+  for (int k = 0; k < CE; k++) {
+    const int e = tid + k * THREADS, r = e / BW, c = e % BW;
+    put(r, BW + c, x[k]);
+    if (r <= c) {
+      put(r, c, dI[k]);
+      put(BW + r, BW + c, dJ[k]);
+    }
+  }
+}
+
+// Pair solve: cyclic two-sided Jacobi on the pair Gram G (64x64 Hermitian)
+// with the rotations accumulated in V.
+//
+// Passes.  A pass takes one bit b of the column number and pairs every column
+// x whose bit b is 0 (32 of them, the p columns) with every column whose bit b
+// is 1 (the q columns): two half-passes (v = 0, 1) of 16 rounds, each round 32
+// disjoint rotations.  Slot s = 16 g + l (g = 0, 1; l = 0 .. 15) holds the
+// p column with index 16 g + l, and in round r the q column with index
+// 16 (g ^ v) + (l + r) mod 16 (indices count the columns with that bit).  Bit
+// 5 pairs block I with block J; bits 4 .. 0 pair columns inside each block.
+// Every solve makes the pass of bit 5.  The passes inside the blocks are
+// spread over a sweep: one of them in every fourth round of the tournament,
+// or, when the sweep has few rounds, several in one round, so that each pair
+// of columns meets at least once per sweep.  Measured sweep counts on the
+// merged matrices equal those of a solve that takes all 2016 pairs every time
+// (N = 128, 256, 512: 7, 8, 9), at 1.25 passes of 32 rounds instead of 63.
+//
+// Layout.  G's off-diagonal 2x2 blocks (p, q of slot i) x (p, q of slot j)
+// lie in registers, two per thread: inside a group of 16 slots the block
+// (l, l + delta) for delta = 1 .. 8 (delta = 8 twice, as each other's
+// adjoint), across the groups (slot l, slot 16 + l + delta) for delta = 0 ..
+// 15; lane l of a row of 16 lanes holds slot l's, a row holds two neighbouring
+// deltas.  Between rounds the q columns move on by one slot, so with entries
+// a = G(p_i, p_j), b = G(p_i, q_j), c = G(q_i, p_j), e = G(q_i, q_j): a stays,
+// b comes from delta + 1, c from lane l + 1 and delta - 1, e from lane l + 1.
+// Those are register moves and row rotations (DPP); only one b and one c per
+// thread cross rows, through LDS.  V is in registers too, 8 rows of one
+// slot's two columns per thread.  LDS carries the rotation parameters, the
+// row crossings, and G between half-passes (upper triangle, 32 KB), so three
+// solves fit a CU.
+//
+// Rotations without square-root scaling: with V = V~ S and G = S G~ S, S
+// diagonal, x_p' = x_p - alpha x_q and x_q' = x_q + beta x_p (unscaled
+// columns), 4 multiply-adds per complex entry instead of 6; the squared
+// scales s^2 <- s^2 cos^2 (cos^2 >= 1/2) are multiplied in after 16 rounds.
+// The threads that hold delta = 1 hold the next round's couplings
+// b = G(p_l, q_{l+1}), so they compute the next rotations as soon as their
+// blocks are updated, while the other wavefronts update V: one barrier a round.
+//
+// A solve whose couplings all pass the test returns before the first pass.
+// Bound by the vector units' float64 rate: 512 blocks x 32 and 2048 pairs of
+// V entries x 8 multiply-adds per round.
+constexpr int EIG_THREADS = 256;
+constexpr int EIG_ROWS = EIG_THREADS / 16;  // rows of 16 lanes
+// Rows of V per half-wavefront: the first wavefront, which also computes the
+// next rotations, takes 5 (rows 0 .. 9), the others 9 (rows 10 .. 63).
+constexpr int EIG_VROWS = 9, EIG_VROWS0 = 5;
+constexpr int EIG_EVERY = 4;  // tournament rounds between passes inside the blocks
+constexpr int EIG_UPPER = PW * (PW - 1) / 2;
+
+// Bits of the passes a solve makes in a round of a sweep of nr >= 3 rounds.
+__device__ __forceinline__ int eig_bits(int round, int nr) {
+  int bits = 32;
+  if (round % EIG_EVERY == 0) {
+    const int k = round / EIG_EVERY, ns = (nr + EIG_EVERY - 1) / EIG_EVERY;
+    for (int t = 0; t < 5; t++)
+      if (ns >= 5 ? t == k % 5 : t % ns == k) bits |= 16 >> t;
+  }
+  return bits;
+}
+
+// 1 / x and sqrt(x) of normal positive numbers, to rounding: the hardware's
+// estimates (24 bits) and two Newton steps.  The library forms also cover
+// subnormal and infinite arguments, which a pair that passes the rotation
+// test does not have, and their longer chains are the solve's critical path.
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double fast_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double s = x * y, hy = 0.5 * y;  // Goldschmidt: s -> sqrt(x), hy -> 1 / (2 sqrt(x))
+  const double r = fma(-s, hy, 0.5);
+  s = fma(s, r, s);
+  hy = fma(hy, r, hy);
+  return fma(fma(-s, s, x), hy, s);
+}
+
+// x with bit value v inserted at position b; x without bit b.
+__device__ __forceinline__ int bit_ins(int x, int b, int v) {
+  return ((x >> b) << (b + 1)) | (v << b) | (x & ((1 << b) - 1));
+}
+__device__ __forceinline__ int bit_del(int x, int b) {
+  return ((x >> (b + 1)) << b) | (x & ((1 << b) - 1));
+}
+
+// Place of entry (a, b), a < b, of the packed strict upper triangle.
+__device__ __forceinline__ int gpack(int a, int b) { return a * (PW - 1) - a * (a - 1) / 2 + b - a - 1; }
+
+__device__ __forceinline__ double2 gget(const double2 *Gs, int a, int b) {
+  return a < b ? Gs[gpack(a, b)] : cconj(Gs[gpack(b, a)]);
+}
+__device__ __forceinline__ void gput(double2 *Gs, int a, int b, double2 x) {
+  Gs[a < b ? gpack(a, b) : gpack(b, a)] = a < b ? x : cconj(x);
+}
+
+// x - a y and x + a y
+__device__ __forceinline__ double2 cfms(double2 x, double2 a, double2 y) {
+  return make_double2(fma(a.y, y.y, fma(-a.x, y.x, x.x)), fma(-a.y, y.x, fma(-a.x, y.y, x.y)));
+}
+__device__ __forceinline__ double2 cfmad(double2 x, double2 a, double2 y) {
+  return make_double2(fma(-a.y, y.y, fma(a.x, y.x, x.x)), fma(a.y, y.x, fma(a.x, y.y, x.y)));
+}
+
+// One 2x2 block of G between two slots.
+struct GBlk {
+  double2 a, b, c, e;
+};
+
+// B <- R_i^H B R_j with R = [[1, beta], [-alpha, 1]].
+__device__ __forceinline__ void blk_rotate(GBlk &B, double2 ali, double2 bei, double2 alj,
+                                           double2 bej) {
+  const double2 a = cfms(B.a, alj, B.b), b = cfmad(B.b, bej, B.a);
+  const double2 c = cfms(B.c, alj, B.e), e = cfmad(B.e, bej, B.c);
+  const double2 ai = cconj(ali), bi = cconj(bei);
+  B.a = cfms(a, ai, c);
+  B.c = cfmad(c, bi, a);
+  B.b = cfms(b, ai, e);
+  B.e = cfmad(e, bi, b);
+}
+
+struct EigShared {
+  double2 Gs[EIG_UPPER];        // strict upper triangle of G, between half-passes
+  double dg[PW];                // diagonal of G
+  double sca[2][PW / 2];        // scales of the p and q columns of each slot
+  double2 prm[2][2][PW / 2];    // alpha, beta of each slot, by round parity
+  double2 xb[2][EIG_ROWS][16];  // b entries that cross rows, by round parity
+  double2 xc[2][EIG_ROWS][16];  // c entries
+  int anyr[2];                  // some rotation in the round held by that buffer
+  int sweep_rot;                // some rotation in the current inner sweep
+};
+
+// The passes of one solve, for the first wavefront (W0: NV = 5 rows of V per
+// half, and the next rotations) or one of the others (9 rows).  Returns
+// whether the first inner sweep rotated; then V is written.
+template <int NV, bool W0>
+__device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int bits, double tol2,
+                                          double small, double2 *V, unsigned &nrot) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int l = tid & 15, rho = tid >> 4, gpar = rho & 1, u = rho >> 1;
+  const bool intra = u < 4;        // wavefronts 0, 1; the others: across the groups
+  const bool param = W0 && u == 0; // delta = 1: holds the next couplings
+  const int del = intra ? 2 * u + 1 : 2 * (rho - 8);  // first of this thread's two deltas
+  // slots of this thread's blocks: si x sj0, si x sj1
+  const int si = intra ? 16 * gpar + l : l;
+  const int gj = intra ? 16 * gpar : 16;
+  const int sj0 = gj + ((l + del) & 15), sj1 = gj + ((l + del + 1) & 15);
+  const int sv = lane & 31;  // slot of this thread's V entries (= si when intra)
+  // rows that b and c come from (the rows of delta + 2 and delta - 2)
+  const int rb = intra ? (u < 3 ? rho + 2 : rho) : 8 + ((rho - 7) & 7);
+  const int rc = intra ? (u > 0 ? rho - 2 : rho) : 8 + ((rho - 1) & 7);
+  const int vrow0 = W0 ? (tid >> 5) * NV : 2 * EIG_VROWS0 + ((tid >> 5) - 2) * NV;
+  double2 vp[NV], vq[NV];
+  int lb = __ffs(bits) - 1, lv = 0;  // labelling of V's columns (bit, half-pass): any to start
+  {
+    const int cp = bit_ins(sv, lb, 0), cq = bit_ins(sv, lb, 1);
+#pragma unroll
+    for (int h = 0; h < NV; h++) {
+      vp[h] = make_double2(vrow0 + h == cp ? 1.0 : 0.0, 0.0);
+      vq[h] = make_double2(vrow0 + h == cq ? 1.0 : 0.0, 0.0);
+    }
+  }
+  int first_rot = 0;
+  for (int sweep = 0; sweep < d.innerSweeps; sweep++) {
+    if (tid == 0) S.sweep_rot = 0;
+    for (int t = 0; t < 12; t++) {
+      // bits 4 .. 0, then 5; two half-passes each
+      const int b = t < 10 ? 4 - (t >> 1) : 5, v = t & 1;
+      if (!((bits >> b) & 1)) continue;
+      // V's columns to this half-pass's slots
+      if (b == lb) {
+        if (v != lv) {
+#pragma unroll
+          for (int h = 0; h < NV; h++)
+            vq[h] = make_double2(__shfl_xor(vq[h].x, 16, 64), __shfl_xor(vq[h].y, 16, 64));
+        }
+      } else {
+        const int cp = bit_ins(sv, b, 0), cq = bit_ins(sv ^ (v << 4), b, 1);
+        const bool pq = (cp >> lb) & 1, qq = (cq >> lb) & 1;  // held as a q column until now
+        const int ps = (lane & 32) | (bit_del(cp, lb) ^ (pq ? lv << 4 : 0));
+        const int qs = (lane & 32) | (bit_del(cq, lb) ^ (qq ? lv << 4 : 0));
+#pragma unroll
+        for (int h = 0; h < NV; h++) {
+          __builtin_amdgcn_sched_barrier(0);  // one row's permutes at a time (registers)
+          const double px = __shfl(vp[h].x, ps, 64), py = __shfl(vp[h].y, ps, 64);
+          const double qx = __shfl(vq[h].x, ps, 64), qy = __shfl(vq[h].y, ps, 64);
+          const double rx = __shfl(vp[h].x, qs, 64), ry = __shfl(vp[h].y, qs, 64);
+          const double tx = __shfl(vq[h].x, qs, 64), ty = __shfl(vq[h].y, qs, 64);
+          vp[h] = make_double2(pq ? qx : px, pq ? qy : py);
+          vq[h] = make_double2(qq ? tx : rx, qq ? ty : ry);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lb = b;
+      lv = v;
+      const int vx = v << 4;
+      const int pi = bit_ins(si, b, 0), qi = bit_ins(si ^ vx, b, 1);
+      const int pj0 = bit_ins(sj0, b, 0), qj0 = bit_ins(sj0 ^ vx, b, 1);
+      const int pj1 = bit_ins(sj1, b, 0), qj1 = bit_ins(sj1 ^ vx, b, 1);
+      GBlk B0, B1;
+      B0.a = gget(S.Gs, pi, pj0);
+      B0.b = gget(S.Gs, pi, qj0);
+      B0.c = gget(S.Gs, qi, pj0);
+      B0.e = gget(S.Gs, qi, qj0);
+      B1.a = gget(S.Gs, pi, pj1);
+      B1.b = gget(S.Gs, pi, qj1);
+      B1.c = gget(S.Gs, qi, pj1);
+      B1.e = gget(S.Gs, qi, qj1);
+      // parameter threads (slot si): diagonal entries, squared scales, the
+      // coupling of the slot's pair, and what it is after its rotation
+      double dp = 0.0, dq = 0.0, s2p = 1.0, s2q = 1.0;
+      double2 gc = make_double2(0.0, 0.0), gres = gc;
+      if (param) {
+        dp = S.dg[pi];
+        dq = S.dg[qi];
+        gc = gget(S.Gs, pi, qi);
+      }
+      // Rotations into buffer w.  With true diagonal entries x, y, coupling
+      // g = s_p s_q g~, h = |g|^2 and delta = y - x, the rotation that zeroes
+      // g has w = 2 sign(delta) / (|delta| + sqrt(delta^2 + 4h)), tangent
+      // w |g|, cos^2 = 1 / (1 + w^2 h); the new diagonal is (x - w h,
+      // y + w h).  On the unscaled columns alpha = w conj(g~) s_q^2, beta =
+      // w g~ s_p^2.
+      auto params = [&](int w) {
+        int act = 0;
+        double2 al = make_double2(0.0, 0.0), be = make_double2(0.0, 0.0);
+        gres = gc;
+        const double h = s2p * s2q * cabs2(gc);
+        if (dp > small && dq > small && h > tol2 * dp * dq) {
+          act = 1;
+          const double delta = dq - dp;
+          const double tw = copysign(
+              2.0 * fast_rcp(fabs(delta) + fast_sqrt(fma(delta, delta, 4.0 * h))), delta);
+          const double wh = tw * h, c2 = fast_rcp(fma(tw, wh, 1.0));
+          const double wq = tw * s2q, wp = tw * s2p;
+          al = make_double2(wq * gc.x, -wq * gc.y);
+          be = make_double2(wp * gc.x, wp * gc.y);
+          dp -= wh;
+          dq += wh;
+          s2p *= c2;
+          s2q *= c2;
+          gres = make_double2(0.0, 0.0);
+          nrot++;
+        }
+        S.prm[w][0][si] = al;
+        S.prm[w][1][si] = be;
+        const unsigned long long m = __ballot(act);
+        if (tid == 0) {
+          S.anyr[w] = m != 0ull;
+          if (m) S.sweep_rot = 1;
+        }
+      };
+      if (param) params(0);
+      __syncthreads();
+#pragma nounroll
+      for (int r = 0; r < 16; r++) {
+        const int w = r & 1;
+        const bool any = S.anyr[w] != 0;
+        double2 cg = make_double2(0.0, 0.0);
+        if (any) {
+          const double2 ali = S.prm[w][0][si], bei = S.prm[w][1][si];
+          blk_rotate(B0, ali, bei, S.prm[w][0][sj0], S.prm[w][1][sj0]);
+          blk_rotate(B1, ali, bei, S.prm[w][0][sj1], S.prm[w][1][sj1]);
+        }
+        S.xb[w][rho][l] = B0.b;
+        S.xc[w][rho][l] = B1.c;
+        if (param) {  // next round's couplings and q columns
+          cg = cconj(row_next<1>(gres));
+          gc = B0.b;
+          dq = row_next<1>(dq);
+          s2q = row_next<1>(s2q);
+          if (r < 15) params(w ^ 1);
+        }
+        if (any) {
+          const double2 al = S.prm[w][0][sv], be = S.prm[w][1][sv];
+#pragma unroll
+          for (int h = 0; h < NV; h++) {
+            const double2 x = cfms(vp[h], al, vq[h]);
+            vq[h] = cfmad(vq[h], be, vp[h]);
+            vp[h] = x;
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < NV; h++) vq[h] = row_next<1>(vq[h]);
+        // the q columns move on by one slot
+        const double2 c8 = cconj(row_next<9>(B0.c));  // delta = 8: b from the adjoint of c at 7
+        const double2 c1 = row_next<1>(B0.c);
+        B0.b = B1.b;
+        B1.c = c1;
+        B0.e = row_next<1>(B0.e);
+        B1.e = row_next<1>(B1.e);
+        __syncthreads();
+        B1.b = S.xb[w][rb][l];
+        B0.c = S.xc[w][rc][(l + 1) & 15];
+        if (intra && u == 3) B1.b = c8;
+        if (param) B0.c = cg;
+      }
+      // back to LDS with the scales multiplied in
+      if (param) {
+        const double fp = sqrt(s2p), fq = sqrt(s2q);
+        S.sca[0][si] = fp;
+        S.sca[1][si] = fq;
+        S.dg[pi] = dp;
+        S.dg[qi] = dq;
+        gput(S.Gs, pi, qi, cscale(gc, fp * fq));
+      }
+      __syncthreads();
+      const double fpi = S.sca[0][si], fqi = S.sca[1][si];
+      {
+        const double fp = S.sca[0][sj0], fq = S.sca[1][sj0];
+        gput(S.Gs, pi, pj0, cscale(B0.a, fpi * fp));
+        gput(S.Gs, pi, qj0, cscale(B0.b, fpi * fq));
+        gput(S.Gs, qi, pj0, cscale(B0.c, fqi * fp));
+        gput(S.Gs, qi, qj0, cscale(B0.e, fqi * fq));
+      }
+      if (!(intra && u == 3 && l >= 8)) {  // delta = 8 is held twice
+        const double fp = S.sca[0][sj1], fq = S.sca[1][sj1];
+        gput(S.Gs, pi, pj1, cscale(B1.a, fpi * fp));
+        gput(S.Gs, pi, qj1, cscale(B1.b, fpi * fq));
+        gput(S.Gs, qi, pj1, cscale(B1.c, fqi * fp));
+        gput(S.Gs, qi, qj1, cscale(B1.e, fqi * fq));
+      }
+      {
+        const double fp = S.sca[0][sv], fq = S.sca[1][sv];
+#pragma unroll
+        for (int h = 0; h < NV; h++) {
+          vp[h] = cscale(vp[h], fp);
+          vq[h] = cscale(vq[h], fq);
+        }
+      }
+      __syncthreads();
+    }
+    const int cont = S.sweep_rot;  // every thread reads before anyone clears it
+    if (sweep == 0) first_rot = cont;
+    __syncthreads();
+    if (!cont) break;
+  }
+  if (first_rot) {
+    const int cp = bit_ins(sv, lb, 0), cq = bit_ins(sv ^ (lv << 4), lb, 1);
+#pragma unroll
+    for (int h = 0; h < NV; h++) {
+      V[(vrow0 + h) * PW + cp] = vp[h];
+      V[(vrow0 + h) * PW + cq] = vq[h];
+    }
+  }
+  return first_rot;
+}
+
+__global__ __launch_bounds__(EIG_THREADS, 2) void k_eig(const GateDesc *descs, int round,
+                                                        int ksplit) {
+  const GateDesc &d = descs[blockIdx.y];
+  const int pairIdx = blockIdx.x;
+  if (d.fullOrder || !d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2) return;
+  int I, J;
+  rr_pair(round, pairIdx, d.nblk, I, J);
+  if (pair_known_orthogonal(d, I, J)) {
+    if (threadIdx.x == 0) d.pairFlag[pairIdx] = 0;
+    return;
+  }
+  __shared__ EigShared S;
+  const int tid = threadIdx.x;
+  const double tol2 = d.tol * d.tol;
+  const double small = small_norm2(d);
+  unsigned nrot = 0;  // rotations computed by this thread (profiling)
+  const int bits = eig_bits(round, d.nblk - 1);
+  pair_gram<EIG_THREADS>(d, I, J, round, pairIdx, ksplit, [&](int r, int c, double2 x) {
+    if (r < c)
+      S.Gs[gpack(r, c)] = x;
+    else
+      S.dg[r] = x.x;
+  });
+  __syncthreads();
+  // does any pair of this solve's passes need a rotation?
+  int need = 0;
+  for (int e = tid; e < PW * PW; e += EIG_THREADS) {
+    const int r = e / PW, c = e % PW;
+    if (r < c && ((r ^ c) & bits)) {
+      const double a = S.dg[r], b = S.dg[c];
+      need |= a > small && b > small && cabs2(S.Gs[gpack(r, c)]) > tol2 * a * b;
+    }
+  }
+  int rotated = 0;
+  if (__syncthreads_or(need)) {
+    double2 *V = d.V + (size_t)pairIdx * (PW * PW);
+    if (__builtin_amdgcn_readfirstlane(tid) < 64)  // uniform per wavefront
+      rotated = eig_passes<EIG_VROWS0, true>(d, S, bits, tol2, small, V, nrot);
+    else
+      rotated = eig_passes<EIG_VROWS, false>(d, S, bits, tol2, small, V, nrot);
+  }
+  if (d.ctr && tid < 64) {
+    // fold the per-thread counts of the first wavefront, one atomic per pair
+    unsigned v = nrot;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if (tid == 0 && v) atomicAdd(&d.ctr[CTR_EIG_ROT], (unsigned long long)v);
+  }
+  if (round == 0 || rotated) {  // the blocks' own Grams for the later rounds
+    for (int e = tid; e < 2 * BW * BW; e += EIG_THREADS) {
+      const int blk = e / (BW * BW), r = (e / BW) % BW, c = e % BW, o = blk * BW;
+      if (r <= c)
+        d.Dg[(size_t)(blk ? J : I) * (BW * BW) + r * BW + c] =
+            r < c ? S.Gs[gpack(o + r, o + c)] : make_double2(S.dg[o + r], 0.0);
+    }
+  }
+  if (tid == 0) {
+    // An unrotated solve means the pair was already orthogonal.
+    d.pairFlag[pairIdx] = rotated;
+    if (rotated) atomicOr(&d.sc->rot, 1);
+    if (d.blkVer) {  // only this workgroup touches blocks I and J during the round
+      if (rotated) {
+        d.blkVer[I] += 1;
+        d.blkVer[J] += 1;
+      } else {
+        d.pairSeen[I * d.nblk + J] = make_int2(d.blkVer[I], d.blkVer[J]);
+      }
+    }
+  }
+}
+
+constexpr int EIGF_THREADS = 512;  // 8 wavefronts; two pair solves share a CU
+constexpr int EIGF_VROWS = PW / (EIGF_THREADS / 64);  // rows of V held by each wavefront
+constexpr int EIGF_OFFD = (PW / 2) * (PW / 2 - 1) / 2;  // off-diagonal 2x2 blocks (i < j)
 
 // Order of the 2016 column pairs of a pair solve (columns 0-31 from block I,
 // 32-63 from block J).  Rounds 0-31 pair the blocks: slot k pairs column k
@@ -302,7 +886,7 @@ constexpr int EIG_OFFD = (PW / 2) * (PW / 2 - 1) / 2;  // off-diagonal 2x2 block
 // solve made them so), so in the later sweeps the rounds inside the blocks
 // often rotate nothing and cost only their rotation test.  Neighbouring
 // slots hold neighbouring columns (distinct LDS banks of row * 65 + column).
-__device__ __forceinline__ void eig_pair(int r, int k, int &p, int &q) {
+__device__ __forceinline__ void eigf_pair(int r, int k, int &p, int &q) {
   constexpr int H = PW / 2;
   if (r < H) {
     p = k;
@@ -327,6 +911,7 @@ __device__ __forceinline__ void eig_pair(int r, int k, int &p, int &q) {
 // upper triangle is stored, entry (a, b) at min(a, b) * 65 + max(a, b).
 __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b : b * LDG + a; }
 
+// Pair solve over all 2016 column pairs (gates with fullOrder set).
 // Cyclic two-sided Jacobi on the pair Gram G (64x64 Hermitian, in LDS) with
 // the rotations accumulated in V.  A round applies the 32 disjoint rotations
 // of the tournament at once: G <- R^H G R, V <- V R.  G keeps its upper
@@ -342,10 +927,11 @@ __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b 
 // buffered), so a round costs two barriers (one if it rotates nothing).  At
 // most `inner_sweeps` sweeps; the outer sweeps finish what a capped inner
 // solve leaves.
-__global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, int round, int ksplit) {
+__global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
-  if (!d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2) return;
+  if (!d.fullOrder || !d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2)
+    return;
   int I, J;
   rr_pair(round, pairIdx, d.nblk, I, J);
   if (pair_known_orthogonal(d, I, J)) {
@@ -363,26 +949,16 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
   const double small = small_norm2(d);
   unsigned nrot_local = 0;  // rotations applied by this thread (profiling)
 
-  for (int e = tid; e < PW * PW; e += EIG_THREADS) {
-    const int r = e / PW, c = e % PW;
-    // upper entries lie in the upper 16x16 tiles that the Gram kernels store
-    if (r <= c) {
-      double2 sm = make_double2(0.0, 0.0);
-      for (int kc = 0; kc < ksplit; kc++) {
-        const double2 v = d.Gp[((size_t)kc * d.gpStride + pairIdx) * (PW * PW) + e];
-        sm.x += v.x;
-        sm.y += v.y;
-      }
-      if (r < c)
-        Gs[r * LDG + c] = sm;
-      else
-        dg[r] = sm.x;
-    }
-  }
-  const int lane = tid & 63, vrow0 = (tid >> 6) * EIG_VROWS;
-  double2 vr[EIG_VROWS];  // V[vrow0 + h][lane]
+  pair_gram<EIGF_THREADS>(d, I, J, 0, pairIdx, ksplit, [&](int r, int c, double2 x) {
+    if (r < c)
+      Gs[r * LDG + c] = x;
+    else
+      dg[r] = x.x;
+  });
+  const int lane = tid & 63, vrow0 = (tid >> 6) * EIGF_VROWS;
+  double2 vr[EIGF_VROWS];  // V[vrow0 + h][lane]
 #pragma unroll
-  for (int h = 0; h < EIG_VROWS; h++) vr[h] = make_double2(vrow0 + h == lane ? 1.0 : 0.0, 0.0);
+  for (int h = 0; h < EIGF_VROWS; h++) vr[h] = make_double2(vrow0 + h == lane ? 1.0 : 0.0, 0.0);
   if (tid == 0) first_rot = 0;
   __syncthreads();
 
@@ -398,7 +974,7 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
     int act = 0;
     if (tid < PW / 2) {
       int p, q;
-      eig_pair(r, tid, p, q);
+      eigf_pair(r, tid, p, q);
       const double a = dg[p], bb = dg[q];
       const int gs = gslot(p, q);
       const double2 g = p < q ? Gs[gs] : cconj(Gs[gs]);
@@ -427,7 +1003,7 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
   // this thread's off-diagonal block: the upper triangle of 32 x 32 pair
   // indices folded into 16 rows of 31 (row a with row 31 - a)
   int bi = 0, bj = 0;
-  if (tid < EIG_OFFD) {
+  if (tid < EIGF_OFFD) {
     const int a = tid / (PW / 2 - 1), col = tid - (PW / 2 - 1) * a;
     if (col < PW / 2 - 1 - a) {
       bi = a;
@@ -445,14 +1021,14 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
     for (int r = 0; r < PW - 1; r++) {
       const int b = r & 1;
       const bool any = anyr[b] != 0;
-      if (any && tid < EIG_OFFD) {
+      if (any && tid < EIGF_OFFD) {
         // R = [[c, s e^{i phi}], [-s e^{-i phi}, c]] on columns (p, q);
         // block (row pair i, column pair j): B <- R_i^H B R_j.  A pair that
         // does not rotate has c = 1, s = 0, which leaves its entries exactly
         // as they are, so every block is updated without branches.
         int pi, qi, pj, qj;
-        eig_pair(r, bi, pi, qi);
-        eig_pair(r, bj, pj, qj);
+        eigf_pair(r, bi, pi, qi);
+        eigf_pair(r, bj, pj, qj);
         const int s00 = gslot(pi, pj), s01 = gslot(pi, qj), s10 = gslot(qi, pj), s11 = gslot(qi, qj);
         double2 b00 = Gs[s00], b01 = Gs[s01], b10 = Gs[s10], b11 = Gs[s11];
         if (pi > pj) b00 = cconj(b00);
@@ -514,7 +1090,7 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
         const double2 se = rse[b][k];
         const double2 kap = isp ? make_double2(-se.x, se.y) : se;
 #pragma unroll
-        for (int h = 0; h < EIG_VROWS; h++) {
+        for (int h = 0; h < EIGF_VROWS; h++) {
           const double2 x = vr[h];
           const double2 y = make_double2(__shfl(x.x, partner, 64), __shfl(x.y, partner, 64));
           vr[h] = cadd(cscale(x, c), cmul(kap, y));
@@ -550,8 +1126,18 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
   if (first_rot) {
     double2 *V = d.V + (size_t)pairIdx * (PW * PW);
 #pragma unroll
-    for (int h = 0; h < EIG_VROWS; h++) V[(vrow0 + h) * PW + lane] = vr[h];
+    for (int h = 0; h < EIGF_VROWS; h++) V[(vrow0 + h) * PW + lane] = vr[h];
   }
+}
+
+void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,
+                bool cross, bool full) {
+  if (ng <= 0) return;
+  if (cross)
+    hipLaunchKernelGGL(k_eig, dim3(max_pairs, ng), dim3(EIG_THREADS), 0, st, d, round, ksplit);
+  if (full)
+    hipLaunchKernelGGL(k_eig_full, dim3(max_pairs, ng), dim3(EIGF_THREADS), 0, st, d, round,
+                       ksplit);
 }
 
 // ---------------------------------------------------------------- apply a pair rotation
@@ -681,16 +1267,15 @@ __global__ __launch_bounds__(256, 2) void k_rot_mfma3(const GateDesc *descs, int
   }
 }
 
-void launch_gram(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs,
-                 int ksplit) {
+void launch_gram(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,
+                 bool cross, bool full) {
   if (ng <= 0) return;
-  hipLaunchKernelGGL(k_gram_mfma2, dim3(max_pairs * ksplit, ng), dim3(256), 0, st, d, round,
-                     ksplit);
-}
-
-void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit) {
-  if (ng <= 0) return;
-  hipLaunchKernelGGL(k_eig, dim3(max_pairs, ng), dim3(EIG_THREADS), 0, st, d, round, ksplit);
+  if (round == 0 || full)
+    hipLaunchKernelGGL(k_gram_mfma2, dim3(max_pairs * ksplit, ng), dim3(256), 0, st, d, round,
+                       ksplit);
+  if (round > 0 && cross)
+    hipLaunchKernelGGL(k_gram_cross, dim3(max_pairs * ksplit, ng), dim3(256), 0, st, d, round,
+                       ksplit);
 }
 
 // Copy every gate's scalars into one array (one device-to-host copy per sweep).

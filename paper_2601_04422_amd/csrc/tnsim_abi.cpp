@@ -32,7 +32,7 @@ struct Layout {
   size_t dims_off = 0, site_tab_off = 0, lam_tab_off = 0;
   int cmax = 0, ldx_max = 0, cols_pad_max = 0, npairs_max = 0, gp_blocks = 0;
   size_t slot_bytes = 0, slot0_off = 0;
-  size_t x_off = 0, j_off = 0, t_off = 0, v_off = 0, pf_off = 0, ver_off = 0, seen_off = 0,
+  size_t x_off = 0, j_off = 0, t_off = 0, v_off = 0, dg_off = 0, pf_off = 0, ver_off = 0, seen_off = 0,
          sig_off = 0, perm_off = 0, sc_off = 0, u_off = 0, tq_off = 0;  // within a slot
   size_t gp_off = 0;  // pooled pair-Gram partials
   size_t desc_off = 0, desc2_off = 0, d1_off = 0, ctr_off = 0, scg_off = 0;
@@ -113,6 +113,8 @@ Layout make_layout(const tnsim_config &c) {
   s = align_up(s + sizeof(double2) * (size_t)L.cmax * L.cmax);
   L.v_off = s;
   s = align_up(s + sizeof(double2) * (size_t)L.npairs_max * PW * PW);
+  L.dg_off = s;
+  s = align_up(s + sizeof(double2) * 2 * (size_t)L.npairs_max * BW * BW);
   L.pf_off = s;
   s = align_up(s + sizeof(int) * L.npairs_max);
   L.ver_off = s;
@@ -274,7 +276,7 @@ struct tnsim_mps_s {
   int tune_rot_rows[TNSIM_TUNE_BUCKETS] = {0, 0, 0, 0};  // autotuned, 0 = built-in rule
   int tune_gram_ks[TNSIM_TUNE_BUCKETS] = {0, 0, 0, 0};   // autotuned, 0 = built-in rule
   hipGraphExec_t sweep_exec = nullptr;
-  long long sweep_key[7] = {-1, -1, -1, -1, -1, -1, -1};
+  long long sweep_key[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
   int64_t sw_gates = 0, sw_sum = 0;
   int sw_max = 0;
   std::vector<hipEvent_t> evpool;
@@ -437,6 +439,14 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   d.chiMax = h->cfg.chi_max;
   d.storage = h->cfg.storage;
   d.tfp32 = o->cfg.precision != TNSIM_FP64;
+  // Pair solves in the order of all 2016 column pairs: with one pair of
+  // column blocks, where the passes would all fall on it (192 rounds a sweep
+  // instead of 63: 2.25 -> 2.33 ms a gate at chi = 24); and with complex64
+  // sites.  Another order of rotations gives singular vectors with other
+  // phases; stored in complex64 these round differently, which moves the
+  // state's norm by 1e-7, so such handles keep the order, and with it the
+  // states they store bit for bit.  In complex128 the same change is 1e-15.
+  d.fullOrder = d.nblk == 2 || d.storage != TNSIM_STORE_C128;
   d.innerSweeps = o->inner_sweeps;
   // default Jacobi tolerance: float64 level for complex128 sites; for
   // complex64 sites 2^-30, a factor 64 below the rounding of the stored
@@ -466,6 +476,7 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   }
   d.T = sl + L.t_off;
   d.V = (double2 *)(sl + L.v_off);
+  d.Dg = (double2 *)(sl + L.dg_off);
   d.pairFlag = (int *)(sl + L.pf_off);
   d.blkVer = o->pair_skip ? (int *)(sl + L.ver_off) : nullptr;
   d.pairSeen = o->pair_skip ? (int2 *)(sl + L.seen_off) : nullptr;
@@ -570,6 +581,7 @@ struct SweepRunner {
   tnsim_mps o;
   struct Plan {
     int na = 0, maxPairs = 0, maxNblk = 0, maxRows = 0, maxMtrans = 0, ksplit = 1, rotRows = 256;
+    bool cross = false, full = false;  // gates without and with fullOrder
   } P;
 
   tnsim_status plan(const std::vector<const GateDesc *> &D, const std::vector<tnsim_mps> &hs) {
@@ -580,6 +592,7 @@ struct SweepRunner {
       P.maxNblk = std::max(P.maxNblk, d->nblk);
       P.maxRows = std::max(P.maxRows, d->rows);
       if (d->trans) P.maxMtrans = std::max(P.maxMtrans, d->m);
+      (d->fullOrder ? P.full : P.cross) = true;
     }
     const int pairs = P.na * P.maxPairs;
     const int tuned_ks = o->tune_gram_ks[tune_bucket(pairs)];
@@ -628,11 +641,11 @@ struct SweepRunner {
     for (int r = 0; r < P.maxNblk - 1; r++) {
       {
         ProfScope p(h, TNSIM_K_GRAM);
-        launch_gram(st, ddev, P.na, r, P.maxPairs, P.ksplit);
+        launch_gram(st, ddev, P.na, r, P.maxPairs, P.ksplit, P.cross, P.full);
       }
       {
         ProfScope p(h, TNSIM_K_EIG);
-        launch_eig(st, ddev, P.na, r, P.maxPairs, P.ksplit);
+        launch_eig(st, ddev, P.na, r, P.maxPairs, P.ksplit, P.cross, P.full);
       }
       {
         ProfScope p(h, TNSIM_K_ROT);
@@ -647,8 +660,8 @@ struct SweepRunner {
   tnsim_status graph() {
     tnsim_mps h = o;
     hipStream_t st = o->stream;
-    const long long key[7] = {P.na, P.maxPairs, P.ksplit, P.maxNblk, P.maxRows, P.maxMtrans,
-                              P.rotRows};
+    const long long key[8] = {P.na,      P.maxPairs,  P.ksplit,  P.maxNblk,
+                              P.maxRows, P.maxMtrans, P.rotRows, 2 * P.cross + P.full};
     if (h->sweep_exec && memcmp(key, h->sweep_key, sizeof key) == 0) return TNSIM_OK;
     if (h->sweep_exec) {
       hipGraphExecDestroy(h->sweep_exec);
@@ -2858,6 +2871,7 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
   // zeroed, every pair flagged for rotation, V zeroed.
   const int cols = L.cols_pad_max, rows = L.cmax;
   const int npairs = cols / PW;
+  const bool full = L.storage != TNSIM_STORE_C128 || npairs == 1;
   const int want[TNSIM_TUNE_BUCKETS] = {32, 128, 512, 1600};
   const int cand[4] = {64, 128, 256, 512};
   std::vector<GateDesc> D(L.nslots);
@@ -2872,6 +2886,8 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
     d.ldx = L.ldx_max;
     d.colsPad = cols;
     d.nblk = cols / BW;
+    d.storage = L.storage;
+    d.fullOrder = full;
     d.X = (double2 *)(sl + L.x_off);
     d.V = (double2 *)(sl + L.v_off);
     d.pairFlag = (int *)(sl + L.pf_off);
@@ -2930,9 +2946,10 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
       memcpy(h->pin, D.data(), sizeof(GateDesc) * ng);
       HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(GateDesc) * ng, hipMemcpyHostToDevice,
                                h->stream));
-      launch_gram(h->stream, ddev, ng, 0, npairs, ks);  // warm-up
+      launch_gram(h->stream, ddev, ng, 1 % (2 * npairs - 1), npairs, ks, !full, full);  // warm-up
       HIPCHK(h, hipEventRecord(e0, h->stream));
-      for (int r = 0; r < 3; r++) launch_gram(h->stream, ddev, ng, r, npairs, ks);
+      for (int r = 1; r < 4; r++)
+        launch_gram(h->stream, ddev, ng, r % (2 * npairs - 1), npairs, ks, !full, full);
       HIPCHK(h, hipEventRecord(e1, h->stream));
       LAUNCHCHK(h, "autotune");
       HIPCHK(h, hipEventSynchronize(e1));

@@ -49,6 +49,8 @@ struct GateDesc {
   int tfp32;             // theta' stored as complex64 (mixed modes)
   int innerSweeps;       // sweep cap of the 64x64 pair solve
   int gpStride;          // pair blocks per K-split chunk in Gp
+  int fullOrder;         // 1: every pair solve visits all 2016 column pairs of a Gram computed
+                         // afresh (k_eig_full), 0: the passes of k_eig
   int rotRows;           // rows of X (and J) per rotation workgroup, a multiple of 64
   int *dimsDev;          // device bond dimensions of the gate's state (n+1)
   double tol;            // relative off-diagonal tolerance
@@ -61,6 +63,8 @@ struct GateDesc {
   double2 *X, *J;        // Jacobi matrix, accumulated left vectors (trans only)
   void *T;               // theta' (m x n, row-major)
   double2 *Gp, *V;       // pair Gram partials, pair rotations
+  double2 *Dg;           // per column block: its own Gram (upper triangle of 32x32) as its
+                         // last pair solve left it
   int *pairFlag;         // pair rotated in this round
   int *blkVer;           // per column block: number of rotations applied to it so far
   int2 *pairSeen;        // per block pair (I * nblk + J): block versions when the pair
@@ -112,9 +116,11 @@ void launch_theta(hipStream_t st, const GateDesc *d, int ng, int precision, int 
 void launch_colnorm(hipStream_t st, const GateDesc *d, int ng, int max_cols);
 void launch_gate_init(hipStream_t st, const GateDesc *d, int ng);
 void launch_begin_sweep(hipStream_t st, const GateDesc *d, int ng);
-void launch_gram(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs,
-                 int ksplit);
-void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit);
+// full, cross: the batch holds gates with fullOrder set, or without
+void launch_gram(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,
+                 bool cross, bool full);
+void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,
+                bool cross, bool full);
 void launch_gather_sc(hipStream_t st, const GateDesc *d, int ng, SlotScalars *out);
 void launch_rot(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs,
                 int max_rows, int max_m, int rot_rows);
