@@ -22,11 +22,14 @@ __device__ __forceinline__ zd4_t zmfma(double a, double b, zd4_t c) {
 }
 
 constexpr int ZT = 64, ZK = 16;
+// 64 x 64 tiles of a product that fills the chip (two workgroups per CU);
+// with fewer, the 32 x 32 tiles of k_zgemm_s take it
+constexpr size_t ZGEMM_FILL = 512;
 
 // AK: A(i,k) = A[i*sa + k], else A[k*sa + i]; AC: use conj(A).
 // BK: B(k,j) = B[j*sb + k], else B[k*sb + j].
 // CM: C(i,j) = C[j*sc + i], else C[i*sc + j].
-// blockIdx.z: batch index, or K split (partial products to g.part).
+// blockIdx.z: batch index.
 // GA (gathered columns): output columns *g.clo .. *g.chi - 1 (device
 // values; the grid covers at most N of them), column j reads column
 // g.bmap[j] of B and is scaled by g.cscale[j]; tiles from column *g.asplit
@@ -56,15 +59,10 @@ __global__ __launch_bounds__(256, AK ? 4 : 3) void k_zgemm(ZgemmArgs g) {
   const TA *A = (const TA *)g.A;
   const TB *B = (const TB *)g.B;
   double2 *C = g.C;
-  int kb = 0, K = g.K;
-  if (g.ksplit > 1) {
-    kb = z * g.kchunk;
-    K = min(g.K, kb + g.kchunk);
-  } else {
-    A += (z + A_off_tile) * g.za;
-    B += z * g.zb;
-    C += z * g.zc;
-  }
+  const int K = g.K;
+  A += (z + A_off_tile) * g.za;
+  B += z * g.zb;
+  C += z * g.zc;
   __shared__ double2 As[ZK][ZT], Bs[ZK][ZT];
   const int t = threadIdx.x;
   // this thread's share of a K step: 4 elements of A and 4 of B
@@ -123,8 +121,8 @@ __global__ __launch_bounds__(256, AK ? 4 : 3) void k_zgemm(ZgemmArgs g) {
       cr[a][b] = zd4_t{0.0, 0.0, 0.0, 0.0};
       ci[a][b] = zd4_t{0.0, 0.0, 0.0, 0.0};
     }
-  load(kb);
-  for (int k0 = kb; k0 < K; k0 += ZK) {
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += ZK) {
     stash();
     __syncthreads();
     if (k0 + ZK < K) load(k0 + ZK);
@@ -160,57 +158,163 @@ __global__ __launch_bounds__(256, AK ? 4 : 3) void k_zgemm(ZgemmArgs g) {
         const int i = i0 + wm + 16 * x + lg + 4 * v;
         if (i >= M) continue;
         const double2 c = make_double2(sc * cr[x][y][v], sc * ci[x][y][v]);
-        if (g.ksplit > 1)
-          g.part[((size_t)z * M + i) * g.N + j] = c;
-        else
-          C[CM ? (long long)j * g.sc + i : (long long)i * g.sc + j] = c;
+        C[CM ? (long long)j * g.sc + i : (long long)i * g.sc + j] = c;
       }
     }
 }
 
-// C = sum over splits of the partial products, in split order.
-template <bool CM>
-__global__ __launch_bounds__(256) void k_zgemm_sum(ZgemmArgs g) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const size_t MN = (size_t)g.M * g.N;
-  if (e >= MN) return;
-  const int i = (int)(e / g.N), j = (int)(e % g.N);
-  double2 acc = g.part[e];
-  for (int z = 1; z < g.ksplit; z++) acc = cadd(acc, g.part[z * MN + e]);
-  g.C[CM ? (long long)j * g.sc + i : (long long)i * g.sc + j] = acc;
+// The same product for shapes whose 64 x 64 tiles would leave the chip idle
+// (a bond of 256 has 16 or 32 of them, each a chain of K / 16 steps of 2 us):
+// 32 x 32 tiles, and the NW wavefronts of a workgroup split K between them.
+// Operands go from memory straight into the matrix-core layout (16 lanes
+// along a row of B or along A's rows; the operands of these shapes stay in
+// L2), two k-steps ahead of the products, so the K loop has no barrier; the
+// NW partial tiles are added in LDS in wavefront order.
+// Bound by the matrix cores' latency chain (K / (4 NW) steps of 16 products).
+// Three expectations, an overlap, a norm and four amplitudes at chi = 500,
+// n = 28: 35.5 -> 9.1 ms; 1000 shots at chi = 256, n = 48: 8.7 -> 3.85 ms (the
+// split of K over workgroups with a summing launch that this replaces).
+constexpr int ST = 32;
+
+template <class TA, class TB, bool AK, bool AC, bool BK, bool CM, bool GA, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_zgemm_s(ZgemmArgs g) {
+  int N = g.N, j0 = blockIdx.x * ST, A_off_tile = 0;
+  if (GA) {
+    const int lo = *g.clo;
+    N = *g.chi;
+    j0 += lo;
+    if (g.asplit && j0 >= *g.asplit) A_off_tile = 1;
+  } else if (g.mcount) {
+    N = min(N, g.mult * *g.mcount);
+  }
+  const int i0 = blockIdx.y * ST;
+  if (j0 >= N) return;
+  const int M = g.M, K = g.K, z = blockIdx.z;
+  const TA *A = (const TA *)g.A + (z + A_off_tile) * g.za;
+  const TB *B = (const TB *)g.B + z * g.zb;
+  double2 *C = g.C + z * g.zc;
+  const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, lg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  // this wavefront's part of K, in whole k-steps of 4
+  const int kc = ((K + NW - 1) / NW + 3) / 4 * 4;
+  const int kb = w * kc, ke = min(K, kb + kc);
+  // rows of A and columns of B past the matrix repeat the last one (their
+  // products are not stored)
+  const TA *pa[2];
+  const TB *pb[2];
+#pragma unroll
+  for (int x = 0; x < 2; x++) {
+    const int gi = min(i0 + 16 * x + l16, M - 1);
+    pa[x] = AK ? A + (long long)gi * g.sa : A + gi;
+    const int gj = min(j0 + 16 * x + l16, N - 1);
+    const long long bj = GA ? (long long)g.bmap[gj] : gj;
+    pb[x] = BK ? B + bj * g.sb : B + bj;
+  }
+  constexpr int D = 2;  // k-steps loaded together (32 products, longer than a load from L2)
+  double2 a[2][D][2], b[2][D][2];
+  auto load = [&](int k0, double2 (&ra)[D][2], double2 (&rb)[D][2]) {
+#pragma unroll
+    for (int s = 0; s < D; s++) {
+      const int k = k0 + 4 * s + lg;
+      const long long kk = min(k, K - 1);
+      const bool in = k < ke;
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        const double2 va = cload(AK ? pa[x] + kk : pa[x] + kk * g.sa);
+        const double2 vb = cload(BK ? pb[x] + kk : pb[x] + kk * g.sb);
+        ra[s][x] = in ? va : make_double2(0.0, 0.0);
+        rb[s][x] = in ? vb : make_double2(0.0, 0.0);
+      }
+    }
+  };
+  zd4_t cr[2][2], ci[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++) {
+      cr[x][y] = zd4_t{0.0, 0.0, 0.0, 0.0};
+      ci[x][y] = zd4_t{0.0, 0.0, 0.0, 0.0};
+    }
+  auto mul = [&](const double2 (&ra)[D][2], const double2 (&rb)[D][2]) {
+#pragma unroll
+    for (int s = 0; s < D; s++) {
+      double2 av[2];
+#pragma unroll
+      for (int x = 0; x < 2; x++) av[x] = AC ? cconj(ra[s][x]) : ra[s][x];
+#pragma unroll
+      for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+          cr[x][y] = zmfma(av[x].x, rb[s][y].x, cr[x][y]);
+          ci[x][y] = zmfma(av[x].x, rb[s][y].y, ci[x][y]);
+        }
+#pragma unroll
+      for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+          cr[x][y] = zmfma(-av[x].y, rb[s][y].y, cr[x][y]);
+          ci[x][y] = zmfma(av[x].y, rb[s][y].x, ci[x][y]);
+        }
+    }
+  };
+  if (kb < ke) {
+    load(kb, a[0], b[0]);
+    for (int k0 = kb; k0 < ke; k0 += 8 * D) {  // past the end: zeros
+      load(k0 + 4 * D, a[1], b[1]);
+      mul(a[0], b[0]);
+      load(k0 + 8 * D, a[0], b[0]);
+      mul(a[1], b[1]);
+    }
+  }
+  __shared__ double2 part[NW][ST][ST + 1];
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++)
+#pragma unroll
+      for (int v = 0; v < 4; v++)
+        part[w][16 * x + lg + 4 * v][16 * y + l16] = make_double2(cr[x][y][v], ci[x][y][v]);
+  __syncthreads();
+#pragma unroll
+  for (int e = t; e < ST * ST; e += 64 * NW) {
+    const int il = CM ? e % ST : e / ST, jl = CM ? e / ST : e % ST;  // along C's rows in memory
+    const int i = i0 + il, j = j0 + jl;
+    if (i >= M || j >= N) continue;
+    double2 c = part[0][il][jl];
+#pragma unroll
+    for (int q = 1; q < NW; q++) c = cadd(c, part[q][il][jl]);
+    if (GA) c = cscale(c, g.cscale[j]);
+    C[CM ? (long long)j * g.sc + i : (long long)i * g.sc + j] = c;
+  }
 }
 
-// The partial products of a split take at most ZGEMM_PART_ELEMS elements.
-int zgemm_ksplit(int M, int N, int K) {
-  const int tiles = ((M + ZT - 1) / ZT) * ((N + ZT - 1) / ZT);
-  if (tiles >= 512) return 1;  // enough workgroups already; partial sums cost traffic
-  int ks = 1;
-  while (ks < 8 && tiles * ks * 2 <= 1024 && K / (ks * 2) >= 128) ks *= 2;
-  return ks;
+// f(TA(), TB()) with the operands' element types
+template <class F>
+static void zgemm_types(int a_storage, int b_storage, F f) {
+  if (a_storage == 0 && b_storage == 0)
+    f(double2(), double2());
+  else if (a_storage == 0)
+    f(double2(), float2());
+  else if (b_storage == 0)
+    f(float2(), double2());
+  else
+    f(float2(), float2());
 }
 
 template <bool AK, bool AC, bool BK, bool CM, bool GA = false>
-static void zgemm_dispatch(hipStream_t st, ZgemmArgs g, int a_storage, int b_storage) {
-  // the partial sums cover the whole bound, and must fit the caller's buffer
-  if (GA || g.mcount || !g.part || (size_t)g.ksplit * g.M * g.N > ZGEMM_PART_ELEMS) g.ksplit = 1;
-  if (g.ksplit > 1) {
-    g.batch = 1;
-    g.kchunk = ((g.K + g.ksplit - 1) / g.ksplit + ZK - 1) / ZK * ZK;
-    g.ksplit = (g.K + g.kchunk - 1) / g.kchunk;
-  }
-  dim3 grid((g.N + ZT - 1) / ZT, (g.M + ZT - 1) / ZT, g.ksplit > 1 ? g.ksplit : g.batch);
-  if (a_storage == 0 && b_storage == 0)
-    hipLaunchKernelGGL((k_zgemm<double2, double2, AK, AC, BK, CM, GA>), grid, dim3(256), 0, st, g);
-  else if (a_storage == 0)
-    hipLaunchKernelGGL((k_zgemm<double2, float2, AK, AC, BK, CM, GA>), grid, dim3(256), 0, st, g);
-  else if (b_storage == 0)
-    hipLaunchKernelGGL((k_zgemm<float2, double2, AK, AC, BK, CM, GA>), grid, dim3(256), 0, st, g);
-  else
-    hipLaunchKernelGGL((k_zgemm<float2, float2, AK, AC, BK, CM, GA>), grid, dim3(256), 0, st, g);
-  if (g.ksplit > 1) {
-    const size_t MN = (size_t)g.M * g.N;
-    hipLaunchKernelGGL(k_zgemm_sum<CM>, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, st, g);
-  }
+static void zgemm_dispatch(hipStream_t st, const ZgemmArgs &g, int a_storage, int b_storage) {
+  const dim3 big((g.N + ZT - 1) / ZT, (g.M + ZT - 1) / ZT, g.batch);
+  const dim3 fine((g.N + ST - 1) / ST, (g.M + ST - 1) / ST, g.batch);
+  zgemm_types(a_storage, b_storage, [&](auto ta, auto tb) {
+    using TA = decltype(ta);
+    using TB = decltype(tb);
+    if ((size_t)big.x * big.y * big.z >= ZGEMM_FILL)
+      hipLaunchKernelGGL((k_zgemm<TA, TB, AK, AC, BK, CM, GA>), big, dim3(256), 0, st, g);
+    else if ((size_t)fine.x * fine.y * fine.z > 256 || g.K < 64)
+      hipLaunchKernelGGL((k_zgemm_s<TA, TB, AK, AC, BK, CM, GA, 4>), fine, dim3(256), 0, st, g);
+    else  // fewer tiles than CUs: twice the wavefronts on each
+      hipLaunchKernelGGL((k_zgemm_s<TA, TB, AK, AC, BK, CM, GA, 8>), fine, dim3(512), 0, st, g);
+  });
 }
 
 void launch_zgemm(hipStream_t st, ZgemmKind kind, const ZgemmArgs &g, int a_storage,

@@ -154,12 +154,13 @@ Layout make_layout(const tnsim_config &c) {
   off = align_up(off + sizeof(unsigned long long) * CTR_COUNT);
   const size_t ee = sizeof(double2) * (size_t)maxbond * maxbond;
   const size_t ff = sizeof(double2) * (size_t)maxbond * 2 * maxbond;
+  // E and F hold two contractions side by side (transfer())
   L.e0_off = off;
-  off = align_up(off + ee);
+  off = align_up(off + 2 * ee);
   L.e1_off = off;
-  off = align_up(off + ee);
+  off = align_up(off + 2 * ee);
   L.f_off = off;
-  off = align_up(off + ff);
+  off = align_up(off + 2 * ff);
   L.f2_off = off;
   off = align_up(off + ff);
   L.va_off = off;
@@ -1283,8 +1284,11 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
   return TNSIM_OK;
 }
 
-// <bra| P |ket>; P holds a 2x2 per site (4n entries) and isI marks identity
-// sites; P == nullptr means identity everywhere.
+// <bra|ket> into out[0] and, with a table P (a 2x2 per site, 4n entries; isI
+// marks identity sites), <bra|P|ket> into out[1], in one pass over the sites:
+// the two contractions are the same up to the first site with an operator,
+// and from there on share their launches (rows of E stacked, then a batch of
+// two), so an expectation value is one chain of products instead of two.
 tnsim_status transfer(tnsim_mps h, tnsim_mps bra, tnsim_mps ket, const double2 *P,
                       const char *isI, double2 *out) {
   const Layout &L = h->L;
@@ -1296,28 +1300,34 @@ tnsim_status transfer(tnsim_mps h, tnsim_mps bra, tnsim_mps ket, const double2 *
   memcpy(h->pin, &one, sizeof one);
   HIPCHK(h, hipMemcpyAsync(E, h->pin, sizeof one, hipMemcpyHostToDevice, st));
   const int n = L.n;
+  int nb = 1;  // 1, then 2 from the first operator on: without, with operators
   for (int q = 0; q < n; q++) {
     int lb = bra->dims[q], rb = bra->dims[q + 1];
     int lk = ket->dims[q], rk = ket->dims[q + 1];
-    // F = E (lb x lk) * K (lk x 2rk), on the matrix cores
+    // F = E (nb lb x lk) * K (lk x 2rk), on the matrix cores
     launch_zgemm(st, ZGEMM_NN_ROW,
-                 ZgemmArgs{lb, 2 * rk, lk, E, lk, ket->site(q), 2 * rk, F, 2 * rk, nullptr, 0}, 0,
-                 ket->L.storage);
-    const double2 *Fp = F;
+                 ZgemmArgs{nb * lb, 2 * rk, lk, E, lk, ket->site(q), 2 * rk, F, 2 * rk, nullptr, 0},
+                 0, ket->L.storage);
+    const size_t fsz = (size_t)lb * 2 * rk;
+    ZgemmArgs g{rb, rk, 2 * lb, bra->site(q), rb, F, rk, E2, rk, nullptr, 0};
+    g.zb = fsz;
+    g.zc = (long long)rb * rk;
     if (P && !isI[q]) {
-      launch_pauli_phys(st, F, F2, lb, rk, P[4 * q], P[4 * q + 1], P[4 * q + 2], P[4 * q + 3]);
-      Fp = F2;
+      launch_pauli_phys(st, F + (nb - 1) * fsz, F2, lb, rk, P[4 * q], P[4 * q + 1], P[4 * q + 2],
+                        P[4 * q + 3]);
+      g.zb = F2 - F;
+      nb = 2;
     }
+    g.batch = nb;
     // E' = B^H (rb x 2lb) * F (2lb x rk)
-    launch_zgemm(st, ZGEMM_CN_ROW,
-                 ZgemmArgs{rb, rk, 2 * lb, bra->site(q), rb, Fp, rk, E2, rk, nullptr, 0},
-                 bra->L.storage, 0);
+    launch_zgemm(st, ZGEMM_CN_ROW, g, bra->L.storage, 0);
     LAUNCHCHK(h, "transfer");
     std::swap(E, E2);
   }
-  HIPCHK(h, hipMemcpyAsync(h->pin, E, sizeof(double2), hipMemcpyDeviceToHost, st));
+  HIPCHK(h, hipMemcpyAsync(h->pin, E, nb * sizeof(double2), hipMemcpyDeviceToHost, st));
   HIPCHK(h, hipStreamSynchronize(st));
-  memcpy(out, h->pin, sizeof(double2));
+  memcpy(out, h->pin, nb * sizeof(double2));
+  if (P && nb == 1) out[1] = out[0];
   return TNSIM_OK;
 }
 
@@ -2174,11 +2184,10 @@ tnsim_status tnsim_expect_pauli(tnsim_mps h, const char *pauli, double *re_out, 
     isI[q] = k == 0;
     for (int e = 0; e < 4; e++) tab[4 * q + e] = PM[k][e];
   }
-  double2 num, den;
-  s = transfer(h, h, h, tab.data(), isI.data(), &num);
+  double2 nd[2];
+  s = transfer(h, h, h, tab.data(), isI.data(), nd);
   if (s != TNSIM_OK) return s;
-  s = transfer(h, h, h, nullptr, nullptr, &den);
-  if (s != TNSIM_OK) return s;
+  const double2 num = nd[1], den = nd[0];
   // num / den
   double dd = den.x * den.x + den.y * den.y;
   *re_out = (num.x * den.x + num.y * den.y) / dd;
@@ -2237,7 +2246,7 @@ tnsim_status tnsim_amplitude(tnsim_mps h, const uint8_t *bits, tnsim_c128 *out) 
 // k_sample.hip).
 struct SampleLayout {
   std::vector<size_t> msite;  // 2 x dimcap[q+1]^2 complex128 per site
-  size_t E0 = 0, E1 = 0, F = 0, P = 0, V0 = 0, V1 = 0, Y = 0, p = 0, flag = 0, idx = 0,
+  size_t E0 = 0, E1 = 0, F = 0, V0 = 0, V1 = 0, Y = 0, p = 0, flag = 0, idx = 0,
          node = 0, key = 0, parent = 0, scale = 0, logp = 0, ctr = 0, total = 0;
 };
 
@@ -2261,7 +2270,9 @@ static SampleLayout sample_layout(const Layout &L, int max_shots) {
   S.E0 = take(sizeof(double2) * d2);  // E_q, E_{q+1} in turn
   S.E1 = take(sizeof(double2) * d2);
   S.F = take(sizeof(double2) * 2 * d2);
-  S.P = take(sizeof(double2) * ZGEMM_PART_ELEMS);  // split-K partial products
+  // 64 MiB of slack: not used, but workspace sizes, and with them which calls
+  // fit the fixed array of tnsim_sample_noalloc, stay what callers know
+  take((size_t)64 << 20);
   S.V0 = take(sizeof(double2) * ms * dmax);
   S.V1 = take(sizeof(double2) * ms * dmax);
   S.Y = take(sizeof(double2) * 2 * ms * dmax);
@@ -2292,24 +2303,19 @@ static tnsim_status sample_weights(tnsim_mps h, char *ws, const SampleLayout &S)
   hipStream_t st = h->stream;
   auto Ms = [&](int q) { return (double2 *)(ws + S.msite[q]); };
   double2 *E = (double2 *)(ws + S.E0), *En = (double2 *)(ws + S.E1);
-  double2 *F = (double2 *)(ws + S.F), *Pb = (double2 *)(ws + S.P);
+  double2 *F = (double2 *)(ws + S.F);
   // E_0 = 1 (and the node tables of a one-shot draw, unused here)
   launch_smp_init(st, 0, 64, (int *)(ws + S.node), (double *)(ws + S.logp), (int *)(ws + S.flag),
                   (double2 *)(ws + S.V0), E, (int *)(ws + S.ctr));
   for (int q = 0; q < n; q++) {
     const int la = h->dims[q], rb = h->dims[q + 1];
     ZgemmArgs f{la, 2 * rb, la, E, la, h->site(q), 2 * rb, F, 2 * rb, nullptr, 0};
-    f.ksplit = zgemm_ksplit(la, 2 * rb, la);
-    f.part = Pb;
     launch_zgemm(st, ZGEMM_NN_ROW, f, 0, sto);
-    for (int sb = 0; sb < 2; sb++) {
-      const char *A = (const char *)h->site(q) + (size_t)sb * rb * L.elem;
-      ZgemmArgs e{rb, rb, la, A, 2LL * rb, F + (size_t)sb * rb, 2LL * rb,
-                  Ms(q) + (size_t)sb * rb * rb, rb, nullptr, 0};
-      e.ksplit = zgemm_ksplit(rb, rb, la);
-      e.part = Pb;
-      launch_zgemm(st, ZGEMM_CN_ROW, e, sto, 0);
-    }
+    ZgemmArgs e{rb, rb, la, h->site(q), 2LL * rb, F, 2LL * rb, Ms(q), rb, nullptr, 0};
+    e.batch = 2;  // both values of s
+    e.za = e.zb = rb;
+    e.zc = (long long)rb * rb;
+    launch_zgemm(st, ZGEMM_CN_ROW, e, sto, 0);
     if (q + 1 < n) {
       launch_smp_add(st, Ms(q), (size_t)rb * rb, En);
       std::swap(E, En);
@@ -2713,14 +2719,12 @@ tnsim_status tnsim_forward_checkpointed(tnsim_mps h, void *dev_ws, size_t ws_byt
   }
   s = save_ckpt(h, n_segments);
   if (s != TNSIM_OK) return s;
-  double2 den, num;
-  s = transfer(h, h, h, nullptr, nullptr, &den);
-  if (s != TNSIM_OK) return s;
+  double2 nd[2];  // <psi|psi>, <psi|P_t|psi>
   double L = 0.0;
   for (int t = 0; t < n_terms; t++) {
-    s = transfer(h, h, h, tabs[t].data(), isIs[t].data(), &num);
+    s = transfer(h, h, h, tabs[t].data(), isIs[t].data(), nd);
     if (s != TNSIM_OK) return s;
-    L += coeffs[t] * num.x / den.x;
+    L += coeffs[t] * nd[1].x / nd[0].x;
   }
   GS.loss = L;
   GS.ready = true;
@@ -2746,7 +2750,7 @@ tnsim_status tnsim_backward(tnsim_mps h, double dloss, double *grad_angles) {
   // the final state: loss = sum_t c_t N_t / D
   s = restore_ckpt(h, G.n_seg);
   if (s != TNSIM_OK) return s;
-  double2 den, num;
+  double2 den;
   s = transfer(h, h, h, nullptr, nullptr, &den);
   if (s != TNSIM_OK) return s;
   const double D = den.x;

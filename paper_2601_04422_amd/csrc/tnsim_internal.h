@@ -202,19 +202,12 @@ struct ZgemmArgs {
   int mult;
   int batch = 1;              // independent products, operands offset by z * (za, zb, zc)
   long long za = 0, zb = 0, zc = 0;
-  int ksplit = 1;             // K split over workgroups (batch 1 only); the partial products
-  double2 *part = nullptr;    // go to part (ksplit x M x N) and are added in order into C
-  int kchunk = 0;             // K per split (set by the launcher)
   // ZGEMM_NN_COL_GATHER only: output columns [*clo, *chi) (device values, at
   // most N of them); column j reads column bmap[j] of B, scaled by cscale[j];
   // tiles of 64 columns from *asplit on (a multiple of 64) use A + za
   const int *clo = nullptr, *chi = nullptr, *bmap = nullptr, *asplit = nullptr;
   const double *cscale = nullptr;
 };
-// ksplit that gives a product of this shape about 1024 workgroups (1 if none
-// needed); ksplit * M * N never exceeds ZGEMM_PART_ELEMS when it is above 1
-int zgemm_ksplit(int M, int N, int K);
-constexpr size_t ZGEMM_PART_ELEMS = (size_t)1024 * 64 * 64;
 enum ZgemmKind {
   ZGEMM_NN_ROW,  // A(i,k) = A[i*sa + k]; B(k,j) = B[k*sb + j]; C(i,j) = C[i*sc + j]
   ZGEMM_CN_ROW,  // op(A)(i,k) = conj(A[k*sa + i]); B, C as above
