@@ -65,6 +65,7 @@ __device__ __forceinline__ bool pair_known_orthogonal(const GateDesc &d, int I, 
 // Zero X's padding columns; J = identity (trans gates).
 __global__ void k_setup_slots(const GateDesc *descs) {
   const GateDesc &d = descs[blockIdx.y];
+  if (d.small) return;
   int col = blockIdx.x;
   if (col < d.colsPad && col >= d.cols) {
     for (int r = threadIdx.x; r < d.ldx; r += blockDim.x)
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(256) void k_colnorm(const GateDesc *descs) {
   const GateDesc &d = descs[blockIdx.y];
   int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int col = blockIdx.x * 4 + wave;
-  if (col >= d.colsPad) return;
+  if (d.small || col >= d.colsPad) return;
   const double2 *x = d.X + (size_t)col * d.ldx;
   double s = 0.0;
   for (int r = lane; r < d.rows; r += 64) s += cabs2(x[r]);
@@ -103,6 +104,7 @@ void launch_colnorm(hipStream_t st, const GateDesc *d, int ng, int max_cols) {
 // orthogonal yet.
 __global__ void k_gate_init(const GateDesc *descs) {
   const GateDesc &d = descs[blockIdx.x];
+  if (d.small) return;
   if (d.blkVer) {
     for (int b = threadIdx.x; b < d.nblk; b += blockDim.x) d.blkVer[b] = 0;
     for (int e = threadIdx.x; e < d.nblk * d.nblk; e += blockDim.x)
@@ -1300,8 +1302,13 @@ void launch_rot(hipStream_t st, const GateDesc *d, int ng, int round, int max_pa
 
 constexpr int SORT_MAX = 4096;
 
-__global__ __launch_bounds__(256) void k_trunc(const GateDesc *descs) {
+// If some gate of the launch has not converged (k_small), none is cut: the
+// call then fails and its sites and Schmidt weights keep their values.
+__global__ __launch_bounds__(256) void k_trunc(const GateDesc *descs, int ng) {
   const GateDesc &d = descs[blockIdx.x];
+  int failed = 0;
+  for (int g = threadIdx.x; g < ng; g += 256) failed |= descs[g].small && descs[g].sc->rot;
+  if (__syncthreads_or(failed)) return;
   __shared__ double key[SORT_MAX];
   __shared__ int idx[SORT_MAX];
   __shared__ double tail[SORT_MAX + 1];
@@ -1380,7 +1387,7 @@ __global__ __launch_bounds__(256) void k_trunc(const GateDesc *descs) {
 
 void launch_trunc(hipStream_t st, const GateDesc *d, int ng) {
   if (ng <= 0) return;
-  hipLaunchKernelGGL(k_trunc, dim3(ng), dim3(256), 0, st, d);
+  hipLaunchKernelGGL(k_trunc, dim3(ng), dim3(256), 0, st, d, ng);
 }
 
 }  // namespace tn

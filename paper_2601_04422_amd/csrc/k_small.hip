@@ -1,0 +1,218 @@
+// Two-qubit gates whose Jacobi matrix fits in the LDS of one workgroup:
+// merge, gate, weight (Sec. III.A, IV.A) and the whole one-sided Jacobi SVD in
+// one launch, one workgroup per gate.
+//
+// The block Jacobi (k_jacobi.hip) takes about 140 us per sweep on such a
+// matrix, nearly all of it launches, the host's convergence test and one pair
+// solve of 63 rounds, whatever the size; a circuit of 10 qubits spent 97% of
+// its time there.  Here the columns of X (X = M, or M^H when M is wide or the
+// caller needs the full left basis, then with J's rows appended below) lie in
+// LDS, and a round rotates all disjoint pairs of the circle method on `cols`
+// columns, 16 lanes per pair: x^H y by row rotations, the rotation, both
+// columns written back, one barrier.  Squared norms are kept with the columns
+// and computed afresh at the start of every sweep, so the last sweep, which
+// rotates nothing, tests against exact norms.
+//
+// Bound by the chain of a round (LDS read, 16-lane sum, rotation parameters,
+// LDS write, barrier).  Ten layers of a 10-qubit circuit: 8.7 -> 2.2 ms; one
+// gate at chi = 24 with its readout: 2.2 -> 1.2 ms; loss and gradient of a
+// 14-qubit ansatz: 75 -> 31 ms.
+#include "tnsim_internal.h"
+#include "tn_complex.h"
+#include "tn_lanes.h"
+
+namespace tn {
+
+// 1 / x and sqrt(x) of normal positive numbers, to rounding (hardware
+// estimate and Newton steps)
+__device__ __forceinline__ double sm_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double sm_rsqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+// sum over the 16 lanes of a row, in every lane
+__device__ __forceinline__ double row_sum(double x) {
+  x += row_next<8>(x);
+  x += row_next<4>(x);
+  x += row_next<2>(x);
+  return x + row_next<1>(x);
+}
+
+template <int THREADS, int ELEMS, int CLASS>
+__global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
+  const GateDesc &d = descs[blockIdx.x];
+  if (d.small != CLASS) return;
+  __shared__ double2 X[ELEMS];       // column c, row r at c * ld + r
+  __shared__ double nrm[64];         // squared column norms
+  __shared__ int rotated;
+  const int tid = threadIdx.x, l = tid & 15, grp = tid >> 4;
+  constexpr int GROUPS = THREADS / 16;
+  const int m = d.m, n = d.n, chiL = d.chiL, chiM = d.chiM, chiR = d.chiR;
+  const int rows = d.rows, cols = d.cols, tot = rows + (d.trans ? m : 0);
+  const int ld = (tot + 15) / 16 * 16;
+
+  // theta' (kept for the write-back) and X
+  for (int e = tid; e < cols * ld; e += THREADS) {
+    const int r = e % ld, c = e / ld;
+    if (r >= rows) X[e] = make_double2(d.trans && r - rows == c ? 1.0 : 0.0, 0.0);
+  }
+  const double2 *A0 = (const double2 *)d.A0, *A1 = (const double2 *)d.A1;
+  double2 *T = (double2 *)d.T;
+  for (int task = tid; task < chiL * chiR; task += THREADS) {
+    const int a = task / chiR, c = task - a * chiR;
+    const double2 *p0 = A0 + (size_t)a * 2 * chiM, *q0 = A1 + c;
+    double2 v[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) v[e] = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int b = 0; b < chiM; b++) {
+      const double2 x0 = p0[b], x1 = p0[chiM + b];
+      const double2 y0 = q0[(size_t)b * 2 * chiR], y1 = q0[(size_t)b * 2 * chiR + chiR];
+      cfma(v[0], x0, y0);
+      cfma(v[1], x0, y1);
+      cfma(v[2], x1, y0);
+      cfma(v[3], x1, y1);
+    }
+    const double w = d.lamR ? d.lamR[c] : 1.0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      double2 o = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int j = 0; j < 4; j++) cfma(o, d.g[e * 4 + j], v[j]);
+      const int r = 2 * a + (e >> 1), t = e & 1;
+      T[(size_t)r * n + t * chiR + c] = o;
+      if (!d.trans)
+        X[(2 * c + t) * ld + r] = cscale(o, w);  // columns in the order (c, t), as the merge
+      else
+        X[r * ld + t * chiR + c] = cscale(cconj(o), w);
+    }
+  }
+  if (tid == 0) rotated = 0;
+  __syncthreads();
+
+  auto norms = [&]() {
+    for (int c = grp; c < cols; c += GROUPS) {
+      double s = 0.0;
+      for (int r = l; r < rows; r += 16) s += cabs2(X[c * ld + r]);
+      s = row_sum(s);
+      if (l == 0) nrm[c] = s;
+    }
+  };
+  norms();
+  __syncthreads();
+  double fro2 = 0.0;
+  for (int c = 0; c < cols; c++) fro2 += nrm[c];
+  const double eps_r = rows * 0x1p-53, small = fro2 * eps_r * eps_r, tol2 = d.tol * d.tol;
+
+  const int P = (cols + 1) & ~1, nt = ld / 16;  // players of the circle method, rows per lane
+  int sweep = 0, rot = 1;
+  while (rot && sweep < d.maxSweeps) {
+    sweep++;
+    for (int r = 0; r < P - 1; r++) {
+      // pair grp of round r
+      int p = -1, q = 0;
+      if (grp < P / 2) {
+        if (grp == 0) {
+          p = r;
+          q = P - 1;
+        } else {
+          p = r + grp;
+          p -= p >= P - 1 ? P - 1 : 0;
+          q = r - grp;
+          q += q < 0 ? P - 1 : 0;
+        }
+        if (p > q) {
+          const int t = p;
+          p = q;
+          q = t;
+        }
+        if (q >= cols) p = -1;  // the odd column out
+      }
+      if (p >= 0) {
+        double2 *xp = X + p * ld + l, *yp = X + q * ld + l;
+        const double a = nrm[p], b = nrm[q];
+        double2 x[SMALL_ROWS / 16], y[SMALL_ROWS / 16];
+        double2 g = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < SMALL_ROWS / 16; i++)
+          if (i < nt) {
+            x[i] = xp[16 * i];
+            y[i] = yp[16 * i];
+          }
+#pragma unroll
+        for (int i = 0; i < SMALL_ROWS / 16; i++)
+          if (16 * i + l < rows) cfmac(g, x[i], y[i]);
+        g = make_double2(row_sum(g.x), row_sum(g.y));
+        const double h = cabs2(g);
+        if (a > small && b > small && h > tol2 * a * b) {
+          // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
+          // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
+          const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
+          const double w = copysign(2.0 * sm_rcp(fabs(delta) + s2 * sm_rsqrt(s2)), delta);
+          const double wh = w * h, c = sm_rsqrt(fma(w, wh, 1.0)), cw = c * w;
+          const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
+#pragma unroll
+          for (int i = 0; i < SMALL_ROWS / 16; i++)
+            if (i < nt) {
+              xp[16 * i] = csub(cscale(x[i], c), cmul(sec, y[i]));
+              yp[16 * i] = cadd(cmul(se, x[i]), cscale(y[i], c));
+            }
+          if (l == 0) {
+            nrm[p] = a - wh;
+            nrm[q] = b + wh;
+            rotated = 1;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    rot = rotated;
+    __syncthreads();
+    if (rot) {
+      if (tid == 0) rotated = 0;
+      norms();
+      __syncthreads();
+    }
+  }
+  // left vectors and squared norms where the truncation and the write-back
+  // (and the adjoint) look for them
+  for (int e = tid; e < cols * ld; e += THREADS) {
+    const int r = e % ld, c = e / ld;
+    if (!d.trans && r < rows) d.X[(size_t)c * d.ldx + r] = X[e];
+    if (d.trans && r >= rows && r < tot) d.J[(size_t)c * d.ldj + r - rows] = X[e];
+  }
+  for (int c = tid; c < cols; c += THREADS) d.sig2[c] = nrm[c];
+  if (tid == 0) {
+    d.sc->fro2 = fro2;
+    d.sc->rot = rot;  // 1: not converged
+    d.sc->active = 0;
+    d.sc->sweeps = sweep;
+    d.sc->k = 0;
+  }
+}
+
+// Class of a gate: 0 (block Jacobi), or the k_small variant that holds it.
+// X takes `cols` columns of its rows (and J's) in LDS; the first variant
+// leaves room for four workgroups on a CU.
+int small_class(int rows, int cols, int jrows) {
+  const int tot = rows + jrows, ld = (tot + 15) / 16 * 16;
+  if (tot > SMALL_ROWS || cols > 64) return 0;
+  if (cols <= 32 && cols * ld <= SMALL_ELEMS_1) return 1;
+  return cols * ld <= SMALL_ELEMS_2 ? 2 : 0;
+}
+
+void launch_small(hipStream_t st, const GateDesc *d, int ng, bool class1, bool class2) {
+  if (ng <= 0) return;
+  if (class1)
+    hipLaunchKernelGGL((k_small<256, SMALL_ELEMS_1, 1>), dim3(ng), dim3(256), 0, st, d);
+  if (class2)
+    hipLaunchKernelGGL((k_small<512, SMALL_ELEMS_2, 2>), dim3(ng), dim3(512), 0, st, d);
+}
+
+}  // namespace tn

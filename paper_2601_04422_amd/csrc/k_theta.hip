@@ -177,7 +177,7 @@ __device__ void theta_tile_f64mfma(const GateDesc &d, int r0, int c0, double2 *s
 __global__ __launch_bounds__(256) void k_theta_f64mfma(const GateDesc *descs) {
   const GateDesc &d = descs[blockIdx.z];
   int r0 = blockIdx.x * TM, c0 = blockIdx.y * TC;
-  if (r0 >= d.m || c0 >= d.chiR) return;
+  if (d.small || r0 >= d.m || c0 >= d.chiR) return;
   __shared__ double2 smem[TM * (2 * TC + 1)];
   if (d.storage == 0)
     theta_tile_f64mfma<double2>(d, r0, c0, smem);

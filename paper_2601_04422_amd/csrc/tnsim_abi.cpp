@@ -407,6 +407,10 @@ struct BatchItem {
 // Pair-count class of a launch, for the autotuned rotation shape.
 int tune_bucket(int pairs) { return pairs <= 32 ? 0 : pairs <= 128 ? 1 : pairs <= 512 ? 2 : 3; }
 
+int max_sweeps(tnsim_mps o) {
+  return o->cfg.jacobi_max_sweeps > 0 ? o->cfg.jacobi_max_sweeps : 60;
+}
+
 SlotScalars *pin_scalars(tnsim_mps o, int buf = 0) {
   if (buf) return reinterpret_cast<SlotScalars *>(o->pin + o->pin_sc1_off);
   return reinterpret_cast<SlotScalars *>(o->pin + align_up(sizeof(GateDesc) * o->L.desc_cap));
@@ -430,7 +434,12 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   // always when the caller needs the full left basis (the adjoint)
   d.trans = force_trans || d.n > d.m;
   // QR-preconditioned SVD for square or tall M that fits one panel workgroup
-  d.qr = h->cfg.svd_precondition && !d.trans && d.m <= QR_MAX_ROWS;
+  // a matrix that one workgroup holds in LDS is decomposed there; with
+  // complex64 sites the block Jacobi keeps such gates too (see fullOrder)
+  if (o->cfg.precision == TNSIM_FP64 && h->cfg.storage == TNSIM_STORE_C128)
+    d.small = d.trans ? small_class(d.n, d.m, d.m) : small_class(d.m, d.n, 0);
+  d.maxSweeps = max_sweeps(o);
+  d.qr = h->cfg.svd_precondition && !d.trans && !d.small && d.m <= QR_MAX_ROWS;
   d.rows = d.qr ? d.n : (d.trans ? d.n : d.m);
   d.cols = d.trans ? d.m : d.n;
   d.ldx = pad_to(d.rows, 16);
@@ -511,9 +520,12 @@ tnsim_status put_descs(tnsim_mps o, const GateDesc *D, int n, bool second = fals
 tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second = false) {
   tnsim_mps h = o;
   int maxM = 0, maxColsPad = 0, maxChiR = 0, qrN = 0, qrMr = 0;
+  bool small1 = false, small2 = false, block = false;
   double theta_flop = 0.0, theta_byte = 0.0, colnorm_byte = 0.0, qr_flop = 0.0;
   for (int g = 0; g < ng; g++) {
     const GateDesc &d = D[g];
+    (d.small == 0 ? block : d.small == 1 ? small1 : small2) = true;
+    if (d.small) continue;
     maxM = std::max(maxM, d.m);
     maxColsPad = std::max(maxColsPad, d.colsPad);
     maxChiR = std::max(maxChiR, d.chiR);
@@ -532,6 +544,13 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
   if (s != TNSIM_OK) return s;
   GateDesc *ddev = o->at<GateDesc>(second ? o->L.desc2_off : o->L.desc_off);
   hipStream_t st = second ? o->stream2 : o->stream;
+  // small gates: merge and SVD in one launch (they take no sweeps)
+  if (small1 || small2) {
+    ProfScope p(h, TNSIM_K_EIG, 0.0, 0.0, second);
+    launch_small(st, ddev, ng, small1, small2);
+    LAUNCHCHK(h, "small gates");
+  }
+  if (!block) return TNSIM_OK;
   {
     ProfScope p(h, TNSIM_K_OTHER, 0.0, 0.0, second);
     launch_setup_slots(st, ddev, ng, maxColsPad, 0);
@@ -740,9 +759,10 @@ void record_gate(const BatchItem &it, const GateDesc &d, int k, int sweeps) {
 }
 
 // Everything after convergence: norms, sort and truncation, U_k, the
-// write-back; updates each handle's bond dimensions and statistics.
+// write-back; updates each handle's bond dimensions and statistics.  With
+// `staged`, the descriptors of exactly these gates are in place already.
 tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D,
-                          const int *sweeps, int ng) {
+                          const int *sweeps, int ng, bool staged = false) {
   tnsim_mps h = o;
   hipStream_t st = o->stream;
   int maxM = 0, maxN = 0, maxColsPad = 0, qrN = 0;
@@ -750,15 +770,18 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
   for (int g = 0; g < ng; g++) {
     maxM = std::max(maxM, D[g].m);
     maxN = std::max(maxN, D[g].n);
+    if (D[g].small) continue;  // its norms are in place
     maxColsPad = std::max(maxColsPad, D[g].colsPad);
     colnorm_byte += 16.0 * D[g].rows * D[g].cols;
     if (D[g].qr) qrN = std::max(qrN, D[g].n);
   }
-  tnsim_status s = put_descs(o, D, ng);
-  if (s != TNSIM_OK) return s;
+  if (!staged) {
+    tnsim_status s = put_descs(o, D, ng);
+    if (s != TNSIM_OK) return s;
+  }
   GateDesc *ddev = o->at<GateDesc>(o->L.desc_off);
   SlotScalars *scg = o->at<SlotScalars>(o->L.scg_off);
-  {
+  if (maxColsPad) {
     ProfScope p(h, TNSIM_K_COLNORM, 0.0, colnorm_byte);
     launch_colnorm(st, ddev, ng, maxColsPad);
   }
@@ -772,6 +795,16 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
   HIPCHK(h, hipMemcpyAsync(sc_pin, scg, sizeof(SlotScalars) * ng, hipMemcpyDeviceToHost, st));
   HIPCHK(h, hipStreamSynchronize(st));
   prof_drain(h);
+  // a small gate that ran out of sweeps: nothing was cut (k_trunc), nothing
+  // is written back
+  bool failed = false;
+  for (int g = 0; g < ng; g++) failed |= D[g].small && sc_pin[g].rot;
+  if (failed) {
+    for (int g = 0; g < ng; g++)
+      record_gate(items[g], D[g], 0, D[g].small ? sc_pin[g].sweeps : sweeps[g]);
+    o->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
+    return TNSIM_E_NOCONV;
+  }
   int maxK = 0, qrK = 0, qrM = 0;
   double wbl_byte = 0.0, wbr_flop = 0.0, wbr_byte = 0.0, qa_flop = 0.0;
   for (int g = 0; g < ng; g++) {
@@ -784,7 +817,7 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
       hg->sum_eps += sv.eps;
       hg->prod_keep *= (1.0 - sv.eps);
       if (!(fl & PEND_EPS_ONLY)) {
-        record_gate(items[g], d, sv.k, sweeps[g]);
+        record_gate(items[g], d, sv.k, d.small ? sv.sweeps : sweeps[g]);
         hg->n2q += 1;
       }
     }
@@ -829,9 +862,12 @@ tnsim_status run_2q_items(tnsim_mps o, const BatchItem *items, int ng, bool forc
   tnsim_status s = gates_prepare(o, D.data(), ng);
   if (s != TNSIM_OK) return s;
 
-  const int max_sweeps = o->cfg.jacobi_max_sweeps > 0 ? o->cfg.jacobi_max_sweeps : 60;
-  std::vector<int> done_at(ng, 0), act(ng);
-  for (int g = 0; g < ng; g++) act[g] = g;
+  const int max_sweeps = ::max_sweeps(o);
+  std::vector<int> done_at(ng, 0), act;
+  for (int g = 0; g < ng; g++)
+    if (!D[g].small) act.push_back(g);
+  if (act.empty())
+    return gates_finish(o, items, D.data(), done_at.data(), ng, /*staged=*/true);
   SweepRunner sw{o};
   auto replan = [&]() {
     std::vector<const GateDesc *> pd;
@@ -1157,9 +1193,10 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
   std::vector<Flight> fl;
   std::vector<int> free_slots;
   for (int sl = h->L.nslots - 1; sl >= 0; sl--) free_slots.push_back(sl);
-  const int max_sweeps = h->cfg.jacobi_max_sweeps > 0 ? h->cfg.jacobi_max_sweeps : 60;
+  const int max_sweeps = ::max_sweeps(h);
   SweepRunner sw{h};
   bool dirty = true;
+  int in_line = 0;  // gates of a preparation whose descriptors are still in place
   std::vector<char> rot;
   // gates admitted while others sweep are prepared on the second stream and
   // join the sweeps once their preparation has finished
@@ -1214,6 +1251,7 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
       } else {
         tnsim_status s = gates_prepare(h, nd.data(), (int)nd.size());
         if (s != TNSIM_OK) return s;
+        in_line = (int)nd.size();
         for (const Flight &f : nf) fl.push_back(f);
         dirty = true;
       }
@@ -1227,6 +1265,42 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
       if (ready1.empty() && ready2.empty()) break;
       continue;
     }
+    // write back the gates of `fin` and release their successors
+    auto finish = [&](const std::vector<Flight> &fin, bool staged) -> tnsim_status {
+      std::vector<BatchItem> fi;
+      std::vector<GateDesc> fd;
+      std::vector<int> fs;
+      for (const Flight &f : fin) {
+        fi.push_back(f.it);
+        fd.push_back(f.d);
+        fs.push_back(f.sweeps);
+      }
+      tnsim_status s = gates_finish(h, fi.data(), fd.data(), fs.data(), (int)fin.size(), staged);
+      if (s != TNSIM_OK) return s;
+      for (const Flight &f : fin) {
+        free_slots.push_back(f.it.slot);
+        release(f.op);
+      }
+      dirty = true;
+      return TNSIM_OK;
+    };
+    // small gates are decomposed by their preparation: they are written back
+    // at once, and what they release is admitted before the next sweep
+    {
+      std::vector<Flight> done, rest;
+      for (const Flight &f : fl) (f.d.small ? done : rest).push_back(f);
+      if (!done.empty()) {
+        // the descriptors of a preparation in line are still in place when it
+        // held these gates and no others
+        const bool staged = rest.empty() && in_line == (int)done.size();
+        in_line = 0;
+        fl.swap(rest);
+        tnsim_status s = finish(done, staged);
+        if (s != TNSIM_OK) return s;
+        continue;
+      }
+    }
+    in_line = 0;
     // one Jacobi sweep over every gate in flight
     if (dirty) {
       std::vector<const GateDesc *> pd;
@@ -1254,22 +1328,9 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
         keep.push_back(fl[a]);
     }
     if (!fin.empty()) {
-      std::vector<BatchItem> fi;
-      std::vector<GateDesc> fd;
-      std::vector<int> fs;
-      for (const Flight &f : fin) {
-        fi.push_back(f.it);
-        fd.push_back(f.d);
-        fs.push_back(f.sweeps);
-      }
-      s = gates_finish(h, fi.data(), fd.data(), fs.data(), (int)fin.size());
-      if (s != TNSIM_OK) return s;
-      for (const Flight &f : fin) {
-        free_slots.push_back(f.it.slot);
-        release(f.op);
-      }
       fl.swap(keep);
-      dirty = true;
+      s = finish(fin, false);
+      if (s != TNSIM_OK) return s;
     }
     if (!prep.empty()) {
       const hipError_t q = hipEventQuery(h->ev_prep);

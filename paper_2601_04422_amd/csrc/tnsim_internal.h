@@ -21,6 +21,11 @@ constexpr int QG = 32;  // reflectors applied together to the rest of the matrix
 constexpr int QR_RC = 256;  // rows per workgroup in a group update
 constexpr int QR_MAX_ROWS = 2048;
 
+// Gates whose Jacobi matrix one workgroup holds in LDS (k_small.hip): rows
+// (with J's, when it is accumulated) and elements of the two variants.
+constexpr int SMALL_ROWS = 192;
+constexpr int SMALL_ELEMS_1 = 2304, SMALL_ELEMS_2 = 9728;
+
 // Scalars per gate slot (device memory).
 struct SlotScalars {
   double fro2;  // squared Frobenius norm of the Jacobi matrix
@@ -31,6 +36,8 @@ struct SlotScalars {
   int rot;      // some pair rotated during the current sweep
   int active;   // gate still sweeping
   int nz;       // count above the numerical-zero floor
+  int sweeps;   // Jacobi sweeps taken (k_small)
+  int pad;
 };
 
 // Device descriptor of one two-qubit gate in a batch.  The host fills it from
@@ -49,6 +56,8 @@ struct GateDesc {
   int tfp32;             // theta' stored as complex64 (mixed modes)
   int innerSweeps;       // sweep cap of the 64x64 pair solve
   int gpStride;          // pair blocks per K-split chunk in Gp
+  int small;             // k_small variant that decomposes the gate, 0: block Jacobi
+  int maxSweeps;         // sweep cap (k_small; the host caps the block Jacobi's)
   int fullOrder;         // 1: every pair solve visits all 2016 column pairs of a Gram computed
                          // afresh (k_eig_full), 0: the passes of k_eig
   int rotRows;           // rows of X (and J) per rotation workgroup, a multiple of 64
@@ -115,6 +124,8 @@ void launch_theta(hipStream_t st, const GateDesc *d, int ng, int precision, int 
                   int max_chiR);
 void launch_colnorm(hipStream_t st, const GateDesc *d, int ng, int max_cols);
 void launch_gate_init(hipStream_t st, const GateDesc *d, int ng);
+int small_class(int rows, int cols, int jrows);
+void launch_small(hipStream_t st, const GateDesc *d, int ng, bool class1, bool class2);
 void launch_begin_sweep(hipStream_t st, const GateDesc *d, int ng);
 // full, cross: the batch holds gates with fullOrder set, or without
 void launch_gram(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,

@@ -50,3 +50,62 @@ def test_gate_vs_numpy(chi, profile, precondition):
     assert np.abs(a.conj().T @ a - np.eye(k)).max() <= 8 * s.size * EPS
     kept = u[:, :k] @ (u[:, :k].conj().T @ th) / norm
     assert np.abs(a @ b - kept).max() <= (8 * err + 8 * err / gap) * np.abs(kept).max()
+
+
+@pytest.mark.parametrize("dims", [
+    [1, 2, 4, 8, 16, 32, 64, 64, 32, 16, 8, 4, 2, 1],       # every ramp of a saturated chain
+    [1, 2, 3, 5, 9, 17, 33, 47, 31, 29, 15, 7, 3, 2, 1],    # odd sizes, one column out per round
+    [1, 2, 1, 2, 4, 3, 6, 12, 24, 48, 96, 60, 1, 1],        # wide and tall M, bonds of 1
+])
+def test_every_site_vs_numpy(dims):
+    """Square, wide and tall matrices on both sides of the one that a
+    workgroup holds in LDS; one gate at a time and a whole layer."""
+    from paper_2601_04422_amd import tnsim as T
+
+    n = len(dims) - 1
+    sites, lams = W.random_canonical_mps(n, dims, 77)
+    rng = np.random.default_rng(7)
+    gates = [W.haar_u4(rng) for _ in range(n - 1)]
+    cap = 128
+    base = T.MPS(n, cap, 0.0, max_layer_gates=1)
+    # a chain's bonds are capped at 2^distance to the nearer end
+    if any(dims[q] > min(cap, 2 ** min(q, n - q)) for q in range(1, n)):
+        dims = [min(d, 2 ** min(q, n - q)) for q, d in enumerate(dims)]
+        sites, lams = W.random_canonical_mps(n, dims, 77)
+    base.import_state(sites, lams)
+    m = T.MPS(n, cap, 0.0)
+    for parity in (0, 1):
+        m.copy_from(base)
+        assert m.apply_layer([(i, i + 1, gates[i]) for i in range(parity, n - 1, 2)]) == T.OK
+        for i in range(parity, n - 1, 2):
+            th, u, s = reference(sites, lams + [np.ones(1)], i, gates[i])
+            floor = 2 * dims[i] * EPS * s[0] ** 2
+            k = min(int(np.sum(s * s > floor)), min(cap, 2 ** min(i + 1, n - 1 - i)))
+            norm = np.sqrt(np.sum(s[:k] ** 2))
+            err = s.size ** 1.5 * EPS * s[0] / norm
+            lam = m.lam(i)
+            assert lam.size == k
+            assert np.abs(lam - s[:k] / norm).max() <= 4 * err
+            a, b = m.site(i), m.site(i + 1)
+            a, b = a.reshape(-1, k), b.reshape(k, -1)
+            assert np.abs(a.conj().T @ a - np.eye(k)).max() <= 8 * max(a.shape) * EPS
+            # nothing is cut: the pair is theta' itself
+            assert np.abs(a @ b - th / norm).max() <= 16 * err * np.abs(th).max() / norm + 16 * err
+
+
+def test_no_convergence_leaves_the_layer_unwritten():
+    """One gate of a layer runs out of sweeps (the other is diagonal already):
+    no site, Schmidt weight or bond dimension of the layer changes."""
+    from paper_2601_04422_amd import tnsim as T
+
+    n = 8
+    sites, lams = W.random_canonical_mps(n, W.saturated_dims(n, 16), 5)
+    m = T.MPS(n, 16, 0.0, jacobi_max_sweeps=1)
+    m.import_state(sites, lams)
+    before = ([m.site(q) for q in range(n)], [m.lam(b) for b in range(n - 1)], m.bond_dims())
+    layer = [(2, 3, W.haar_u4(np.random.default_rng(3))), (6, 7, np.eye(4))]
+    assert m.apply_layer(layer) == T.E_NOCONV
+    assert (m.bond_dims() == before[2]).all()
+    assert all((m.site(q) == before[0][q]).all() for q in range(n))
+    assert all((m.lam(b) == before[1][b]).all() for b in range(n - 1))
+    assert m.apply_circuit(layer) == T.E_NOCONV
