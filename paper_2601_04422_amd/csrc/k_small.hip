@@ -21,6 +21,8 @@
 #include "tn_complex.h"
 #include "tn_lanes.h"
 
+#include <type_traits>
+
 namespace tn {
 
 // 1 / x and sqrt(x) of normal positive numbers, to rounding (hardware
@@ -36,12 +38,93 @@ __device__ __forceinline__ double sm_rsqrt(double x) {
   return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
+// Rows of a column in LDS: whole rows of 16 lanes, one of the counts that
+// small_sweeps is unrolled for.
+__host__ __device__ __forceinline__ int small_ld(int tot) {
+  const int nt = (tot + 15) / 16;
+  return 16 * (nt <= 4 ? nt : nt <= 6 ? 6 : nt <= 8 ? 8 : SMALL_ROWS / 16);
+}
+
 // sum over the 16 lanes of a row, in every lane
 __device__ __forceinline__ double row_sum(double x) {
   x += row_next<8>(x);
   x += row_next<4>(x);
   x += row_next<2>(x);
   return x + row_next<1>(x);
+}
+
+// Sweeps over the columns of X (rows of the dot products, then J's rows, NT
+// rows of 16 lanes in all) until one rotates nothing; returns whether the last
+// sweep still rotated, with the sweeps taken in `sweep`.
+template <int NT, int GROUPS>
+__device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotated, int rows,
+                                            int cols, int maxSweeps, double tol2, double small,
+                                            int &sweep) {
+  constexpr int ld = 16 * NT;
+  const int tid = threadIdx.x, l = tid & 15, grp = tid >> 4;
+  const int P = (cols + 1) & ~1;  // players of the circle method
+  int rot = 1;
+  sweep = 0;
+  while (rot && sweep < maxSweeps) {
+    sweep++;
+    // squared norms afresh
+    for (int c = grp; c < cols; c += GROUPS) {
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < NT; i++)
+        if (16 * i + l < rows) s += cabs2(X[c * ld + 16 * i + l]);
+      s = row_sum(s);
+      if (l == 0) nrm[c] = s;
+    }
+    if (tid == 0) rotated = 0;
+    __syncthreads();
+    // pair grp of round r: (r, P - 1) for grp = 0, (r + grp, r - grp) mod P - 1 otherwise
+    int pu = grp, pd = grp ? P - 1 - grp : 0;
+    for (int r = 0; r < P - 1; r++) {
+      const int o = grp ? pd : P - 1;
+      const int p = min(pu, o), q = max(pu, o);
+      pu = pu + 1 == P - 1 ? 0 : pu + 1;
+      pd = pd + 1 == P - 1 ? 0 : pd + 1;
+      if (grp < P / 2 && q < cols) {  // an odd column sits out
+        double2 *xp = X + p * ld + l, *yp = X + q * ld + l;
+        const double a = nrm[p], b = nrm[q];
+        double2 x[NT], y[NT];
+#pragma unroll
+        for (int i = 0; i < NT; i++) {
+          x[i] = xp[16 * i];
+          y[i] = yp[16 * i];
+        }
+        double2 g = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < NT; i++)
+          if (16 * i + l < rows) cfmac(g, x[i], y[i]);
+        g = make_double2(row_sum(g.x), row_sum(g.y));
+        const double h = cabs2(g);
+        if (a > small && b > small && h > tol2 * a * b) {
+          // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
+          // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
+          const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
+          const double w = copysign(2.0 * sm_rcp(fabs(delta) + s2 * sm_rsqrt(s2)), delta);
+          const double wh = w * h, c = sm_rsqrt(fma(w, wh, 1.0)), cw = c * w;
+          const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
+#pragma unroll
+          for (int i = 0; i < NT; i++) {
+            xp[16 * i] = csub(cscale(x[i], c), cmul(sec, y[i]));
+            yp[16 * i] = cadd(cmul(se, x[i]), cscale(y[i], c));
+          }
+          if (l == 0) {
+            nrm[p] = a - wh;
+            nrm[q] = b + wh;
+            rotated = 1;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    rot = rotated;
+    __syncthreads();  // every thread reads before it is cleared
+  }
+  return rot;
 }
 
 template <int THREADS, int ELEMS, int CLASS>
@@ -55,7 +138,7 @@ __global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
   constexpr int GROUPS = THREADS / 16;
   const int m = d.m, n = d.n, chiL = d.chiL, chiM = d.chiM, chiR = d.chiR;
   const int rows = d.rows, cols = d.cols, tot = rows + (d.trans ? m : 0);
-  const int ld = (tot + 15) / 16 * 16;
+  const int ld = small_ld(tot);
 
   // theta' (kept for the write-back) and X
   for (int e = tid; e < cols * ld; e += THREADS) {
@@ -93,92 +176,35 @@ __global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
         X[r * ld + t * chiR + c] = cscale(cconj(o), w);
     }
   }
-  if (tid == 0) rotated = 0;
   __syncthreads();
 
-  auto norms = [&]() {
-    for (int c = grp; c < cols; c += GROUPS) {
-      double s = 0.0;
-      for (int r = l; r < rows; r += 16) s += cabs2(X[c * ld + r]);
-      s = row_sum(s);
-      if (l == 0) nrm[c] = s;
-    }
-  };
-  norms();
+  // ||X||_F^2 for the rounding-noise rule, every thread the same sum
+  for (int c = grp; c < cols; c += GROUPS) {
+    double v = 0.0;
+    for (int r = l; r < rows; r += 16) v += cabs2(X[c * ld + r]);
+    v = row_sum(v);
+    if (l == 0) nrm[c] = v;
+  }
   __syncthreads();
   double fro2 = 0.0;
   for (int c = 0; c < cols; c++) fro2 += nrm[c];
+  __syncthreads();
   const double eps_r = rows * 0x1p-53, small = fro2 * eps_r * eps_r, tol2 = d.tol * d.tol;
-
-  const int P = (cols + 1) & ~1, nt = ld / 16;  // players of the circle method, rows per lane
-  int sweep = 0, rot = 1;
-  while (rot && sweep < d.maxSweeps) {
-    sweep++;
-    for (int r = 0; r < P - 1; r++) {
-      // pair grp of round r
-      int p = -1, q = 0;
-      if (grp < P / 2) {
-        if (grp == 0) {
-          p = r;
-          q = P - 1;
-        } else {
-          p = r + grp;
-          p -= p >= P - 1 ? P - 1 : 0;
-          q = r - grp;
-          q += q < 0 ? P - 1 : 0;
-        }
-        if (p > q) {
-          const int t = p;
-          p = q;
-          q = t;
-        }
-        if (q >= cols) p = -1;  // the odd column out
-      }
-      if (p >= 0) {
-        double2 *xp = X + p * ld + l, *yp = X + q * ld + l;
-        const double a = nrm[p], b = nrm[q];
-        double2 x[SMALL_ROWS / 16], y[SMALL_ROWS / 16];
-        double2 g = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int i = 0; i < SMALL_ROWS / 16; i++)
-          if (i < nt) {
-            x[i] = xp[16 * i];
-            y[i] = yp[16 * i];
-          }
-#pragma unroll
-        for (int i = 0; i < SMALL_ROWS / 16; i++)
-          if (16 * i + l < rows) cfmac(g, x[i], y[i]);
-        g = make_double2(row_sum(g.x), row_sum(g.y));
-        const double h = cabs2(g);
-        if (a > small && b > small && h > tol2 * a * b) {
-          // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
-          // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
-          const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
-          const double w = copysign(2.0 * sm_rcp(fabs(delta) + s2 * sm_rsqrt(s2)), delta);
-          const double wh = w * h, c = sm_rsqrt(fma(w, wh, 1.0)), cw = c * w;
-          const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
-#pragma unroll
-          for (int i = 0; i < SMALL_ROWS / 16; i++)
-            if (i < nt) {
-              xp[16 * i] = csub(cscale(x[i], c), cmul(sec, y[i]));
-              yp[16 * i] = cadd(cmul(se, x[i]), cscale(y[i], c));
-            }
-          if (l == 0) {
-            nrm[p] = a - wh;
-            nrm[q] = b + wh;
-            rotated = 1;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    rot = rotated;
-    __syncthreads();
-    if (rot) {
-      if (tid == 0) rotated = 0;
-      norms();
-      __syncthreads();
-    }
+  int sweep = 0, rot = 0;
+  auto run = [&](auto nt) {
+    rot = small_sweeps<decltype(nt)::value, GROUPS>(X, nrm, rotated, rows, cols, d.maxSweeps,
+                                                    tol2, small, sweep);
+  };
+  switch (ld / 16) {
+    case 1: run(std::integral_constant<int, 1>()); break;
+    case 2: run(std::integral_constant<int, 2>()); break;
+    case 3: run(std::integral_constant<int, 3>()); break;
+    case 4: run(std::integral_constant<int, 4>()); break;
+    case 5:
+    case 6: run(std::integral_constant<int, 6>()); break;
+    case 7:
+    case 8: run(std::integral_constant<int, 8>()); break;
+    default: run(std::integral_constant<int, SMALL_ROWS / 16>()); break;
   }
   // left vectors and squared norms where the truncation and the write-back
   // (and the adjoint) look for them
@@ -201,7 +227,7 @@ __global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
 // X takes `cols` columns of its rows (and J's) in LDS; the first variant
 // leaves room for four workgroups on a CU.
 int small_class(int rows, int cols, int jrows) {
-  const int tot = rows + jrows, ld = (tot + 15) / 16 * 16;
+  const int tot = rows + jrows, ld = small_ld(tot);
   if (tot > SMALL_ROWS || cols > 64) return 0;
   if (cols <= 32 && cols * ld <= SMALL_ELEMS_1) return 1;
   return cols * ld <= SMALL_ELEMS_2 ? 2 : 0;
