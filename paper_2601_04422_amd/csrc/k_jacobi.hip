@@ -20,6 +20,7 @@
 #include "tn_complex.h"
 #include "tn_buffer.h"
 #include "tn_lanes.h"
+#include "tn_fast.h"
 
 namespace tn {
 
@@ -514,24 +515,6 @@ __device__ __forceinline__ int eig_bits(int round, int nr) {
       if (ns >= 5 ? t == k % 5 : t % ns == k) bits |= 16 >> t;
   }
   return bits;
-}
-
-// 1 / x and sqrt(x) of normal positive numbers, to rounding: the hardware's
-// estimates (24 bits) and two Newton steps.  The library forms also cover
-// subnormal and infinite arguments, which a pair that passes the rotation
-// test does not have, and their longer chains are the solve's critical path.
-__device__ __forceinline__ double fast_rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double fast_sqrt(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  double s = x * y, hy = 0.5 * y;  // Goldschmidt: s -> sqrt(x), hy -> 1 / (2 sqrt(x))
-  const double r = fma(-s, hy, 0.5);
-  s = fma(s, r, s);
-  hy = fma(hy, r, hy);
-  return fma(fma(-s, s, x), hy, s);
 }
 
 // x with bit value v inserted at position b; x without bit b.

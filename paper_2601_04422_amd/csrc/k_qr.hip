@@ -15,9 +15,13 @@
 // Householder QR in the LAPACK convention: H = I - tau v v^H with v(0) = 1,
 // H^H [alpha; x] = [beta; 0], beta real; a panel of QNB reflectors is
 // I - V T V^H (compact WY, T upper triangular).  Everything is float64.
+#include <algorithm>
+
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 #include "tn_buffer.h"
+#include "tn_lanes.h"
+#include "tn_fast.h"
 
 namespace tn {
 
@@ -61,7 +65,7 @@ constexpr int QP_WAVES = QP_THREADS / 64;
 __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, int stage,
                                                         int panel) {
   const GateDesc &d = descs[blockIdx.x];
-  if (!d.qr) return;
+  if (!d.qr || d.storage == 0) return;
   const QrView q = qr_view(d, stage);
   const int j0 = panel * QNB;
   if (j0 >= q.cols) return;
@@ -194,9 +198,159 @@ __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, 
   if (tid < QNB * QNB) T[tid] = Ts[tid / QNB][tid % QNB];
 }
 
-void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int panel) {
+// The same panel with one reduction and one barrier per column (gates with
+// complex128 sites; the order of the sums differs from k_qr_panel's, and
+// complex64 handles keep theirs, see GateDesc::fullOrder).  The products
+// conj(x) a_p of the column below its diagonal with every panel column come
+// out of one transposed sum (wave_sums), the norm among them; reflector,
+// update factors and T follow from them in every wavefront by itself:
+//   v = [1; scale x],  v^H a_p = a_p(c) + conj(scale) x^H a_p      (p > c)
+//   v_p^H v = conj(v_p(c)) + scale conj(x^H v_p)                   (p < c)
+// RPT rows per thread, chosen with the threads by the rows that are left.
+// Bound by the column's chain (sum, barrier, square root and two reciprocals):
+// a panel takes 24 instead of 51 us at 2048 rows, 12 instead of 49 at 256
+// (k_qr_panel: four barriers and 96 lane exchanges a column).
+template <int THREADS, int RPT>
+__global__ __launch_bounds__(THREADS) void k_qr_panel1(const GateDesc *descs, int stage,
+                                                          int panel) {
+  const GateDesc &d = descs[blockIdx.x];
+  if (!d.qr || d.storage != 0) return;
+  const QrView q = qr_view(d, stage);
+  const int j0 = panel * QNB;
+  if (j0 >= q.cols) return;
+  const int w = min(QNB, q.cols - j0);
+  const int nr = q.rows - j0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int WAVES = THREADS / 64;
+  __shared__ double red[2][WAVES][2 * QNB];  // by column parity
+  __shared__ double2 top[2][QNB];               // row c of the panel
+  double2 a[RPT][QNB];
+#pragma unroll
+  for (int i = 0; i < RPT; i++) {
+    const int lr = tid + THREADS * i;
+#pragma unroll
+    for (int c = 0; c < QNB; c++)
+      a[i][c] = (lr < nr && c < w) ? q.A[(size_t)(j0 + c) * q.ld + j0 + lr]
+                                   : make_double2(0.0, 0.0);
+  }
+  double2 trow[QNB];  // thread t < 8: row t of T
+#pragma unroll
+  for (int c = 0; c < QNB; c++) trow[c] = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int c = 0; c < QNB; c++) {
+    if (c >= w) break;
+    double s[2 * QNB];
+#pragma unroll
+    for (int p = 0; p < QNB; p++) {
+      double2 g = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int i = 0; i < RPT; i++) {
+        const bool below = i > 0 || tid > c;
+        const double2 x = below ? a[i][c] : make_double2(0.0, 0.0);
+        if (p == c)
+          g.x = fma(x.x, x.x, fma(x.y, x.y, g.x));
+        else
+          cfmac(g, x, a[i][p]);
+      }
+      s[2 * p] = g.x;
+      s[2 * p + 1] = g.y;
+    }
+    const double mine = wave_sums<2 * QNB>(s);  // lane l: value l / 4
+    if ((lane & 3) == 0) red[c & 1][wave][lane >> 2] = mine;
+    if (tid == c) {
+#pragma unroll
+      for (int p = 0; p < QNB; p++) top[c & 1][p] = a[0][p];
+    }
+    __syncthreads();
+    double tot = 0.0;
+#pragma unroll
+    for (int v = 0; v < WAVES; v++) tot += red[c & 1][v][lane & 15];
+    const double x2 = lane_value(tot, 2 * c);
+    const double2 al = top[c & 1][c];
+    double2 tau = make_double2(0.0, 0.0), scale = tau;
+    double beta = al.x;
+    if (!(x2 == 0.0 && al.y == 0.0)) {  // else already triangular: H = I
+      const double n2 = cabs2(al) + x2;
+      double rb, inv;  // 1 / beta, 1 / |alpha - beta|^2
+      double2 dn;      // alpha - beta
+      if (n2 > 0x1p-900 && n2 < 0x1p900) {  // (uniform) the short chains hold
+        const double r = fast_rsqrt(n2);
+        beta = -copysign(fast_sqrt(n2), al.x);
+        rb = -copysign(r, al.x);
+        dn = make_double2(al.x - beta, al.y);
+        inv = fast_rcp(cabs2(dn));
+      } else {
+        beta = -copysign(sqrt(n2), al.x);
+        rb = 1.0 / beta;
+        dn = make_double2(al.x - beta, al.y);
+        inv = 1.0 / cabs2(dn);
+      }
+      tau = make_double2((beta - al.x) * rb, -al.y * rb);
+      scale = make_double2(dn.x * inv, -dn.y * inv);  // 1 / (alpha - beta)
+    }
+    const double2 ctau = cconj(tau);
+    double2 tc = make_double2(0.0, 0.0);  // sum over p < c of T(t, p) v_p^H v
+    double2 v[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; i++) {
+      const bool below = i > 0 || tid > c, diag = i == 0 && tid == c;
+      v[i] = below ? cmul(a[i][c], scale) : make_double2(diag ? 1.0 : 0.0, 0.0);
+      if (below) a[i][c] = v[i];
+      if (diag) a[i][c] = make_double2(beta, 0.0);
+    }
+#pragma unroll
+    for (int p = 0; p < QNB; p++) {
+      if (p == c || p >= w) continue;
+      const double2 g = make_double2(lane_value(tot, 2 * p), lane_value(tot, 2 * p + 1));
+      const double2 t = top[c & 1][p];
+      if (p > c) {  // a_p <- a_p - conj(tau) (v^H a_p) v
+        const double2 f = cmul(ctau, cadd(t, cmulc(scale, g)));
+#pragma unroll
+        for (int i = 0; i < RPT; i++) a[i][p] = csub(a[i][p], cmul(v[i], f));
+      } else {
+        tc = cadd(tc, cmul(trow[p], cadd(cconj(t), cmul(scale, cconj(g)))));
+      }
+    }
+    // T(0:c, c) = -tau T(0:c, 0:c) (V^H v)(0:c), T(c, c) = tau
+    trow[c] = tid < c ? cmul(make_double2(-tau.x, -tau.y), tc)
+                      : (tid == c ? tau : make_double2(0.0, 0.0));
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; i++) {
+    const int lr = tid + THREADS * i;
+    if (lr < nr) {
+#pragma unroll
+      for (int c = 0; c < QNB; c++)
+        if (c < w) q.A[(size_t)(j0 + c) * q.ld + j0 + lr] = a[i][c];
+    }
+  }
+  double2 *T = qr_tfac(d, stage, panel);
+  if (tid < QNB) {
+#pragma unroll
+    for (int c = 0; c < QNB; c++) T[tid * QNB + c] = trow[c];
+  }
+}
+
+void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int panel, int max_rows,
+                     bool c128, bool c64) {
   if (ng <= 0) return;
-  hipLaunchKernelGGL(k_qr_panel, dim3(ng), dim3(QP_THREADS), 0, st, d, stage, panel);
+  if (c64)
+    hipLaunchKernelGGL(k_qr_panel, dim3(ng), dim3(QP_THREADS), 0, st, d, stage, panel);
+  if (!c128) return;
+  const int left = max_rows - panel * QNB;
+  auto run = [&](auto threads, auto rpt) {
+    constexpr int T = decltype(threads)::value, R = decltype(rpt)::value;
+    hipLaunchKernelGGL((k_qr_panel1<T, R>), dim3(ng), dim3(T), 0, st, d, stage, panel);
+  };
+  using std::integral_constant;
+  if (left <= 256)
+    run(integral_constant<int, 256>(), integral_constant<int, 1>());
+  else if (left <= 512)
+    run(integral_constant<int, 256>(), integral_constant<int, 2>());
+  else if (left <= 1024)
+    run(integral_constant<int, 512>(), integral_constant<int, 2>());
+  else
+    run(integral_constant<int, 512>(), integral_constant<int, 4>());
 }
 
 // ---------------------------------------------------------------- block update
@@ -317,16 +471,103 @@ constexpr int QU_COLS = 32;   // target columns per workgroup, panel updates
 __global__ __launch_bounds__(256) void k_qr_update(const GateDesc *descs, int stage, int panel,
                                                    int col_end) {
   const GateDesc &d = descs[blockIdx.y];
-  if (!d.qr) return;
+  if (!d.qr || d.storage == 0) return;
   qr_block_update<QNB, QU_COLS>(d, qr_view(d, stage), panel * QNB, qr_tfac(d, stage, panel), 0,
                                 col_end);
 }
 
+// The same for gates with complex128 sites: QU1_COLS columns per workgroup,
+// rows dealt to the threads, the 8 x 4 products V^H B in registers and summed
+// over the workgroup once.  77 -> 17 us at 2048 rows, 14 -> 7.5 at 256 (one workgroup took all
+// columns of the group, its dot products serial over the rows in LDS).
+constexpr int QU1_COLS = 4;
+__global__ __launch_bounds__(256) void k_qr_update1(const GateDesc *descs, int stage, int panel,
+                                                    int col_end) {
+  const GateDesc &d = descs[blockIdx.y];
+  if (!d.qr || d.storage != 0) return;
+  const QrView q = qr_view(d, stage);
+  const int j0 = panel * QNB;
+  if (j0 >= q.cols) return;
+  const int w = min(QNB, q.cols - j0), rows = q.rows;
+  const int ncols = min(col_end, q.cols) - j0 - w;
+  const int c0 = blockIdx.x * QU1_COLS;
+  if (c0 >= ncols) return;
+  const int nc = min(QU1_COLS, ncols - c0);
+  const double2 *V = q.A + (size_t)j0 * q.ld;
+  double2 *B = q.A + (size_t)(j0 + w + c0) * q.ld;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto vget = [&](int r, int p) {  // reflector p: 1 on its diagonal, stored below
+    const int dr = r - (j0 + p);
+    return p < w && dr > 0 ? V[(size_t)p * q.ld + r]
+                           : make_double2(p < w && dr == 0 ? 1.0 : 0.0, 0.0);
+  };
+  double s[2 * QNB * QU1_COLS];
+#pragma unroll
+  for (int e = 0; e < 2 * QNB * QU1_COLS; e++) s[e] = 0.0;
+  for (int r = j0 + tid; r < rows; r += 256) {
+    double2 v[QNB], b[QU1_COLS];
+#pragma unroll
+    for (int p = 0; p < QNB; p++) v[p] = vget(r, p);
+#pragma unroll
+    for (int c = 0; c < QU1_COLS; c++)
+      b[c] = c < nc ? B[(size_t)c * q.ld + r] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int p = 0; p < QNB; p++)
+#pragma unroll
+      for (int c = 0; c < QU1_COLS; c++) {
+        double2 g = make_double2(s[2 * (p * QU1_COLS + c)], s[2 * (p * QU1_COLS + c) + 1]);
+        cfmac(g, v[p], b[c]);
+        s[2 * (p * QU1_COLS + c)] = g.x;
+        s[2 * (p * QU1_COLS + c) + 1] = g.y;
+      }
+  }
+  __shared__ double red[4][2 * QNB * QU1_COLS];
+  __shared__ double2 Y[QNB][QU1_COLS];
+  red[wave][lane] = wave_sums<2 * QNB * QU1_COLS>(s);
+  __syncthreads();
+  if (tid < QNB * QU1_COLS) {  // Y = T^H S
+    const int p = tid / QU1_COLS, c = tid % QU1_COLS;
+    const double2 *T = qr_tfac(d, stage, panel);
+    double2 y = make_double2(0.0, 0.0);
+    for (int l = 0; l <= p; l++) {
+      const int e = 2 * (l * QU1_COLS + c);
+      const double2 sum = make_double2(red[0][e] + red[1][e] + red[2][e] + red[3][e],
+                                       red[0][e + 1] + red[1][e + 1] + red[2][e + 1] + red[3][e + 1]);
+      y = cadd(y, cmulc(T[l * QNB + p], sum));
+    }
+    Y[p][c] = y;
+  }
+  __syncthreads();
+  double2 y[QNB][QU1_COLS];
+#pragma unroll
+  for (int p = 0; p < QNB; p++)
+#pragma unroll
+    for (int c = 0; c < QU1_COLS; c++) y[p][c] = Y[p][c];
+  for (int r = j0 + tid; r < rows; r += 256) {
+    double2 v[QNB];
+#pragma unroll
+    for (int p = 0; p < QNB; p++) v[p] = vget(r, p);
+#pragma unroll
+    for (int c = 0; c < QU1_COLS; c++)
+      if (c < nc) {
+        double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int p = 0; p < QNB; p++) cfma(acc, v[p], y[p][c]);
+        double2 *bp = B + (size_t)c * q.ld + r;
+        *bp = csub(*bp, acc);
+      }
+  }
+}
+
 void launch_qr_update(hipStream_t st, const GateDesc *d, int ng, int stage, int panel,
-                      int col_end, int max_cols) {
+                      int col_end, int max_cols, bool c128, bool c64) {
   if (ng <= 0 || max_cols <= 0) return;
-  hipLaunchKernelGGL(k_qr_update, dim3((max_cols + QU_COLS - 1) / QU_COLS, ng), dim3(256), 0, st,
-                     d, stage, panel, col_end);
+  if (c64)
+    hipLaunchKernelGGL(k_qr_update, dim3((max_cols + QU_COLS - 1) / QU_COLS, ng), dim3(256), 0, st,
+                       d, stage, panel, col_end);
+  if (c128)
+    hipLaunchKernelGGL(k_qr_update1, dim3((max_cols + QU1_COLS - 1) / QU1_COLS, ng), dim3(256), 0,
+                       st, d, stage, panel, col_end);
 }
 
 // ------------------------------------------------ group update on matrix cores
@@ -389,7 +630,7 @@ __device__ __forceinline__ double2 qr_vget(const QrView &q, int j0, int w, int r
 }
 
 __global__ __launch_bounds__(256) void k_qrg_s(const GateDesc *descs, int stage, int group,
-                                               int apply) {
+                                               int apply, int gram_tile) {
   const GateDesc &d = descs[blockIdx.z];
   if (!d.qr) return;
   const int stg = apply ? 0 : stage;
@@ -398,9 +639,13 @@ __global__ __launch_bounds__(256) void k_qrg_s(const GateDesc *descs, int stage,
   if (j0 >= q.cols) return;
   const int w = min(QG, q.cols - j0);
   const QrTarget t = qr_target(d, q, j0, w, apply);
-  const int c0 = blockIdx.x * QGT;
+  // while factoring a gate with complex128 sites, the first column tile of
+  // the launch is V itself: V^H V, from which k_qrg_y solves for T's product
+  const bool gram = gram_tile && blockIdx.x == 0;
+  if (gram && d.storage != 0) return;
+  const int c0 = ((int)blockIdx.x - gram_tile) * QGT;
   const int rbeg = j0 + blockIdx.y * QR_RC;
-  if (c0 >= t.ncols || rbeg >= t.rows) return;
+  if ((!gram && c0 >= t.ncols) || rbeg >= t.rows) return;
   const int rend = min(t.rows, rbeg + QR_RC);
   __shared__ double2 Vs[32][QG + 1];
   __shared__ double2 Bs[32][QGT + 1];
@@ -414,13 +659,14 @@ __global__ __launch_bounds__(256) void k_qrg_s(const GateDesc *descs, int stage,
   // skipped, and masked only when written to LDS.
   static_assert(32 * QG == 4 * 256 && 32 * QGT == 4 * 256, "four elements per thread");
   const BufRes rA = make_res(q.A, q.ld * q.cols);
-  const BufRes rB = make_res(t.B, t.ldb * t.ncols);
+  const BufRes rB = gram ? rA : make_res(t.B, t.ldb * t.ncols);
+  const int ldb = gram ? q.ld : t.ldb, cb = gram ? j0 : c0;
   auto load = [&](int r0, double2 *vv, double2 *bb) {
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const int e = tid + 256 * k, r = e % 32, p = e / 32;
       vv[k] = bload(rA, (j0 + p) * q.ld + r0 + r);
-      bb[k] = bload(rB, (c0 + p) * t.ldb + r0 + r);
+      bb[k] = bload(rB, (cb + p) * ldb + r0 + r);
     }
   };
   auto to_lds = [&](int r0, const double2 *vv, const double2 *bb) {
@@ -430,7 +676,7 @@ __global__ __launch_bounds__(256) void k_qrg_s(const GateDesc *descs, int stage,
       const int rr = r0 + r, dr = rr - (j0 + p);  // reflector p: 1 on its diagonal, stored below
       const bool in = rr < rend;
       Vs[r][p] = (in && p < w && dr > 0) ? vv[k] : make_double2(in && p < w && dr == 0 ? 1.0 : 0.0, 0.0);
-      Bs[r][p] = (in && c0 + p < t.ncols) ? bb[k] : make_double2(0.0, 0.0);
+      Bs[r][p] = gram ? Vs[r][p] : (in && c0 + p < t.ncols) ? bb[k] : make_double2(0.0, 0.0);
     }
   };
   auto chunk = [&]() {
@@ -465,7 +711,12 @@ __global__ __launch_bounds__(256) void k_qrg_s(const GateDesc *descs, int stage,
 #pragma unroll
   for (int v = 0; v < 4; v++) {
     const int p = tp + lg + 4 * v, c = c0 + tc + l16;
-    if (c < t.ncols) Sp[(size_t)p * t.ldS + c] = make_double2(accR[v], accI[v]);
+    // V^H V goes to the last QG columns of the scratch rows: a full group has
+    // at most ldS - QG columns after it, a narrower (last) one has none
+    if (gram)
+      Sp[(size_t)p * t.ldS + t.ldS - QG + tc + l16] = make_double2(accR[v], accI[v]);
+    else if (c < t.ncols)
+      Sp[(size_t)p * t.ldS + c] = make_double2(accR[v], accI[v]);
   }
 }
 
@@ -480,13 +731,14 @@ __global__ __launch_bounds__(256) void k_qrg_y(const GateDesc *descs, int stage,
   const int w = min(QG, q.cols - j0);
   const QrTarget t = qr_target(d, q, j0, w, apply);
   const int c0 = blockIdx.x * QGT;
-  if (c0 >= t.ncols) return;
+  const bool solve = d.storage == 0;
+  // the first workgroup also keeps V^H V and tau for U = Q1 [W; 0]
+  if (c0 >= t.ncols && !(solve && !apply && blockIdx.x == 0)) return;
   const int nch = (t.rows - j0 + QR_RC - 1) / QR_RC;
   __shared__ double2 S[QG][QGT + 1];
   __shared__ double2 Tl[QG][QG + 1];
-  const double2 *T = qr_tgrp(d, stg, group);
+  double2 *T = qr_tgrp(d, stg, group);
   const int tid = threadIdx.x;
-  for (int e = tid; e < QG * QG; e += 256) Tl[e / QG][e % QG] = T[e];
   for (int e = tid; e < QG * QGT; e += 256) {
     const int p = e / QGT, cc = e % QGT, c = c0 + cc;
     double2 sum = make_double2(0.0, 0.0);
@@ -495,8 +747,56 @@ __global__ __launch_bounds__(256) void k_qrg_y(const GateDesc *descs, int stage,
         sum = cadd(sum, t.scr[((size_t)ch * QG + p) * t.ldS + c]);
     S[p][cc] = sum;
   }
+  for (int e = tid; e < QG * QG; e += 256) {
+    const int p = e / QG, l = e % QG;
+    if (solve && !apply) {  // T of the panels on the diagonal, V^H V above
+      double2 g = make_double2(0.0, 0.0);
+      if (p / QNB == l / QNB) {
+        if (j0 + p < q.cols) g = qr_tfac(d, stg, (j0 + p) / QNB)[(p % QNB) * QNB + l % QNB];
+      } else if (p < l) {
+        for (int ch = 0; ch < nch; ch++)
+          g = cadd(g, t.scr[((size_t)ch * QG + p) * t.ldS + t.ldS - QG + l]);
+      }
+      Tl[p][l] = g;
+      if (blockIdx.x == 0) T[e] = g;
+    } else {
+      Tl[p][l] = T[e];
+    }
+  }
   __syncthreads();
   double2 *Yg = t.scr + (size_t)nch * QG * t.ldS;  // after the partials
+  if (solve) {
+    // T^-1 is block upper triangular with the panels' T_b^-1 on the diagonal
+    // and V_a^H V_b above, so Y = op(T) S is a block substitution over the
+    // four panels: Y_b = op(T_b) S_b, then Y_b is taken out of the panels
+    // after it (T^H: ascending) or before it (T: descending).  Thread (cc,
+    // part) has column cc and row `part` of each panel.
+    const int cc = tid % QGT, part = tid / QGT, nb = (w + QNB - 1) / QNB;
+    static_assert(256 / QGT == QNB, "a row of the panel per thread");
+    for (int k = 0; k < nb; k++) {
+      const int o = QNB * (apply ? nb - 1 - k : k);
+      double2 y = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int l = 0; l < QNB; l++)  // T_b is upper triangular
+        y = cadd(y, cmul(apply ? Tl[o + part][o + l] : cconj(Tl[o + l][o + part]), S[o + l][cc]));
+      __syncthreads();
+      S[o + part][cc] = y;
+      __syncthreads();
+      for (int r = apply ? part : o + QNB + part; r < (apply ? o : QG); r += QNB) {
+        double2 x = S[r][cc];
+#pragma unroll
+        for (int l = 0; l < QNB; l++)
+          x = csub(x, cmul(apply ? Tl[r][o + l] : cconj(Tl[o + l][r]), S[o + l][cc]));
+        S[r][cc] = x;
+      }
+      __syncthreads();
+    }
+    for (int e = tid; e < QG * QGT; e += 256) {
+      const int p = e / QGT, c = c0 + e % QGT;
+      if (c < t.ncols) Yg[(size_t)p * t.ldS + c] = S[p][e % QGT];
+    }
+    return;
+  }
   for (int e = tid; e < QG * QGT; e += 256) {
     const int p = e / QGT, cc = e % QGT, c = c0 + cc;
     double2 y = make_double2(0.0, 0.0);
@@ -587,21 +887,26 @@ __global__ __launch_bounds__(256) void k_qrg_b(const GateDesc *descs, int stage,
 }
 
 void launch_qr_update_group(hipStream_t st, const GateDesc *d, int ng, int stage, int group,
-                            int apply, int max_cols, int max_rows) {
-  if (ng <= 0 || max_cols <= 0 || max_rows <= group * QG) return;
-  const int ct = (max_cols + QGT - 1) / QGT;
+                            int apply, int max_cols, int max_rows, bool c128) {
+  if (ng <= 0 || max_rows <= group * QG) return;
+  const int gram = c128 && !apply;  // V^H V of every group, also the last
+  if (max_cols <= 0 && !gram) return;
+  const int ct = max_cols > 0 ? (max_cols + QGT - 1) / QGT : 0;
   const int rc = (max_rows - group * QG + QR_RC - 1) / QR_RC;
-  hipLaunchKernelGGL(k_qrg_s, dim3(ct, rc, ng), dim3(256), 0, st, d, stage, group, apply);
-  hipLaunchKernelGGL(k_qrg_y, dim3(ct, ng), dim3(256), 0, st, d, stage, group, apply);
-  hipLaunchKernelGGL(k_qrg_b, dim3(ct, rc, ng), dim3(256), 0, st, d, stage, group, apply);
+  hipLaunchKernelGGL(k_qrg_s, dim3(ct + gram, rc, ng), dim3(256), 0, st, d, stage, group, apply,
+                     gram);
+  hipLaunchKernelGGL(k_qrg_y, dim3(std::max(ct, 1), ng), dim3(256), 0, st, d, stage, group, apply);
+  if (ct)
+    hipLaunchKernelGGL(k_qrg_b, dim3(ct, rc, ng), dim3(256), 0, st, d, stage, group, apply);
 }
 
 // T factor of a group of QG reflectors (compact WY, forward, columnwise):
 // T(i, i) = tau_i (from the panels' factors), T(0:i, i) = -tau_i T(0:i, 0:i)
-// (V(:, 0:i)^H v_i), with the Gram V^H V summed over the group's rows.
+// (V(:, 0:i)^H v_i), with the Gram V^H V summed over the group's rows.  Gates
+// with complex128 sites take V^H V from k_qrg_s instead.
 __global__ __launch_bounds__(256) void k_qr_tgroup(const GateDesc *descs, int stage, int group) {
   const GateDesc &d = descs[blockIdx.x];
-  if (!d.qr) return;
+  if (!d.qr || d.storage == 0) return;
   const QrView q = qr_view(d, stage);
   const int j0 = group * QG;
   if (j0 >= q.cols) return;

@@ -20,23 +20,11 @@
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 #include "tn_lanes.h"
+#include "tn_fast.h"
 
 #include <type_traits>
 
 namespace tn {
-
-// 1 / x and sqrt(x) of normal positive numbers, to rounding (hardware
-// estimate and Newton steps)
-__device__ __forceinline__ double sm_rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double sm_rsqrt(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
 
 // Rows of a column in LDS: whole rows of 16 lanes, one of the counts that
 // small_sweeps is unrolled for.
@@ -104,8 +92,8 @@ __device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotate
           // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
           // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
           const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
-          const double w = copysign(2.0 * sm_rcp(fabs(delta) + s2 * sm_rsqrt(s2)), delta);
-          const double wh = w * h, c = sm_rsqrt(fma(w, wh, 1.0)), cw = c * w;
+          const double w = copysign(2.0 * fast_rcp(fabs(delta) + s2 * fast_rsqrt(s2)), delta);
+          const double wh = w * h, c = fast_rsqrt(fma(w, wh, 1.0)), cw = c * w;
           const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
 #pragma unroll
           for (int i = 0; i < NT; i++) {

@@ -520,7 +520,7 @@ tnsim_status put_descs(tnsim_mps o, const GateDesc *D, int n, bool second = fals
 tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second = false) {
   tnsim_mps h = o;
   int maxM = 0, maxColsPad = 0, maxChiR = 0, qrN = 0, qrMr = 0;
-  bool small1 = false, small2 = false, block = false;
+  bool small1 = false, small2 = false, block = false, qr128 = false, qr64 = false;
   double theta_flop = 0.0, theta_byte = 0.0, colnorm_byte = 0.0, qr_flop = 0.0;
   for (int g = 0; g < ng; g++) {
     const GateDesc &d = D[g];
@@ -537,6 +537,7 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
       const double mm = d.m, nn = d.n;
       qrN = std::max(qrN, d.n);
       qrMr = std::max(qrMr, d.m);
+      (d.storage == TNSIM_STORE_C128 ? qr128 : qr64) = true;
       qr_flop += 8.0 * (mm * nn * nn - nn * nn * nn / 3.0) + 16.0 * nn * nn * nn / 3.0;
     }
   }
@@ -568,14 +569,16 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
   if (qrN > 0) {
     ProfScope p(h, TNSIM_K_QR, qr_flop, 0.0, second);
     for (int stage = 0; stage < 2; stage++) {
+      const int rows = stage ? qrN : qrMr;
       for (int grp = 0; grp < qrGroups; grp++) {
         const int gend = (grp + 1) * QG;
         for (int pnl = grp * (QG / QNB); pnl < (grp + 1) * (QG / QNB) && pnl * QNB < qrN; pnl++) {
-          launch_qr_panel(st, ddev, ng, stage, pnl);
-          launch_qr_update(st, ddev, ng, stage, pnl, gend, gend - (pnl + 1) * QNB);
+          launch_qr_panel(st, ddev, ng, stage, pnl, rows, qr128, qr64);
+          launch_qr_update(st, ddev, ng, stage, pnl, gend, std::min(gend, qrN) - (pnl + 1) * QNB,
+                           qr128, qr64);
         }
-        launch_qr_tgroup(st, ddev, ng, stage, grp);
-        launch_qr_update_group(st, ddev, ng, stage, grp, 0, qrN - gend, stage ? qrN : qrMr);
+        if (qr64) launch_qr_tgroup(st, ddev, ng, stage, grp);
+        launch_qr_update_group(st, ddev, ng, stage, grp, 0, qrN - gend, rows, qr128);
       }
       if (stage == 0) launch_qr_r1h(st, ddev, ng, qrN);
     }
@@ -838,7 +841,7 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
     ProfScope p(h, TNSIM_K_QR, qa_flop, 0.0);
     launch_qr_gather(st, ddev, ng, qrM, qrK);
     for (int grp = (qrN + QG - 1) / QG - 1; grp >= 0; grp--)
-      launch_qr_update_group(st, ddev, ng, 0, grp, 1, qrK, qrM);
+      launch_qr_update_group(st, ddev, ng, 0, grp, 1, qrK, qrM, false);
     LAUNCHCHK(h, "qr apply");
   }
   {

@@ -140,12 +140,14 @@ void launch_trunc(hipStream_t st, const GateDesc *d, int ng);
 // R1^H (in X).  Panels of QNB columns are factored and applied inside their
 // group of QG columns; a group's reflectors then update the rest at once
 // (apply = 1: multiply U by Q1 instead).
-void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int panel);
+// c128, c64: the batch holds gates with sites of that storage.
+void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int panel, int max_rows,
+                     bool c128, bool c64);
 void launch_qr_update(hipStream_t st, const GateDesc *d, int ng, int stage, int panel,
-                      int col_end, int max_cols);
+                      int col_end, int max_cols, bool c128, bool c64);
 void launch_qr_tgroup(hipStream_t st, const GateDesc *d, int ng, int stage, int group);
 void launch_qr_update_group(hipStream_t st, const GateDesc *d, int ng, int stage, int group,
-                            int apply, int max_cols, int max_rows);
+                            int apply, int max_cols, int max_rows, bool c128);
 void launch_qr_r1h(hipStream_t st, const GateDesc *d, int ng, int max_n);
 void launch_qr_r2h(hipStream_t st, const GateDesc *d, int ng, int max_n);
 void launch_qr_gather(hipStream_t st, const GateDesc *d, int ng, int max_m, int max_k);

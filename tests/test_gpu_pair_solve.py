@@ -109,3 +109,34 @@ def test_no_convergence_leaves_the_layer_unwritten():
     assert all((m.site(q) == before[0][q]).all() for q in range(n))
     assert all((m.lam(b) == before[1][b]).all() for b in range(n - 1))
     assert m.apply_circuit(layer) == T.E_NOCONV
+
+
+@pytest.mark.parametrize("precondition", [False, True])
+@pytest.mark.parametrize("chi, rank", [(40, 1), (64, 23), (150, 40)])
+def test_rank_deficient(chi, rank, precondition):
+    """Bonds that carry only `rank` of their chi values: zero columns in the
+    merged matrix, reflectors that are the identity, no noise in the result."""
+    from paper_2601_04422_amd import tnsim as T
+
+    n = 2 * int(np.ceil(np.log2(chi))) + 2
+    dims = W.saturated_dims(n, chi)
+    small = [min(d, rank) for d in dims]
+    sites, lams = W.random_canonical_mps(n, small, 31 + chi)
+    pad = [np.zeros((dims[q], 2, dims[q + 1]), dtype=np.complex128) for q in range(n)]
+    for p, s in zip(pad, sites):
+        p[: s.shape[0], :, : s.shape[2]] = s
+    plam = [np.concatenate([l, np.zeros(dims[b + 1] - l.size)]) for b, l in enumerate(lams)]
+    m = T.MPS(n, chi, 0.0, svd_precondition=precondition, max_layer_gates=1)
+    m.import_state(pad, plam)
+    i = n // 2 - 1
+    g = W.haar_u4(np.random.default_rng(chi))
+    assert m.apply_2q(i, i + 1, g) == T.OK
+    th, u, s = reference(pad, plam, i, g)
+    k = min(chi, int(np.sum(s * s > 2 * dims[i] * EPS * s[0] ** 2)))
+    assert k <= 2 * rank
+    norm = np.sqrt(np.sum(s[:k] ** 2))
+    lam = m.lam(i)
+    assert lam.size == k
+    assert np.abs(lam - s[:k] / norm).max() <= 4 * s.size ** 1.5 * EPS * s[0] / norm
+    a = m.site(i).reshape(-1, k)
+    assert np.abs(a.conj().T @ a - np.eye(k)).max() <= 8 * s.size * EPS
