@@ -2,12 +2,23 @@
 //
 // A complex product is four real products (C_re += A_re B_re - A_im B_im,
 // C_im += A_re B_im + A_im B_re), each a v_mfma_f64_16x16x4f64.  A workgroup
-// of four waves computes a 64 x 64 tile of C; each wave owns a 32 x 32
-// quarter (2 x 2 MFMA tiles).  K advances 16 at a time through LDS, with
-// the next step's global loads issued before the current step's products.
-// Operands are read in their storage precision (complex64 sites are widened
-// on load); C is complex128.  The summation order is fixed, so results do
-// not depend on scheduling.
+// computes a 32 x 32 tile of C, and its NW wavefronts split K between them,
+// each with all 2 x 2 MFMA tiles.  Operands go from memory straight into the
+// matrix-core layout (16 lanes along a row of B or along A's rows), two
+// k-steps ahead of the products, so the K loop has no barrier; the NW partial
+// tiles are added in LDS in wavefront order, so results do not depend on
+// scheduling.  Operands are read in their storage precision (complex64 sites
+// are widened on load); C is complex128.
+//
+// Why this split: with 64 x 64 tiles (16 or 32 of them at a bond of 256, each
+// a chain of K / 16 staged steps of 2 us) most CUs stood idle.  Three
+// expectations, an overlap, a norm and four amplitudes at chi = 500, n = 28:
+// 35.5 -> 9.1 ms; 1000 shots at chi = 256, n = 48: 8.7 -> 3.85 ms.  Large
+// products gain nothing from larger tiles either (the four wavefronts' loads
+// of a tile meet in L1 and L2): an expectation value at chi = 1024 5.8 -> 5.7
+// ms, at 2048 42.0 -> 41.3 (65 TFLOP/s), 2048 shots at 1024 8.5 -> 7.8.
+// Bound by the matrix cores: their rate when the chip is full, the chain of
+// K / (4 NW) steps of 16 products when it is not.
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 
@@ -21,10 +32,7 @@ __device__ __forceinline__ zd4_t zmfma(double a, double b, zd4_t c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-constexpr int ZT = 64, ZK = 16;
-// 64 x 64 tiles of a product that fills the chip (two workgroups per CU);
-// with fewer, the 32 x 32 tiles of k_zgemm_s take it
-constexpr size_t ZGEMM_FILL = 512;
+constexpr int ZT = 32;
 
 // AK: A(i,k) = A[i*sa + k], else A[k*sa + i]; AC: use conj(A).
 // BK: B(k,j) = B[j*sb + k], else B[k*sb + j].
@@ -34,151 +42,9 @@ constexpr size_t ZGEMM_FILL = 512;
 // values; the grid covers at most N of them), column j reads column
 // g.bmap[j] of B and is scaled by g.cscale[j]; tiles from column *g.asplit
 // on read A + g.za.
-template <class TA, class TB, bool AK, bool AC, bool BK, bool CM, bool GA>
-__global__ __launch_bounds__(256, AK ? 4 : 3) void k_zgemm(ZgemmArgs g) {
-  // XCD-aware tile order: workgroups are dealt to the 8 XCDs in turn, so
-  // workgroup L runs on XCD L % 8.  Each XCD gets a contiguous run of tiles
-  // in row-tile-major order, so the A rows of its tiles stay in its own L2.
-  const int nx = gridDim.x, ntile = gridDim.x * gridDim.y;
-  const int L = blockIdx.x + nx * blockIdx.y, xcd = L & 7, slot = L >> 3;
-  const int per = ntile >> 3, extra = ntile & 7;
-  const int t_lin = xcd * per + min(xcd, extra) + slot;
-  const int tx = t_lin % nx, ty = t_lin / nx;
-  int N = g.N, j0 = tx * ZT, A_off_tile = 0;
-  if (GA) {
-    const int lo = *g.clo;
-    N = *g.chi;
-    j0 += lo;
-    if (g.asplit && j0 >= *g.asplit) A_off_tile = 1;
-  } else if (g.mcount) {
-    N = min(N, g.mult * *g.mcount);
-  }
-  const int i0 = ty * ZT;
-  if (j0 >= N) return;
-  const int M = g.M, z = blockIdx.z;
-  const TA *A = (const TA *)g.A;
-  const TB *B = (const TB *)g.B;
-  double2 *C = g.C;
-  const int K = g.K;
-  A += (z + A_off_tile) * g.za;
-  B += z * g.zb;
-  C += z * g.zc;
-  __shared__ double2 As[ZK][ZT], Bs[ZK][ZT];
-  const int t = threadIdx.x;
-  // this thread's share of a K step: 4 elements of A and 4 of B
-  const int ar = AK ? (t >> 2) : (t >> 4), ac = AK ? (t & 3) * 4 : (t & 15) * 4;
-  const int br = BK ? (t >> 2) : (t >> 4), bc = BK ? (t & 3) * 4 : (t & 15) * 4;
-  double2 ra[4], rb[4];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      int gi, gk;
-      if (AK) {
-        gi = i0 + ar;
-        gk = k0 + ac + q;
-      } else {
-        gi = i0 + ac + q;
-        gk = k0 + ar;
-      }
-      ra[q] = (gi < M && gk < K)
-                  ? cload(A + (AK ? (long long)gi * g.sa + gk : (long long)gk * g.sa + gi))
-                  : make_double2(0.0, 0.0);
-      int gj;
-      if (BK) {
-        gj = j0 + br;
-        gk = k0 + bc + q;
-      } else {
-        gj = j0 + bc + q;
-        gk = k0 + br;
-      }
-      const long long bj = GA ? (long long)(gj < N ? g.bmap[gj] : 0) : gj;
-      rb[q] = (gj < N && gk < K)
-                  ? cload(B + (BK ? bj * g.sb + gk : (long long)gk * g.sb + bj))
-                  : make_double2(0.0, 0.0);
-    }
-  };
-  auto stash = [&]() {
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const double2 a = AC ? cconj(ra[q]) : ra[q];
-      if (AK)
-        As[ac + q][ar] = a;
-      else
-        As[ar][ac + q] = a;
-      if (BK)
-        Bs[bc + q][br] = rb[q];
-      else
-        Bs[br][bc + q] = rb[q];
-    }
-  };
-  const int w = t >> 6, lane = t & 63, l16 = lane & 15, lg = lane >> 4;
-  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
-  zd4_t cr[2][2], ci[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; a++)
-#pragma unroll
-    for (int b = 0; b < 2; b++) {
-      cr[a][b] = zd4_t{0.0, 0.0, 0.0, 0.0};
-      ci[a][b] = zd4_t{0.0, 0.0, 0.0, 0.0};
-    }
-  load(0);
-  for (int k0 = 0; k0 < K; k0 += ZK) {
-    stash();
-    __syncthreads();
-    if (k0 + ZK < K) load(k0 + ZK);
-#pragma unroll
-    for (int kk = 0; kk < ZK; kk += 4) {
-      double2 a[2], b[2];
-#pragma unroll
-      for (int x = 0; x < 2; x++) {
-        a[x] = As[kk + lg][wm + 16 * x + l16];
-        b[x] = Bs[kk + lg][wn + 16 * x + l16];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; x++)
-#pragma unroll
-        for (int y = 0; y < 2; y++) {
-          cr[x][y] = zmfma(a[x].x, b[y].x, cr[x][y]);
-          cr[x][y] = zmfma(-a[x].y, b[y].y, cr[x][y]);
-          ci[x][y] = zmfma(a[x].x, b[y].y, ci[x][y]);
-          ci[x][y] = zmfma(a[x].y, b[y].x, ci[x][y]);
-        }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int x = 0; x < 2; x++)
-#pragma unroll
-    for (int y = 0; y < 2; y++) {
-      const int j = j0 + wn + 16 * y + l16;
-      if (j >= N) continue;
-      const double sc = GA ? g.cscale[j] : 1.0;
-#pragma unroll
-      for (int v = 0; v < 4; v++) {
-        const int i = i0 + wm + 16 * x + lg + 4 * v;
-        if (i >= M) continue;
-        const double2 c = make_double2(sc * cr[x][y][v], sc * ci[x][y][v]);
-        C[CM ? (long long)j * g.sc + i : (long long)i * g.sc + j] = c;
-      }
-    }
-}
-
-// The same product for shapes whose 64 x 64 tiles would leave the chip idle
-// (a bond of 256 has 16 or 32 of them, each a chain of K / 16 steps of 2 us):
-// 32 x 32 tiles, and the NW wavefronts of a workgroup split K between them.
-// Operands go from memory straight into the matrix-core layout (16 lanes
-// along a row of B or along A's rows; the operands of these shapes stay in
-// L2), two k-steps ahead of the products, so the K loop has no barrier; the
-// NW partial tiles are added in LDS in wavefront order.
-// Bound by the matrix cores' latency chain (K / (4 NW) steps of 16 products).
-// Three expectations, an overlap, a norm and four amplitudes at chi = 500,
-// n = 28: 35.5 -> 9.1 ms; 1000 shots at chi = 256, n = 48: 8.7 -> 3.85 ms (the
-// split of K over workgroups with a summing launch that this replaces).
-constexpr int ST = 32;
-
 template <class TA, class TB, bool AK, bool AC, bool BK, bool CM, bool GA, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void k_zgemm_s(ZgemmArgs g) {
-  int N = g.N, j0 = blockIdx.x * ST, A_off_tile = 0;
+__global__ __launch_bounds__(64 * NW, 2) void k_zgemm(ZgemmArgs g) {
+  int N = g.N, j0 = blockIdx.x * ZT, A_off_tile = 0;
   if (GA) {
     const int lo = *g.clo;
     N = *g.chi;
@@ -187,7 +53,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_zgemm_s(ZgemmArgs g) {
   } else if (g.mcount) {
     N = min(N, g.mult * *g.mcount);
   }
-  const int i0 = blockIdx.y * ST;
+  const int i0 = blockIdx.y * ZT;
   if (j0 >= N) return;
   const int M = g.M, K = g.K, z = blockIdx.z;
   const TA *A = (const TA *)g.A + (z + A_off_tile) * g.za;
@@ -266,7 +132,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_zgemm_s(ZgemmArgs g) {
       mul(a[1], b[1]);
     }
   }
-  __shared__ double2 part[NW][ST][ST + 1];
+  __shared__ double2 part[NW][ZT][ZT + 1];
 #pragma unroll
   for (int x = 0; x < 2; x++)
 #pragma unroll
@@ -276,8 +142,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_zgemm_s(ZgemmArgs g) {
         part[w][16 * x + lg + 4 * v][16 * y + l16] = make_double2(cr[x][y][v], ci[x][y][v]);
   __syncthreads();
 #pragma unroll
-  for (int e = t; e < ST * ST; e += 64 * NW) {
-    const int il = CM ? e % ST : e / ST, jl = CM ? e / ST : e % ST;  // along C's rows in memory
+  for (int e = t; e < ZT * ZT; e += 64 * NW) {
+    const int il = CM ? e % ZT : e / ZT, jl = CM ? e / ZT : e % ZT;  // along C's rows in memory
     const int i = i0 + il, j = j0 + jl;
     if (i >= M || j >= N) continue;
     double2 c = part[0][il][jl];
@@ -303,17 +169,16 @@ static void zgemm_types(int a_storage, int b_storage, F f) {
 
 template <bool AK, bool AC, bool BK, bool CM, bool GA = false>
 static void zgemm_dispatch(hipStream_t st, const ZgemmArgs &g, int a_storage, int b_storage) {
-  const dim3 big((g.N + ZT - 1) / ZT, (g.M + ZT - 1) / ZT, g.batch);
-  const dim3 fine((g.N + ST - 1) / ST, (g.M + ST - 1) / ST, g.batch);
+  const dim3 grid((g.N + ZT - 1) / ZT, (g.M + ZT - 1) / ZT, g.batch);
+  // fewer tiles than CUs and a K to split: twice the wavefronts on each
+  const bool few = (size_t)grid.x * grid.y * grid.z <= 256 && g.K >= 64;
   zgemm_types(a_storage, b_storage, [&](auto ta, auto tb) {
     using TA = decltype(ta);
     using TB = decltype(tb);
-    if ((size_t)big.x * big.y * big.z >= ZGEMM_FILL)
-      hipLaunchKernelGGL((k_zgemm<TA, TB, AK, AC, BK, CM, GA>), big, dim3(256), 0, st, g);
-    else if ((size_t)fine.x * fine.y * fine.z > 256 || g.K < 64)
-      hipLaunchKernelGGL((k_zgemm_s<TA, TB, AK, AC, BK, CM, GA, 4>), fine, dim3(256), 0, st, g);
-    else  // fewer tiles than CUs: twice the wavefronts on each
-      hipLaunchKernelGGL((k_zgemm_s<TA, TB, AK, AC, BK, CM, GA, 8>), fine, dim3(512), 0, st, g);
+    if (few)
+      hipLaunchKernelGGL((k_zgemm<TA, TB, AK, AC, BK, CM, GA, 8>), grid, dim3(512), 0, st, g);
+    else
+      hipLaunchKernelGGL((k_zgemm<TA, TB, AK, AC, BK, CM, GA, 4>), grid, dim3(256), 0, st, g);
   });
 }
 
