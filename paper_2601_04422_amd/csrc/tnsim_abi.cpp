@@ -216,7 +216,7 @@ struct GradState {
   size_t state_bytes = 0, ckpt0 = 0;
   std::vector<size_t> st_site, st_lam;  // offsets inside one checkpoint
   std::vector<size_t> cot_site, cot_lam;
-  size_t envL = 0, envR = 0, env_stride = 0, envF = 0, envF2 = 0;
+  size_t envL = 0, envR = 0, envLS = 0, envRS = 0, envT = 0, env_stride = 0, envF = 0, envF2 = 0;
   size_t tmp0 = 0, tmp_stride = 0, lam2 = 0, sbar = 0, dots = 0, ubar = 0, grad = 0;
   size_t rec0 = 0, rec_stride = 0, rec_a = 0, rec_b = 0, rec_lam = 0, rec_T = 0, rec_J = 0,
          rec_sig = 0, rec_perm = 0;
@@ -1447,6 +1447,12 @@ GradState grad_layout(const Layout &L, int n_seg, int max_seg, int n_params) {
   off += G.env_stride * (n + 1);
   G.envR = off;
   off += G.env_stride * (n + 1);
+  G.envLS = off;
+  off += G.env_stride * (n + 1);
+  G.envRS = off;
+  off += G.env_stride * (n + 1);
+  G.envT = off;
+  off += G.env_stride * (n + 3);
   G.envF = off;
   off = align_up(off + sizeof(double2) * (size_t)maxbond * 2 * maxbond);
   G.envF2 = off;
@@ -1631,7 +1637,9 @@ tnsim_status grad_apply(tnsim_mps h, int gi, GradRec *rec) {
 }
 
 // One left transfer step: E' (rb x rk) = B^H [P] (E (lb x lk) K) for site q.
-void env_left(tnsim_mps h, int q, const double2 *E, double2 *Eo, const double2 *P) {
+// With `acc`, w times the result is added to Eo instead.
+void env_left(tnsim_mps h, int q, const double2 *E, double2 *Eo, const double2 *P, double w = 1.0,
+              int acc = 0) {
   GradState &G = h->grad;
   hipStream_t st = h->stream;
   const int lb = h->dims[q], rb = h->dims[q + 1], sto = h->L.storage;
@@ -1644,11 +1652,13 @@ void env_left(tnsim_mps h, int q, const double2 *E, double2 *Eo, const double2 *
     Fp = F2;
   }
   launch_gemm_gen(st, gemm(rb, rb, 2 * lb, h->site(q), 1, rb, 1, sto, Fp, rb, 1, 0, 0, Eo, rb, 1,
-                           cr(1.0), 0));
+                           cr(w), acc));
 }
 
 // One right transfer step: R' (lb x lb)[a, a'] = sum conj(A[a,s,b]) P[s,s'] A[a',s',b'] R[b,b'].
-void env_right(tnsim_mps h, int q, const double2 *R, double2 *Ro, const double2 *P) {
+// With `acc`, w times the result is added to Ro instead.
+void env_right(tnsim_mps h, int q, const double2 *R, double2 *Ro, const double2 *P, double w = 1.0,
+               int acc = 0) {
   GradState &G = h->grad;
   hipStream_t st = h->stream;
   const int lb = h->dims[q], rb = h->dims[q + 1], sto = h->L.storage;
@@ -1663,39 +1673,156 @@ void env_right(tnsim_mps h, int q, const double2 *R, double2 *Ro, const double2 
   }
   // R'[a, a'] = sum_{(s,b)} conj(A[a, (s,b)]) G2[a', (s,b)]
   launch_gemm_gen(st, gemm(lb, lb, 2 * rb, h->site(q), 2 * rb, 1, 1, sto, Fp, 1, 2 * rb, 0, 0, Ro,
-                           lb, 1, cr(1.0), 0));
+                           lb, 1, cr(w), acc));
 }
 
-// Abar_q += w * (d <psi|P|psi> / d conj(A_q)) for every site, P given per site
-// (identity where isI).
-tnsim_status loss_cotangent_term(tnsim_mps h, const double2 *tab, const char *isI, double w) {
+// The loss sum_t c_t <P_t> / <1> and its cotangents.  An environment is linear
+// in what it closes, so the terms share everything but their own support
+// [a_t, b_t] (first to last site with an operator): left of it the identity's
+// left environments LI, right of it the identity's right environments RI, and
+// past their support all terms travel in one sum,
+//   LS_q = sum over b_t < q of c_t L_t,q,   RS_q = sum over a_t >= q of c_t R_t,q.
+// One chain per term over the whole state, as it was, takes sites x terms
+// products; this takes sites + the supports (14 qubits, 13 neighbouring
+// pairs: 1180 -> 350 products in the backward pass).
+tnsim_status pauli_table(const char *p, int n, std::vector<double2> &tab, std::vector<char> &isI);
+
+struct LossTerm {
+  std::vector<double2> tab;
+  std::vector<char> isI;
+  double c = 0.0;
+  int a = 0, b = -1;  // support; empty for the identity
+  const double2 *op(int q) const { return isI[q] ? nullptr : tab.data() + 4 * q; }
+};
+
+std::vector<LossTerm> loss_terms(tnsim_mps h) {
+  const GradState &G = h->grad;
+  const int n = h->L.n;
+  std::vector<LossTerm> T(G.paulis.size());
+  for (size_t t = 0; t < T.size(); t++) {
+    pauli_table(G.paulis[t].c_str(), n, T[t].tab, T[t].isI);
+    T[t].c = G.coeffs[t];
+    T[t].a = n;
+    for (int q = 0; q < n; q++)
+      if (!T[t].isI[q]) {
+        T[t].a = std::min(T[t].a, q);
+        T[t].b = q;
+      }
+  }
+  return T;
+}
+
+// LI and LS of every site; norm = <psi|psi>, sum = sum of c_t <psi|P_t|psi>.
+tnsim_status loss_left(tnsim_mps h, const std::vector<LossTerm> &T, double &norm, double &sum) {
+  GradState &G = h->grad;
+  hipStream_t st = h->stream;
+  const int n = h->L.n;
+  auto env = [&](size_t base, int q) { return (double2 *)(G.ws + base + G.env_stride * q); };
+  launch_fill_c(st, env(G.envL, 0), 1, cr(1.0));
+  launch_fill_zero(st, G.ws + G.envLS, G.env_stride * (n + 1));
+  for (int q = 0; q < n; q++) env_left(h, q, env(G.envL, q), env(G.envL, q + 1), nullptr);
+  double c_id = 0.0;
+  int first = n;  // LS_q is zero up to the first term's end
+  for (const LossTerm &t : T) {
+    if (t.b < 0) {
+      c_id += t.c;
+      continue;
+    }
+    first = std::min(first, t.b + 1);
+    const double2 *cur = env(G.envL, t.a);
+    for (int q = t.a; q <= t.b; q++) {
+      double2 *out = q == t.b ? env(G.envLS, q + 1) : env(G.envT, n + 1 + (q & 1));
+      env_left(h, q, cur, out, t.op(q), q == t.b ? t.c : 1.0, q == t.b);
+      cur = out;
+    }
+  }
+  for (int q = first; q < n; q++)
+    env_left(h, q, env(G.envLS, q), env(G.envLS, q + 1), nullptr, 1.0, 1);
+  LAUNCHCHK(h, "loss environments");
+  HIPCHK(h, hipStreamSynchronize(st));  // the staging buffer is free
+  double2 *pin = (double2 *)h->pin;
+  HIPCHK(h, hipMemcpyAsync(pin, env(G.envL, n), sizeof(double2), hipMemcpyDeviceToHost, st));
+  HIPCHK(h, hipMemcpyAsync(pin + 1, env(G.envLS, n), sizeof(double2), hipMemcpyDeviceToHost, st));
+  HIPCHK(h, hipStreamSynchronize(st));
+  norm = pin[0].x;
+  sum = pin[1].x + c_id * norm;
+  return TNSIM_OK;
+}
+
+// Abar_q += dloss * d loss / d conj(A_q) for every site, loss = sum / norm.
+tnsim_status loss_cotangents(tnsim_mps h, double dloss) {
   GradState &G = h->grad;
   hipStream_t st = h->stream;
   const int n = h->L.n, sto = h->L.storage;
-  auto envL = [&](int q) { return (double2 *)(G.ws + G.envL + G.env_stride * q); };
-  auto envR = [&](int q) { return (double2 *)(G.ws + G.envR + G.env_stride * q); };
-  launch_fill_c(st, envL(0), 1, cr(1.0));
-  for (int q = 0; q < n; q++) env_left(h, q, envL(q), envL(q + 1), isI[q] ? nullptr : tab + 4 * q);
-  launch_fill_c(st, envR(n), 1, cr(1.0));
-  for (int q = n - 1; q >= 0; q--)
-    env_right(h, q, envR(q + 1), envR(q), isI[q] ? nullptr : tab + 4 * q);
+  const std::vector<LossTerm> T = loss_terms(h);
+  double norm, sum;
+  tnsim_status s = loss_left(h, T, norm, sum);
+  if (s != TNSIM_OK) return s;
+  const double scale = dloss / norm;
+  auto env = [&](size_t base, int q) { return (double2 *)(G.ws + base + G.env_stride * q); };
   double2 *F = (double2 *)(G.ws + G.envF), *F2 = (double2 *)(G.ws + G.envF2);
-  for (int q = 0; q < n; q++) {
+  launch_fill_c(st, env(G.envR, n), 1, cr(1.0));
+  launch_fill_zero(st, G.ws + G.envRS, G.env_stride * (n + 1));
+  for (int q = n - 1; q >= 0; q--) env_right(h, q, env(G.envR, q + 1), env(G.envR, q), nullptr);
+  // F (+)= w E A_q
+  auto left_site = [&](int q, const double2 *E, double w, int acc) {
     const int lb = h->dims[q], rb = h->dims[q + 1];
-    launch_gemm_gen(st, gemm(lb, 2 * rb, lb, envL(q), lb, 1, 0, 0, h->site(q), 2 * rb, 1, 0, sto,
-                             F, 2 * rb, 1, cr(1.0), 0));
-    const double2 *Fp = F;
-    if (!isI[q]) {
-      const double2 *P = tab + 4 * q;
-      launch_pauli_phys(st, F, F2, lb, rb, P[0], P[1], P[2], P[3]);
-      Fp = F2;
+    launch_gemm_gen(st, gemm(lb, 2 * rb, lb, E, lb, 1, 0, 0, h->site(q), 2 * rb, 1, 0, sto, F,
+                             2 * rb, 1, cr(w), acc));
+  };
+  // Abar[(a,s), b] += w sum_b' X[(a,s), b'] R[b, b']
+  auto add = [&](int q, const double2 *X, const double2 *R, double w) {
+    const int lb = h->dims[q], rb = h->dims[q + 1];
+    launch_gemm_gen(st, gemm(2 * lb, rb, rb, X, rb, 1, 0, 0, R, 1, rb, 0, 0,
+                             (double2 *)(G.ws + G.cot_site[q]), rb, 1, cr(w), 1));
+  };
+  double w_id = -sum / norm;  // the norm's term, and identities among the P_t
+  int firstL = n, lastR = -1;
+  for (const LossTerm &t : T) {
+    if (t.b < 0) {
+      w_id += t.c;
+      continue;
     }
-    double2 *Ab = (double2 *)(G.ws + G.cot_site[q]);
-    // Abar[(a,s), b] += w sum_b' Fp[(a,s), b'] R[b, b']
-    launch_gemm_gen(st, gemm(2 * lb, rb, rb, Fp, rb, 1, 0, 0, envR(q + 1), 1, rb, 0, 0, Ab, rb, 1,
-                             cr(w), 1));
+    firstL = std::min(firstL, t.b + 1);
+    lastR = std::max(lastR, t.a);
+    // inside the support: R_t,q in envT(q), L_t,q as the sites go by
+    const double2 *R = env(G.envR, t.b + 1);
+    for (int q = t.b; q > t.a; q--) {
+      env_right(h, q, R, env(G.envT, q), t.op(q));
+      R = env(G.envT, q);
+    }
+    env_right(h, t.a, R, env(G.envRS, t.a), t.op(t.a), t.c, 1);
+    const double2 *E = env(G.envL, t.a);
+    for (int q = t.a; q <= t.b; q++) {
+      const int lb = h->dims[q], rb = h->dims[q + 1];
+      left_site(q, E, 1.0, 0);
+      const double2 *X = F, *P = t.op(q);
+      if (P) {
+        launch_pauli_phys(st, F, F2, lb, rb, P[0], P[1], P[2], P[3]);
+        X = F2;
+      }
+      add(q, X, q == t.b ? env(G.envR, q + 1) : env(G.envT, q + 1), scale * t.c);
+      if (q < t.b) {
+        double2 *out = env(G.envT, n + 1 + (q & 1));
+        launch_gemm_gen(st, gemm(rb, rb, 2 * lb, h->site(q), 1, rb, 1, sto, X, rb, 1, 0, 0, out,
+                                 rb, 1, cr(1.0), 0));
+        E = out;
+      }
+    }
   }
-  LAUNCHCHK(h, "loss cotangent");
+  for (int q = lastR - 1; q >= 0; q--)
+    env_right(h, q, env(G.envRS, q + 1), env(G.envRS, q), nullptr, 1.0, 1);
+  // sites outside a term's support, and the norm
+  for (int q = 0; q < n; q++) {
+    left_site(q, env(G.envL, q), w_id, 0);
+    if (q >= firstL) left_site(q, env(G.envLS, q), 1.0, 1);
+    add(q, F, env(G.envR, q + 1), scale);
+    if (q < lastR) {
+      left_site(q, env(G.envL, q), 1.0, 0);
+      add(q, F, env(G.envRS, q + 1), scale);
+    }
+  }
+  LAUNCHCHK(h, "loss cotangents");
   return TNSIM_OK;
 }
 
@@ -2568,20 +2695,21 @@ tnsim_status tnsim_mps_copy(tnsim_mps dst, tnsim_mps src) {
   for (int q = 1; q < n; q++)
     if (src->dims[q] > dst->L.dimcap[q]) return TNSIM_E_CAPACITY;
   HIPCHK(src, hipStreamSynchronize(src->stream));
-  for (int q = 0; q < n; q++) {
-    size_t cnt = (size_t)src->dims[q] * 2 * src->dims[q + 1];
-    launch_convert(dst->stream, src->site(q), src->L.storage, dst->site(q), dst->L.storage, cnt);
-  }
-  LAUNCHCHK(dst, "copy");
-  for (int b = 0; b < n - 1; b++)
-    HIPCHK(dst, hipMemcpyAsync(dst->lam(b), src->lam(b), sizeof(double) * src->dims[b + 1],
-                               hipMemcpyDeviceToDevice, dst->stream));
-  dst->dims = src->dims;
-  HIPCHK(dst, hipStreamSynchronize(dst->stream));
+  HIPCHK(dst, hipStreamSynchronize(dst->stream));  // the staging buffer is free
   memcpy(dst->pin, src->dims.data(), sizeof(int32_t) * (n + 1));
   HIPCHK(dst, hipMemcpyAsync(dst->dims_dev(), dst->pin, sizeof(int32_t) * (n + 1),
                              hipMemcpyHostToDevice, dst->stream));
-  HIPCHK(dst, hipStreamSynchronize(dst->stream));
+  size_t most = 1;
+  for (int q = 0; q < n; q++)
+    most = std::max(most, (size_t)src->dims[q] * 2 * src->dims[q + 1]);
+  launch_copy_state(dst->stream, n, dst->dims_dev(), src->at<void *const>(src->L.site_tab_off),
+                    src->L.storage, dst->at<void *const>(dst->L.site_tab_off), dst->L.storage,
+                    src->at<double *const>(src->L.lam_tab_off),
+                    dst->at<double *const>(dst->L.lam_tab_off), most);
+  LAUNCHCHK(dst, "copy");
+  dst->dims = src->dims;
+  // src may be changed on its own stream as soon as the call returns
+  if (dst->stream != src->stream) HIPCHK(dst, hipStreamSynchronize(dst->stream));
   dst->sum_eps = src->sum_eps;
   dst->prod_keep = src->prod_keep;
   dst->n2q = src->n2q;
@@ -2634,6 +2762,23 @@ tnsim_status tnsim_last_batch(tnsim_mps h, int32_t *out, int32_t max_gates, int3
   return TNSIM_OK;
 }
 
+// Device memory to the caller's array, after everything on the handle's
+// stream.  What fits goes through the pinned staging buffer on that stream
+// (a direct copy to pageable memory took 24 us, whatever its size); larger
+// reads are copied directly.
+static tnsim_status read_back(tnsim_mps h, void *host, const void *dev, size_t bytes) {
+  if (bytes <= h->pin_bytes) {
+    HIPCHK(h, hipStreamSynchronize(h->stream));  // the buffer may feed an earlier copy
+    HIPCHK(h, hipMemcpyAsync(h->pin, dev, bytes, hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    memcpy(host, h->pin, bytes);
+    return TNSIM_OK;
+  }
+  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, hipMemcpy(host, dev, bytes, hipMemcpyDeviceToHost));
+  return TNSIM_OK;
+}
+
 tnsim_status tnsim_export_site(tnsim_mps h, int32_t q, tnsim_c128 *host, int32_t *chiL,
                                int32_t *chiR) {
   tnsim_status s = check_handle(h);
@@ -2644,12 +2789,12 @@ tnsim_status tnsim_export_site(tnsim_mps h, int32_t q, tnsim_c128 *host, int32_t
   if (chiR) *chiR = b;
   if (!host) return TNSIM_OK;
   size_t cnt = (size_t)a * 2 * b;
-  HIPCHK(h, hipStreamSynchronize(h->stream));
   if (h->L.storage == 0) {
-    HIPCHK(h, hipMemcpy(host, h->site(q), cnt * 16, hipMemcpyDeviceToHost));
+    return read_back(h, host, h->site(q), cnt * 16);
   } else {
     std::vector<float> tmp(2 * cnt);
-    HIPCHK(h, hipMemcpy(tmp.data(), h->site(q), cnt * 8, hipMemcpyDeviceToHost));
+    s = read_back(h, tmp.data(), h->site(q), cnt * 8);
+    if (s != TNSIM_OK) return s;
     for (size_t e = 0; e < cnt; e++) {
       host[e].re = tmp[2 * e];
       host[e].im = tmp[2 * e + 1];
@@ -2665,9 +2810,7 @@ tnsim_status tnsim_export_lambda(tnsim_mps h, int32_t bond, double *host, int32_
   int c = h->dims[bond + 1];
   if (chi) *chi = c;
   if (!host) return TNSIM_OK;
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  HIPCHK(h, hipMemcpy(host, h->lam(bond), sizeof(double) * c, hipMemcpyDeviceToHost));
-  return TNSIM_OK;
+  return read_back(h, host, h->lam(bond), sizeof(double) * c);
 }
 
 tnsim_status tnsim_import_state(tnsim_mps h, const tnsim_c128 *const *sites,
@@ -2783,13 +2926,10 @@ tnsim_status tnsim_forward_checkpointed(tnsim_mps h, void *dev_ws, size_t ws_byt
   }
   s = save_ckpt(h, n_segments);
   if (s != TNSIM_OK) return s;
-  double2 nd[2];  // <psi|psi>, <psi|P_t|psi>
-  double L = 0.0;
-  for (int t = 0; t < n_terms; t++) {
-    s = transfer(h, h, h, tabs[t].data(), isIs[t].data(), nd);
-    if (s != TNSIM_OK) return s;
-    L += coeffs[t] * nd[1].x / nd[0].x;
-  }
+  double norm, sum;
+  s = loss_left(h, loss_terms(h), norm, sum);
+  if (s != TNSIM_OK) return s;
+  const double L = sum / norm;
   GS.loss = L;
   GS.ready = true;
   *loss = L;
@@ -2814,23 +2954,8 @@ tnsim_status tnsim_backward(tnsim_mps h, double dloss, double *grad_angles) {
   // the final state: loss = sum_t c_t N_t / D
   s = restore_ckpt(h, G.n_seg);
   if (s != TNSIM_OK) return s;
-  double2 den;
-  s = transfer(h, h, h, nullptr, nullptr, &den);
+  s = loss_cotangents(h, dloss);
   if (s != TNSIM_OK) return s;
-  const double D = den.x;
-  std::vector<double2> tab;
-  std::vector<char> isI;
-  for (size_t t = 0; t < G.paulis.size(); t++) {
-    pauli_table(G.paulis[t].c_str(), n, tab, isI);
-    s = loss_cotangent_term(h, tab.data(), isI.data(), dloss * G.coeffs[t] / D);
-    if (s != TNSIM_OK) return s;
-  }
-  {  // d(N/D): the norm term, weight -L/D
-    std::vector<char> allI(n, 1);
-    std::vector<double2> idt(4 * n, make_double2(0, 0));
-    s = loss_cotangent_term(h, idt.data(), allI.data(), -dloss * G.loss / D);
-    if (s != TNSIM_OK) return s;
-  }
   const int n_gates = (int)G.gates.size();
   std::vector<GradRec> recs;
   for (int sg = G.n_seg - 1; sg >= 0; sg--) {

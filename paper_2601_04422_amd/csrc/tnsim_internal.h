@@ -112,6 +112,12 @@ double launch_probe(hipStream_t st, int unit, int groups, int iters, double *out
 void launch_apply_1q(hipStream_t st, const Gate1Desc *d, int ng, int max_elems);
 void launch_convert(hipStream_t st, const void *src, int src_storage, void *dst, int dst_storage,
                     size_t count);
+// Every site (storage converted) and Schmidt weight of a state in one launch;
+// the site and weight tables and the bond dimensions are in device memory,
+// `most` is the largest site's element count.
+void launch_copy_state(hipStream_t st, int n, const int *dims, void *const *src, int src_storage,
+                       void *const *dst, int dst_storage, double *const *lam_src,
+                       double *const *lam_dst, size_t most);
 // rg 2x2 factors of a gate's operator Schmidt decomposition (bond propagation)
 struct Mat4x4 {
   double2 v[4][4];
