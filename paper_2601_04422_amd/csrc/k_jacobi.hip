@@ -474,18 +474,18 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
 // (N = 128, 256, 512: 7, 8, 9), at 1.25 passes of 32 rounds instead of 63.
 //
 // Layout.  G's off-diagonal 2x2 blocks (p, q of slot i) x (p, q of slot j)
-// lie in registers, two per thread: inside a group of 16 slots the block
-// (l, l + delta) for delta = 1 .. 8 (delta = 8 twice, as each other's
-// adjoint), across the groups (slot l, slot 16 + l + delta) for delta = 0 ..
-// 15; lane l of a row of 16 lanes holds slot l's, a row holds two neighbouring
-// deltas.  Between rounds the q columns move on by one slot, so with entries
-// a = G(p_i, p_j), b = G(p_i, q_j), c = G(q_i, p_j), e = G(q_i, q_j): a stays,
-// b comes from delta + 1, c from lane l + 1 and delta - 1, e from lane l + 1.
-// Those are register moves and row rotations (DPP); only one b and one c per
-// thread cross rows, through LDS.  V is in registers too, 8 rows of one
-// slot's two columns per thread.  LDS carries the rotation parameters, the
-// row crossings, and G between half-passes (upper triangle, 32 KB), so three
-// solves fit a CU.
+// lie in the registers of wavefronts 0 .. 3, two per thread: inside a group of
+// 16 slots the block (l, l + delta) for delta = 1 .. 8 (delta = 8 twice, as
+// each other's adjoint), across the groups (slot l, slot 16 + l + delta) for
+// delta = 0 .. 15; lane l of a row of 16 lanes holds slot l's, a row holds two
+// neighbouring deltas.  Between rounds the q columns move on by one slot, so
+// with entries a = G(p_i, p_j), b = G(p_i, q_j), c = G(q_i, p_j),
+// e = G(q_i, q_j): a stays, b comes from delta + 1, c from lane l + 1 and
+// delta - 1, e from lane l + 1.  Those are register moves and row rotations
+// (DPP); only one b and one c per thread cross rows, through LDS.  V is in the
+// registers of wavefronts 4 .. 7, EIG_VROWS rows of one slot's two columns per
+// thread.  LDS carries the rotation parameters, the row crossings, and G
+// between half-passes (upper triangle, 32 KB).
 //
 // Rotations without square-root scaling: with V = V~ S and G = S G~ S, S
 // diagonal, x_p' = x_p - alpha x_q and x_q' = x_q + beta x_p (unscaled
@@ -493,16 +493,22 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
 // scales s^2 <- s^2 cos^2 (cos^2 >= 1/2) are multiplied in after 16 rounds.
 // The threads that hold delta = 1 hold the next round's couplings
 // b = G(p_l, q_{l+1}), so they compute the next rotations as soon as their
-// blocks are updated, while the other wavefronts update V: one barrier a round.
+// first block is updated, while the other wavefronts update the rest: one
+// barrier a round.
 //
 // A solve whose couplings all pass the test returns before the first pass.
-// Bound by the vector units' float64 rate: 512 blocks x 32 and 2048 pairs of
-// V entries x 8 multiply-adds per round.
-constexpr int EIG_THREADS = 256;
-constexpr int EIG_ROWS = EIG_THREADS / 16;  // rows of 16 lanes
-// Rows of V per half-wavefront: the first wavefront, which also computes the
-// next rotations, takes 5 (rows 0 .. 9), the others 9 (rows 10 .. 63).
-constexpr int EIG_VROWS = 9, EIG_VROWS0 = 5;
+// Bound by the chain of a round (parameters through LDS, first block, next
+// parameters, barrier: about 2000 clocks with rotations, 700 without), not by
+// the vector units, so G and V go to wavefronts of their own: one wavefront of
+// each per SIMD in place of one that does both in turn, and a V wavefront
+// never waits for the parameters.  The 16 half-pass relayouts through LDS cost
+// 8000 clocks.  Per launch, against 256 threads that hold both: chi 300
+// (10 pairs) 41.5 -> 34.8 us, chi 128 (layers of 4 .. 32 pairs) 57 -> 48 us,
+// chi 1024 (32 pairs, 9 gates at once) 46 -> 46 us, where two such workgroups
+// share a CU as three of the smaller ones did.
+constexpr int EIG_THREADS = 512;  // wavefronts 0 .. 3 hold G, 4 .. 7 hold V
+constexpr int EIG_ROWS = 16;      // rows of 16 lanes that hold G
+constexpr int EIG_VROWS = PW / 8; // rows of V held by each half-wavefront
 constexpr int EIG_EVERY = 4;  // tournament rounds between passes inside the blocks
 constexpr int EIG_UPPER = PW * (PW - 1) / 2;
 
@@ -571,13 +577,26 @@ struct EigShared {
   int sweep_rot;                // some rotation in the current inner sweep
 };
 
-// The passes of one solve, for the first wavefront (W0: NV = 5 rows of V per
-// half, and the next rotations) or one of the others (9 rows).  Returns
-// whether the first inner sweep rotated; then V is written.
-template <int NV, bool W0>
-__device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int bits, double tol2,
-                                          double small, double2 *V, unsigned &nrot) {
-  const int tid = threadIdx.x, lane = tid & 63;
+// A solve's walk over its half-passes; the wavefronts that hold G and those
+// that hold V take the same steps and meet the same barriers.
+struct EigWalk {
+  int b, v;  // bit and half of the current half-pass
+  int t;
+  __device__ __forceinline__ bool next(int bits) {  // bits 4 .. 0, then 5; two halves each
+    while (++t < 12) {
+      b = t < 10 ? 4 - (t >> 1) : 5;
+      v = t & 1;
+      if ((bits >> b) & 1) return true;
+    }
+    return false;
+  }
+};
+
+// Wavefronts 0 .. 3: G's blocks and, in the first one (W0), the rotations.
+template <bool W0>
+__device__ __forceinline__ int eig_solve_g(const GateDesc &d, EigShared &S, int bits, double tol2,
+                                           double small, unsigned &nrot) {
+  const int tid = threadIdx.x;
   const int l = tid & 15, rho = tid >> 4, gpar = rho & 1, u = rho >> 1;
   const bool intra = u < 4;        // wavefronts 0, 1; the others: across the groups
   const bool param = W0 && u == 0; // delta = 1: holds the next couplings
@@ -586,55 +605,15 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
   const int si = intra ? 16 * gpar + l : l;
   const int gj = intra ? 16 * gpar : 16;
   const int sj0 = gj + ((l + del) & 15), sj1 = gj + ((l + del + 1) & 15);
-  const int sv = lane & 31;  // slot of this thread's V entries (= si when intra)
   // rows that b and c come from (the rows of delta + 2 and delta - 2)
   const int rb = intra ? (u < 3 ? rho + 2 : rho) : 8 + ((rho - 7) & 7);
   const int rc = intra ? (u > 0 ? rho - 2 : rho) : 8 + ((rho - 1) & 7);
-  const int vrow0 = W0 ? (tid >> 5) * NV : 2 * EIG_VROWS0 + ((tid >> 5) - 2) * NV;
-  double2 vp[NV], vq[NV];
-  int lb = __ffs(bits) - 1, lv = 0;  // labelling of V's columns (bit, half-pass): any to start
-  {
-    const int cp = bit_ins(sv, lb, 0), cq = bit_ins(sv, lb, 1);
-#pragma unroll
-    for (int h = 0; h < NV; h++) {
-      vp[h] = make_double2(vrow0 + h == cp ? 1.0 : 0.0, 0.0);
-      vq[h] = make_double2(vrow0 + h == cq ? 1.0 : 0.0, 0.0);
-    }
-  }
   int first_rot = 0;
   for (int sweep = 0; sweep < d.innerSweeps; sweep++) {
     if (tid == 0) S.sweep_rot = 0;
-    for (int t = 0; t < 12; t++) {
-      // bits 4 .. 0, then 5; two half-passes each
-      const int b = t < 10 ? 4 - (t >> 1) : 5, v = t & 1;
-      if (!((bits >> b) & 1)) continue;
-      // V's columns to this half-pass's slots
-      if (b == lb) {
-        if (v != lv) {
-#pragma unroll
-          for (int h = 0; h < NV; h++)
-            vq[h] = make_double2(__shfl_xor(vq[h].x, 16, 64), __shfl_xor(vq[h].y, 16, 64));
-        }
-      } else {
-        const int cp = bit_ins(sv, b, 0), cq = bit_ins(sv ^ (v << 4), b, 1);
-        const bool pq = (cp >> lb) & 1, qq = (cq >> lb) & 1;  // held as a q column until now
-        const int ps = (lane & 32) | (bit_del(cp, lb) ^ (pq ? lv << 4 : 0));
-        const int qs = (lane & 32) | (bit_del(cq, lb) ^ (qq ? lv << 4 : 0));
-#pragma unroll
-        for (int h = 0; h < NV; h++) {
-          __builtin_amdgcn_sched_barrier(0);  // one row's permutes at a time (registers)
-          const double px = __shfl(vp[h].x, ps, 64), py = __shfl(vp[h].y, ps, 64);
-          const double qx = __shfl(vq[h].x, ps, 64), qy = __shfl(vq[h].y, ps, 64);
-          const double rx = __shfl(vp[h].x, qs, 64), ry = __shfl(vp[h].y, qs, 64);
-          const double tx = __shfl(vq[h].x, qs, 64), ty = __shfl(vq[h].y, qs, 64);
-          vp[h] = make_double2(pq ? qx : px, pq ? qy : py);
-          vq[h] = make_double2(qq ? tx : rx, qq ? ty : ry);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      lb = b;
-      lv = v;
-      const int vx = v << 4;
+    EigWalk at{0, 0, -1};
+    while (at.next(bits)) {
+      const int b = at.b, vx = at.v << 4;
       const int pi = bit_ins(si, b, 0), qi = bit_ins(si ^ vx, b, 1);
       const int pj0 = bit_ins(sj0, b, 0), qj0 = bit_ins(sj0 ^ vx, b, 1);
       const int pj1 = bit_ins(sj1, b, 0), qj1 = bit_ins(sj1 ^ vx, b, 1);
@@ -661,68 +640,66 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
       // g has w = 2 sign(delta) / (|delta| + sqrt(delta^2 + 4h)), tangent
       // w |g|, cos^2 = 1 / (1 + w^2 h); the new diagonal is (x - w h,
       // y + w h).  On the unscaled columns alpha = w conj(g~) s_q^2, beta =
-      // w g~ s_p^2.
-      auto params = [&](int w) {
-        int act = 0;
-        double2 al = make_double2(0.0, 0.0), be = make_double2(0.0, 0.0);
-        gres = gc;
+      // w g~ s_p^2.  The whole first wavefront computes and the parameter
+      // threads' results count, without branches per thread, so that the
+      // chain overlaps the update of the second block; a round in which no
+      // coupling acts leaves after the test (three rounds of four are so).
+      auto params = [&](int w, bool live) {
         const double h = s2p * s2q * cabs2(gc);
-        if (dp > small && dq > small && h > tol2 * dp * dq) {
-          act = 1;
-          const double delta = dq - dp;
-          const double tw = copysign(
-              2.0 * fast_rcp(fabs(delta) + fast_sqrt(fma(delta, delta, 4.0 * h))), delta);
-          const double wh = tw * h, c2 = fast_rcp(fma(tw, wh, 1.0));
-          const double wq = tw * s2q, wp = tw * s2p;
-          al = make_double2(wq * gc.x, -wq * gc.y);
-          be = make_double2(wp * gc.x, wp * gc.y);
-          dp -= wh;
-          dq += wh;
-          s2p *= c2;
-          s2q *= c2;
-          gres = make_double2(0.0, 0.0);
-          nrot++;
-        }
-        S.prm[w][0][si] = al;
-        S.prm[w][1][si] = be;
+        const bool act = live && param && dp > small && dq > small && h > tol2 * dp * dq;
         const unsigned long long m = __ballot(act);
-        if (tid == 0) {
-          S.anyr[w] = m != 0ull;
-          if (m) S.sweep_rot = 1;
+        if (tid == 0) S.anyr[w] = m != 0ull;
+        gres = gc;
+        if (!m) return;
+        if (tid == 0) S.sweep_rot = 1;
+        const double delta = dq - dp;
+        const double tw = copysign(
+            2.0 * fast_rcp(fabs(delta) + fast_sqrt(fma(delta, delta, 4.0 * h))), delta);
+        const double wq = act ? tw * s2q : 0.0, wp = act ? tw * s2p : 0.0;
+        if (param) {
+          S.prm[w][0][si] = make_double2(wq * gc.x, -wq * gc.y);
+          S.prm[w][1][si] = make_double2(wp * gc.x, wp * gc.y);
         }
+        const double wh = tw * h, c2 = fast_rcp(fma(tw, wh, 1.0));
+        gres = act ? make_double2(0.0, 0.0) : gc;
+        dp = act ? dp - wh : dp;
+        dq = act ? dq + wh : dq;
+        s2p = act ? s2p * c2 : s2p;
+        s2q = act ? s2q * c2 : s2q;
+        nrot += act;
       };
-      if (param) params(0);
+      if (W0) params(0, true);
       __syncthreads();
 #pragma nounroll
       for (int r = 0; r < 16; r++) {
         const int w = r & 1;
-        const bool any = S.anyr[w] != 0;
         double2 cg = make_double2(0.0, 0.0);
-        if (any) {
+        if (S.anyr[w]) {
           const double2 ali = S.prm[w][0][si], bei = S.prm[w][1][si];
-          blk_rotate(B0, ali, bei, S.prm[w][0][sj0], S.prm[w][1][sj0]);
-          blk_rotate(B1, ali, bei, S.prm[w][0][sj1], S.prm[w][1][sj1]);
-        }
-        S.xb[w][rho][l] = B0.b;
-        S.xc[w][rho][l] = B1.c;
-        if (param) {  // next round's couplings and q columns
-          cg = cconj(row_next<1>(gres));
-          gc = B0.b;
-          dq = row_next<1>(dq);
-          s2q = row_next<1>(s2q);
-          if (r < 15) params(w ^ 1);
-        }
-        if (any) {
-          const double2 al = S.prm[w][0][sv], be = S.prm[w][1][sv];
-#pragma unroll
-          for (int h = 0; h < NV; h++) {
-            const double2 x = cfms(vp[h], al, vq[h]);
-            vq[h] = cfmad(vq[h], be, vp[h]);
-            vp[h] = x;
+          const double2 al0 = S.prm[w][0][sj0], be0 = S.prm[w][1][sj0];
+          const double2 al1 = S.prm[w][0][sj1], be1 = S.prm[w][1][sj1];
+          blk_rotate(B0, ali, bei, al0, be0);
+          S.xb[w][rho][l] = B0.b;
+          if (W0) {  // next round's couplings and q columns
+            cg = cconj(row_next<1>(gres));
+            gc = B0.b;
+            dq = row_next<1>(dq);
+            s2q = row_next<1>(s2q);
+            params(w ^ 1, r < 15);
+          }
+          blk_rotate(B1, ali, bei, al1, be1);
+          S.xc[w][rho][l] = B1.c;
+        } else {
+          S.xb[w][rho][l] = B0.b;
+          S.xc[w][rho][l] = B1.c;
+          if (W0) {
+            cg = cconj(row_next<1>(gres));
+            gc = B0.b;
+            dq = row_next<1>(dq);
+            s2q = row_next<1>(s2q);
+            params(w ^ 1, r < 15);
           }
         }
-#pragma unroll
-        for (int h = 0; h < NV; h++) vq[h] = row_next<1>(vq[h]);
         // the q columns move on by one slot
         const double2 c8 = cconj(row_next<9>(B0.c));  // delta = 8: b from the adjoint of c at 7
         const double2 c1 = row_next<1>(B0.c);
@@ -738,7 +715,7 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
       }
       // back to LDS with the scales multiplied in
       if (param) {
-        const double fp = sqrt(s2p), fq = sqrt(s2q);
+        const double fp = fast_sqrt(s2p), fq = fast_sqrt(s2q);
         S.sca[0][si] = fp;
         S.sca[1][si] = fq;
         S.dg[pi] = dp;
@@ -761,14 +738,6 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
         gput(S.Gs, qi, pj1, cscale(B1.c, fqi * fp));
         gput(S.Gs, qi, qj1, cscale(B1.e, fqi * fq));
       }
-      {
-        const double fp = S.sca[0][sv], fq = S.sca[1][sv];
-#pragma unroll
-        for (int h = 0; h < NV; h++) {
-          vp[h] = cscale(vp[h], fp);
-          vq[h] = cscale(vq[h], fq);
-        }
-      }
       __syncthreads();
     }
     const int cont = S.sweep_rot;  // every thread reads before anyone clears it
@@ -776,10 +745,89 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
     __syncthreads();
     if (!cont) break;
   }
+  return first_rot;
+}
+
+// Wavefronts 4 .. 7: V, EIG_VROWS rows of one slot's two columns per thread.
+__device__ __forceinline__ int eig_solve_v(const GateDesc &d, EigShared &S, int bits, double2 *V) {
+  const int lane = threadIdx.x & 63, sv = lane & 31;
+  const int vrow0 = ((threadIdx.x >> 5) - 8) * EIG_VROWS;
+  double2 vp[EIG_VROWS], vq[EIG_VROWS];
+  int lb = __ffs(bits) - 1, lv = 0;  // labelling of V's columns (bit, half-pass): any to start
+  {
+    const int cp = bit_ins(sv, lb, 0), cq = bit_ins(sv, lb, 1);
+#pragma unroll
+    for (int h = 0; h < EIG_VROWS; h++) {
+      vp[h] = make_double2(vrow0 + h == cp ? 1.0 : 0.0, 0.0);
+      vq[h] = make_double2(vrow0 + h == cq ? 1.0 : 0.0, 0.0);
+    }
+  }
+  int first_rot = 0;
+  for (int sweep = 0; sweep < d.innerSweeps; sweep++) {
+    EigWalk at{0, 0, -1};
+    while (at.next(bits)) {
+      const int b = at.b, v = at.v;
+      // V's columns to this half-pass's slots
+      if (b == lb) {
+        if (v != lv) {
+#pragma unroll
+          for (int h = 0; h < EIG_VROWS; h++)
+            vq[h] = swap_rows(vq[h]);
+        }
+      } else {
+        const int cp = bit_ins(sv, b, 0), cq = bit_ins(sv ^ (v << 4), b, 1);
+        const bool pq = (cp >> lb) & 1, qq = (cq >> lb) & 1;  // held as a q column until now
+        const int ps = (lane & 32) | (bit_del(cp, lb) ^ (pq ? lv << 4 : 0));
+        const int qs = (lane & 32) | (bit_del(cq, lb) ^ (qq ? lv << 4 : 0));
+#pragma unroll
+        for (int h = 0; h < EIG_VROWS; h++) {
+          __builtin_amdgcn_sched_barrier(0);  // one row's permutes at a time (registers)
+          const double px = __shfl(vp[h].x, ps, 64), py = __shfl(vp[h].y, ps, 64);
+          const double qx = __shfl(vq[h].x, ps, 64), qy = __shfl(vq[h].y, ps, 64);
+          const double rx = __shfl(vp[h].x, qs, 64), ry = __shfl(vp[h].y, qs, 64);
+          const double tx = __shfl(vq[h].x, qs, 64), ty = __shfl(vq[h].y, qs, 64);
+          vp[h] = make_double2(pq ? qx : px, pq ? qy : py);
+          vq[h] = make_double2(qq ? tx : rx, qq ? ty : ry);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lb = b;
+      lv = v;
+      __syncthreads();
+#pragma nounroll
+      for (int r = 0; r < 16; r++) {
+        const int w = r & 1;
+        if (S.anyr[w]) {
+          const double2 al = S.prm[w][0][sv], be = S.prm[w][1][sv];
+#pragma unroll
+          for (int h = 0; h < EIG_VROWS; h++) {
+            const double2 x = cfms(vp[h], al, vq[h]);
+            vq[h] = cfmad(vq[h], be, vp[h]);
+            vp[h] = x;
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < EIG_VROWS; h++) vq[h] = row_next<1>(vq[h]);
+        __syncthreads();
+      }
+      __syncthreads();  // the scales
+      const double fp = S.sca[0][sv], fq = S.sca[1][sv];
+#pragma unroll
+      for (int h = 0; h < EIG_VROWS; h++) {
+        vp[h] = cscale(vp[h], fp);
+        vq[h] = cscale(vq[h], fq);
+      }
+      __syncthreads();
+    }
+    const int cont = S.sweep_rot;
+    if (sweep == 0) first_rot = cont;
+    __syncthreads();
+    if (!cont) break;
+  }
   if (first_rot) {
     const int cp = bit_ins(sv, lb, 0), cq = bit_ins(sv ^ (lv << 4), lb, 1);
 #pragma unroll
-    for (int h = 0; h < NV; h++) {
+    for (int h = 0; h < EIG_VROWS; h++) {
       V[(vrow0 + h) * PW + cp] = vp[h];
       V[(vrow0 + h) * PW + cq] = vq[h];
     }
@@ -787,7 +835,7 @@ __device__ __forceinline__ int eig_passes(const GateDesc &d, EigShared &S, int b
   return first_rot;
 }
 
-__global__ __launch_bounds__(EIG_THREADS, 2) void k_eig(const GateDesc *descs, int round,
+__global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, int round,
                                                         int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
@@ -823,10 +871,13 @@ __global__ __launch_bounds__(EIG_THREADS, 2) void k_eig(const GateDesc *descs, i
   int rotated = 0;
   if (__syncthreads_or(need)) {
     double2 *V = d.V + (size_t)pairIdx * (PW * PW);
-    if (__builtin_amdgcn_readfirstlane(tid) < 64)  // uniform per wavefront
-      rotated = eig_passes<EIG_VROWS0, true>(d, S, bits, tol2, small, V, nrot);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave == 0)
+      rotated = eig_solve_g<true>(d, S, bits, tol2, small, nrot);
+    else if (wave < 4)
+      rotated = eig_solve_g<false>(d, S, bits, tol2, small, nrot);
     else
-      rotated = eig_passes<EIG_VROWS, false>(d, S, bits, tol2, small, V, nrot);
+      rotated = eig_solve_v(d, S, bits, V);
   }
   if (d.ctr && tid < 64) {
     // fold the per-thread counts of the first wavefront, one atomic per pair

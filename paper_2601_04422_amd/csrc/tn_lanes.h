@@ -21,6 +21,17 @@ __device__ __forceinline__ double2 row_next(double2 x) {
   return make_double2(row_next<N>(x.x), row_next<N>(x.y));
 }
 
+// Value of lane l ^ 16 (rows of 16 lanes exchanged in pairs), in registers.
+__device__ __forceinline__ double swap_rows(double x) {
+  const bool odd = threadIdx.x & 16;
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+  return __hiloint2double(odd ? hi[0] : hi[1], odd ? lo[0] : lo[1]);
+}
+__device__ __forceinline__ double2 swap_rows(double2 x) {
+  return make_double2(swap_rows(x.x), swap_rows(x.y));
+}
+
 // Sums over the 64 lanes of a wavefront of N values per lane (N = 16, 32, 64),
 // transposed on the way: lane l ends with the sum of value l / (64 / N).  Each
 // step halves the values a lane holds (it keeps one half and hands the other to
