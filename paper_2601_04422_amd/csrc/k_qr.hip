@@ -54,16 +54,31 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // ---------------------------------------------------------------- panel
 
-constexpr int QP_THREADS = 512;
-constexpr int QP_RPT = QR_MAX_ROWS / QP_THREADS;  // rows per thread
-constexpr int QP_WAVES = QP_THREADS / 64;
-
 // Factor columns j0 .. j0+w-1 (rows j0 ..) of one gate's matrix: one
 // workgroup per gate, the panel in registers (thread t holds panel rows
-// t, t + 512, ...).  Writes R's panel rows, the reflectors below the diagonal
-// and the panel's T factor.
-__global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, int stage,
-                                                        int panel) {
+// t, t + THREADS, ...).  Writes R's panel rows, the reflectors below the
+// diagonal and the panel's T factor.
+//
+// Gates with complex64 sites.  The order of every sum is fixed: over a
+// thread's rows 512 apart, the halving tree of a wavefront, then the
+// wavefronts in turn (rows that do not exist add zeros, so fewer threads or
+// rows per thread change nothing).  The sites these gates write are rounded to
+// float32, so another order would show in every later readout at 1e-8.  Two
+// sums a column, the norm below the diagonal and then v^H a_p and v_p^H v;
+// after each one barrier, and every wavefront computes what follows by itself.
+// Bound by that chain (two reductions and barriers, a square root and three
+// divisions a column).  Against four barriers and a thread that computes for
+// all (one kernel for every height): 49 -> 12.4 us up to 256 rows, 49 -> 17.6 up
+// to 512.
+// Keeps the compiler from folding what x was computed from (signs, products)
+// into the expressions that use it, where another multiply-add would be fused.
+__device__ __forceinline__ void as_loaded(double2 &x) {
+  asm("" : "+v"(x.x), "+v"(x.y));
+}
+
+template <int THREADS, int RPT>
+__global__ __launch_bounds__(THREADS) void k_qr_panel(const GateDesc *descs, int stage, int panel) {
+  static_assert(RPT == 1 || THREADS == 512, "a thread's rows are 512 apart");
   const GateDesc &d = descs[blockIdx.x];
   if (!d.qr || d.storage == 0) return;
   const QrView q = qr_view(d, stage);
@@ -72,23 +87,23 @@ __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, 
   const int w = min(QNB, q.cols - j0);
   const int nr = q.rows - j0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int WAVES = THREADS / 64;
+  __shared__ double rednorm[2][WAVES];          // by column parity
+  __shared__ double reddot[2][WAVES][2 * QNB];
+  __shared__ double2 top[2];                    // the diagonal entry
 
-  __shared__ double2 red[QP_WAVES][QNB];
-  __shared__ double2 bsum[QNB];
-  __shared__ double2 Ts[QNB][QNB];
-  __shared__ double2 s_alpha, s_tau, s_scale;
-  __shared__ double s_beta;
-
-  double2 a[QP_RPT][QNB];
+  double2 a[RPT][QNB];
 #pragma unroll
-  for (int i = 0; i < QP_RPT; i++) {
-    const int lr = tid + QP_THREADS * i;
+  for (int i = 0; i < RPT; i++) {
+    const int lr = tid + THREADS * i;
 #pragma unroll
     for (int c = 0; c < QNB; c++)
       a[i][c] = (lr < nr && c < w) ? q.A[(size_t)(j0 + c) * q.ld + j0 + lr]
                                    : make_double2(0.0, 0.0);
   }
-  if (tid < QNB * QNB) Ts[tid / QNB][tid % QNB] = make_double2(0.0, 0.0);
+  double2 trow[QNB];  // thread t < 8: row t of T
+#pragma unroll
+  for (int c = 0; c < QNB; c++) trow[c] = make_double2(0.0, 0.0);
 
 #pragma unroll
   for (int c = 0; c < QNB; c++) {
@@ -96,43 +111,39 @@ __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, 
     // ||x||^2 below the diagonal of column c
     double xn = 0.0;
 #pragma unroll
-    for (int i = 0; i < QP_RPT; i++) {
-      const int lr = tid + QP_THREADS * i;
+    for (int i = 0; i < RPT; i++) {
+      const int lr = tid + THREADS * i;
       if (lr > c) xn += cabs2(a[i][c]);
     }
-    xn = wave_sum(xn);
-    if (tid == c) s_alpha = a[0][c];
-    if (lane == 0) red[wave][0] = make_double2(xn, 0.0);
+    xn = wave_total(xn);
+    if (tid == c) top[c & 1] = a[0][c];
+    if (lane == 0) rednorm[c & 1][wave] = xn;
     __syncthreads();
-    if (tid == 0) {
-      double x2 = 0.0;
-      for (int v = 0; v < QP_WAVES; v++) x2 += red[v][0].x;
-      const double2 al = s_alpha;
-      if (x2 == 0.0 && al.y == 0.0) {  // already triangular: H = I
-        s_tau = make_double2(0.0, 0.0);
-        s_beta = al.x;
-        s_scale = make_double2(0.0, 0.0);
-      } else {
-        const double beta = -copysign(sqrt(cabs2(al) + x2), al.x);
-        s_tau = make_double2((beta - al.x) / beta, -al.y / beta);
-        const double2 dn = make_double2(al.x - beta, al.y);  // alpha - beta
-        const double inv = 1.0 / cabs2(dn);
-        s_scale = make_double2(dn.x * inv, -dn.y * inv);  // 1 / (alpha - beta)
-        s_beta = beta;
-      }
-    }
-    __syncthreads();
-    const double2 tau = s_tau, scale = s_scale;
-    // reflector below the diagonal, beta on it; vr = v at this thread's rows
-    double2 vr[QP_RPT];
+    double x2 = 0.0;
 #pragma unroll
-    for (int i = 0; i < QP_RPT; i++) {
-      const int lr = tid + QP_THREADS * i;
+    for (int v = 0; v < WAVES; v++) x2 += rednorm[c & 1][v];
+    const double2 al = top[c & 1];
+    double2 tau = make_double2(0.0, 0.0), scale = tau;
+    double beta = al.x;
+    if (!(x2 == 0.0 && al.y == 0.0)) {  // else already triangular: H = I
+      beta = -copysign(sqrt(cabs2(al) + x2), al.x);
+      tau = make_double2((beta - al.x) / beta, -al.y / beta);
+      const double2 dn = make_double2(al.x - beta, al.y);  // alpha - beta
+      const double inv = 1.0 / cabs2(dn);
+      scale = make_double2(dn.x * inv, -dn.y * inv);  // 1 / (alpha - beta)
+    }
+    as_loaded(tau);
+    as_loaded(scale);
+    // reflector below the diagonal, beta on it; vr = v at this thread's rows
+    double2 vr[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; i++) {
+      const int lr = tid + THREADS * i;
       if (lr > c) {
         a[i][c] = cmul(a[i][c], scale);
         vr[i] = a[i][c];
       } else if (lr == c) {
-        a[i][c] = make_double2(s_beta, 0.0);
+        a[i][c] = make_double2(beta, 0.0);
         vr[i] = make_double2(1.0, 0.0);
       } else {
         vr[i] = make_double2(0.0, 0.0);
@@ -140,54 +151,53 @@ __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, 
     }
     // one reduction for both: s_p = v^H a_p (p > c, to update the panel) and
     // g_p = v_p^H v (p < c, for the T factor)
-    double2 part[QNB];
+    double part[2 * QNB];
 #pragma unroll
     for (int p = 0; p < QNB; p++) {
       double2 acc = make_double2(0.0, 0.0);
       if (p != c && p < w) {
 #pragma unroll
-        for (int i = 0; i < QP_RPT; i++) {
+        for (int i = 0; i < RPT; i++) {
           if (p > c)
             cfmac(acc, vr[i], a[i][p]);  // conj(v) a_p
           else
             cfmac(acc, a[i][p], vr[i]);  // conj(v_p) v (rows >= c, where v_p is stored)
         }
       }
-      part[p] = make_double2(wave_sum(acc.x), wave_sum(acc.y));
+      part[2 * p] = acc.x;
+      part[2 * p + 1] = acc.y;
     }
-    if (lane == 0) {
+    const double mine = wave_sums<2 * QNB, true>(part);  // lane l: value l / 4
+    if ((lane & 3) == 0) reddot[c & 1][wave][lane >> 2] = mine;
+    __syncthreads();
+    double tot = 0.0;
 #pragma unroll
-      for (int p = 0; p < QNB; p++) red[wave][p] = part[p];
-    }
-    __syncthreads();
-    if (tid < QNB) {
-      double2 s = make_double2(0.0, 0.0);
-      for (int v = 0; v < QP_WAVES; v++) s = cadd(s, red[v][tid]);
-      bsum[tid] = s;
-    }
-    __syncthreads();
-    // a_p <- a_p - conj(tau) v s_p for the later panel columns
+    for (int v = 0; v < WAVES; v++) tot += reddot[c & 1][v][lane & 15];
+    // a_p <- a_p - conj(tau) v s_p for the later panel columns;
+    // T(0:c, c) = -tau T(0:c, 0:c) g(0:c), T(c, c) = tau
     const double2 ctau = cconj(tau);
+    double2 tc = make_double2(0.0, 0.0);
 #pragma unroll
     for (int p = 0; p < QNB; p++) {
-      if (p > c && p < w) {
-        const double2 f = cmul(ctau, bsum[p]);
+      if (p == c || p >= w) continue;
+      const double2 sp = make_double2(lane_value(tot, 2 * p), lane_value(tot, 2 * p + 1));
+      if (p > c) {
+        const double2 f = cmul(ctau, sp);
 #pragma unroll
-        for (int i = 0; i < QP_RPT; i++) a[i][p] = csub(a[i][p], cmul(vr[i], f));
+        for (int i = 0; i < RPT; i++) a[i][p] = csub(a[i][p], cmul(vr[i], f));
+      } else {
+        const double2 t = trow[p];
+        tc.x += fma(t.x, sp.x, -(t.y * sp.y));
+        tc.y += fma(t.y, sp.x, t.x * sp.y);
       }
     }
-    // T(0:c, c) = -tau T(0:c, 0:c) g(0:c), T(c, c) = tau
-    if (tid < c) {
-      double2 s = make_double2(0.0, 0.0);
-      for (int l = tid; l < c; l++) s = cadd(s, cmul(Ts[tid][l], bsum[l]));
-      Ts[tid][c] = cmul(make_double2(-tau.x, -tau.y), s);
-    }
-    if (tid == c) Ts[c][c] = tau;
-    __syncthreads();
+    trow[c] = tid < c ? make_double2(fma(tau.y, tc.y, -(tau.x * tc.x)),
+                                     fma(-tau.y, tc.x, -(tau.x * tc.y)))
+                      : (tid == c ? tau : make_double2(0.0, 0.0));
   }
 #pragma unroll
-  for (int i = 0; i < QP_RPT; i++) {
-    const int lr = tid + QP_THREADS * i;
+  for (int i = 0; i < RPT; i++) {
+    const int lr = tid + THREADS * i;
     if (lr < nr) {
 #pragma unroll
       for (int c = 0; c < QNB; c++)
@@ -195,7 +205,10 @@ __global__ __launch_bounds__(QP_THREADS) void k_qr_panel(const GateDesc *descs, 
     }
   }
   double2 *T = qr_tfac(d, stage, panel);
-  if (tid < QNB * QNB) T[tid] = Ts[tid / QNB][tid % QNB];
+  if (tid < QNB) {
+#pragma unroll
+    for (int c = 0; c < QNB; c++) T[tid * QNB + c] = trow[c];
+  }
 }
 
 // The same panel with one reduction and one barrier per column (gates with
@@ -334,23 +347,29 @@ __global__ __launch_bounds__(THREADS) void k_qr_panel1(const GateDesc *descs, in
 void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int panel, int max_rows,
                      bool c128, bool c64) {
   if (ng <= 0) return;
-  if (c64)
-    hipLaunchKernelGGL(k_qr_panel, dim3(ng), dim3(QP_THREADS), 0, st, d, stage, panel);
-  if (!c128) return;
   const int left = max_rows - panel * QNB;
-  auto run = [&](auto threads, auto rpt) {
+  using std::integral_constant;
+  auto run1 = [&](auto threads, auto rpt) {
     constexpr int T = decltype(threads)::value, R = decltype(rpt)::value;
     hipLaunchKernelGGL((k_qr_panel1<T, R>), dim3(ng), dim3(T), 0, st, d, stage, panel);
   };
-  using std::integral_constant;
-  if (left <= 256)
-    run(integral_constant<int, 256>(), integral_constant<int, 1>());
-  else if (left <= 512)
-    run(integral_constant<int, 256>(), integral_constant<int, 2>());
-  else if (left <= 1024)
-    run(integral_constant<int, 512>(), integral_constant<int, 2>());
-  else
-    run(integral_constant<int, 512>(), integral_constant<int, 4>());
+  auto run = [&](auto threads, auto rpt) {
+    constexpr int T = decltype(threads)::value, R = decltype(rpt)::value;
+    hipLaunchKernelGGL((k_qr_panel<T, R>), dim3(ng), dim3(T), 0, st, d, stage, panel);
+  };
+  if (left <= 256) {
+    if (c128) run1(integral_constant<int, 256>(), integral_constant<int, 1>());
+    if (c64) run(integral_constant<int, 256>(), integral_constant<int, 1>());
+  } else if (left <= 512) {
+    if (c128) run1(integral_constant<int, 256>(), integral_constant<int, 2>());
+    if (c64) run(integral_constant<int, 512>(), integral_constant<int, 1>());
+  } else if (left <= 1024) {
+    if (c128) run1(integral_constant<int, 512>(), integral_constant<int, 2>());
+    if (c64) run(integral_constant<int, 512>(), integral_constant<int, 2>());
+  } else {
+    if (c128) run1(integral_constant<int, 512>(), integral_constant<int, 4>());
+    if (c64) run(integral_constant<int, 512>(), integral_constant<int, 4>());
+  }
 }
 
 // ---------------------------------------------------------------- block update
