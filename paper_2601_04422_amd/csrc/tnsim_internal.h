@@ -106,6 +106,11 @@ struct Gate1Desc {
 void launch_init_state(hipStream_t st, void *const *sites_dev_list, int n, int storage,
                        double *const *lam_list_dev, int nb);
 void launch_fill_zero(hipStream_t st, void *p, size_t bytes);
+// bytes (a multiple of 8) of device memory to pinned host memory; the host
+// sees `value` at `flag` (pinned) once they are there
+void launch_fetch(hipStream_t st, void *host, const void *dev, size_t bytes, uint32_t *flag,
+                  uint32_t value);
+void launch_put(hipStream_t st, double2 *dst, double2 value);
 // float64 rate probe: unit 0 = matrix cores (16x16x4), 1 = vector FMA, 2 = both at
 // once, 3 = matrix cores (four-block 4x4x4); returns the flops launched
 double launch_probe(hipStream_t st, int unit, int groups, int iters, double *out);
