@@ -54,8 +54,12 @@ __device__ void apply_1q_body(const Gate1Desc &d, int e) {
   int a = e / d.chiR, b = e - a * d.chiR;
   size_t i0 = ((size_t)a * 2) * d.chiR + b, i1 = i0 + d.chiR;
   double2 x0 = cload(A + i0), x1 = cload(A + i1);
-  double2 y0 = cadd(cmul(d.u[0], x0), cmul(d.u[1], x1));
-  double2 y1 = cadd(cmul(d.u[2], x0), cmul(d.u[3], x1));
+  // the fused multiply-adds written out, so that every kernel rounds alike
+  auto mul = [](double2 u, double2 x) {
+    return make_double2(fma(u.x, x.x, -(u.y * x.y)), fma(u.x, x.y, u.y * x.x));
+  };
+  double2 y0 = cadd(mul(d.u[0], x0), mul(d.u[1], x1));
+  double2 y1 = cadd(mul(d.u[2], x0), mul(d.u[3], x1));
   cstore(A + i0, y0);
   cstore(A + i1, y1);
 }
@@ -73,6 +77,79 @@ __global__ void k_apply_1q(const Gate1Desc *descs) {
 void launch_apply_1q(hipStream_t st, const Gate1Desc *d, int ng, int max_elems) {
   if (ng <= 0 || max_elems <= 0) return;
   hipLaunchKernelGGL(k_apply_1q, dim3((max_elems + 255) / 256, ng), dim3(256), 0, st, d);
+}
+
+// Descriptors as kernel arguments, 1 or GATE1_ARGS per launch (the arguments
+// of a kernel are limited to 4 KB): no staging buffer, no copy to the device
+// and no wait for the buffer, 12 us of a 1-qubit layer.
+constexpr int GATE1_ARGS = 32;
+template <int N>
+struct Gate1Args {
+  Gate1Desc d[N];
+};
+
+template <int N>
+__global__ void k_apply_1q_args(const Gate1Args<N> args) {
+  const Gate1Desc &d = args.d[N == 1 ? 0 : blockIdx.y];
+  int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= d.chiL * d.chiR) return;
+  if (d.storage == 0)
+    apply_1q_body<double2>(d, e);
+  else
+    apply_1q_body<float2>(d, e);
+}
+
+void launch_apply_1q_args(hipStream_t st, const Gate1Desc *d, int ng, int max_elems) {
+  if (ng <= 0 || max_elems <= 0) return;
+  if (ng == 1) {
+    hipLaunchKernelGGL(k_apply_1q_args<1>, dim3((max_elems + 255) / 256), dim3(256), 0, st,
+                       Gate1Args<1>{d[0]});
+    return;
+  }
+  for (int g = 0; g < ng; g += GATE1_ARGS) {
+    const int cnt = std::min(GATE1_ARGS, ng - g);
+    Gate1Args<GATE1_ARGS> a{};
+    std::copy(d + g, d + g + cnt, a.d);
+    hipLaunchKernelGGL(k_apply_1q_args<GATE1_ARGS>, dim3((max_elems + 255) / 256, cnt), dim3(256),
+                       0, st, a);
+  }
+}
+
+// Copies inside device memory, up to COPY_ARGS per launch (blockIdx.y).  Each
+// copy on its own took 2 us and a gap of 3; what a gradient records of a gate
+// at chi = 64 is six of them, a checkpoint two per site.
+constexpr int COPY_ARGS = 32;
+struct CopyArgs {
+  CopyItem c[COPY_ARGS];
+};
+
+__global__ __launch_bounds__(256) void k_copy_list(const CopyArgs args) {
+  const CopyItem &c = args.c[blockIdx.y];
+  const uint64_t *src = (const uint64_t *)c.src;
+  uint64_t *dst = (uint64_t *)c.dst;
+  const size_t total = (size_t)c.words * c.rows, stride = (size_t)gridDim.x * blockDim.x;
+  size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c.rows == 1) {
+    for (; e < total; e += stride) dst[e] = src[e];
+  } else {
+    for (; e < total; e += stride) {
+      const size_t r = e / c.words, w = e - r * c.words;
+      dst[r * c.dpitch + w] = src[r * c.spitch + w];
+    }
+  }
+}
+
+void launch_copy_list(hipStream_t st, const CopyItem *items, int n) {
+  for (int g = 0; g < n; g += COPY_ARGS) {
+    const int cnt = std::min(COPY_ARGS, n - g);
+    CopyArgs a{};
+    std::copy(items + g, items + g + cnt, a.c);
+    size_t most = 0;
+    for (int i = 0; i < cnt; i++) most = std::max(most, (size_t)a.c[i].words * a.c[i].rows);
+    if (!most) continue;
+    const size_t blocks = std::min<size_t>((most + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_copy_list, dim3((unsigned)blocks, cnt), dim3(256), 0, st, a);
+  }
 }
 
 __global__ void k_convert(const void *src, int ss, void *dst, int ds, size_t n) {

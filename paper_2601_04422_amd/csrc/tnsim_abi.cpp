@@ -246,6 +246,9 @@ struct tnsim_mps_s {
   // pin + pin_flag_off and the value each will hold (0 general, 1 + b sweep b)
   size_t pin_flag_off = 0;
   uint32_t fetch_seq[3] = {0, 0, 0};
+  // copies out of `pin` so far, how many of them are known to be done, and
+  // how many preceded the last fetch of each flag
+  uint64_t pin_copies = 0, pin_done = 0, fetch_after[3] = {0, 0, 0};
   bool fetch_poll[3] = {false, false, false};  // the kernel moves it, not a copy
   // second stream of the circuit scheduler: gates admitted into the sweeps
   // are prepared there (own descriptor region and pinned staging buffer)
@@ -435,6 +438,7 @@ uint32_t *fetch_flag(tnsim_mps h, int k) {
 
 tnsim_status fetch(tnsim_mps h, hipStream_t st, void *pin_dst, const void *dev, size_t bytes,
                    int k = 0) {
+  h->fetch_after[k] = h->pin_copies;
   h->fetch_poll[k] = bytes % 8 == 0 && bytes <= FETCH_BYTES;
   if (h->fetch_poll[k]) {
     launch_fetch(st, pin_dst, dev, bytes, fetch_flag(h, k), ++h->fetch_seq[k]);
@@ -454,7 +458,10 @@ tnsim_status fetched(tnsim_mps h, hipStream_t st, int k = 0, hipEvent_t ev = nul
     const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
     do {
       for (int t = 0; t < 32; t++) {
-        if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) == want) return TNSIM_OK;
+        if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) == want) {
+          h->pin_done = std::max(h->pin_done, h->fetch_after[k]);
+          return TNSIM_OK;
+        }
         __builtin_ia32_pause();
       }
     } while (std::chrono::steady_clock::now() < until);
@@ -463,6 +470,24 @@ tnsim_status fetched(tnsim_mps h, hipStream_t st, int k = 0, hipEvent_t ev = nul
     HIPCHK(h, hipEventSynchronize(ev));
   else
     HIPCHK(h, hipStreamSynchronize(st));
+  h->pin_done = std::max(h->pin_done, h->fetch_after[k]);
+  return TNSIM_OK;
+}
+
+// Before the host writes to `pin`: wait until no copy out of it is under way
+// on the handle's stream.  After most gates none is: their results were
+// fetched after the copy of their descriptors.
+tnsim_status pin_free(tnsim_mps h) {
+  if (h->pin_done == h->pin_copies && !h->prof) return TNSIM_OK;
+  HIPCHK(h, hipStreamSynchronize(h->stream));
+  h->pin_done = h->pin_copies;
+  return TNSIM_OK;
+}
+
+// The first `bytes` of `pin` to the device.
+tnsim_status pin_copy(tnsim_mps h, void *dev, size_t bytes) {
+  h->pin_copies++;
+  HIPCHK(h, hipMemcpyAsync(dev, h->pin, bytes, hipMemcpyHostToDevice, h->stream));
   return TNSIM_OK;
 }
 
@@ -550,17 +575,22 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   return d;
 }
 
-// Copy descriptors into the owner's descriptor array.  Waits for the stream
-// first: the pinned staging buffer may still feed an earlier copy.  With
-// `second`, the second stream, its staging buffer and descriptor region.
+// Copy descriptors into the owner's descriptor array, once the pinned staging
+// buffer feeds no earlier copy.  With `second`, the second stream, its staging
+// buffer and descriptor region.
 tnsim_status put_descs(tnsim_mps o, const GateDesc *D, int n, bool second = false) {
-  hipStream_t st = second ? o->stream2 : o->stream;
-  char *pin = second ? o->pin2 : o->pin;
-  HIPCHK(o, hipStreamSynchronize(st));
-  prof_drain(o, second);
-  memcpy(pin, D, sizeof(GateDesc) * n);
-  HIPCHK(o, hipMemcpyAsync(o->at<GateDesc>(second ? o->L.desc2_off : o->L.desc_off), pin,
-                           sizeof(GateDesc) * n, hipMemcpyHostToDevice, st));
+  if (!second) {
+    tnsim_status s = pin_free(o);
+    if (s != TNSIM_OK) return s;
+    prof_drain(o);
+    memcpy(o->pin, D, sizeof(GateDesc) * n);
+    return pin_copy(o, o->at<GateDesc>(o->L.desc_off), sizeof(GateDesc) * n);
+  }
+  HIPCHK(o, hipStreamSynchronize(o->stream2));
+  prof_drain(o, true);
+  memcpy(o->pin2, D, sizeof(GateDesc) * n);
+  HIPCHK(o, hipMemcpyAsync(o->at<GateDesc>(o->L.desc2_off), o->pin2, sizeof(GateDesc) * n,
+                           hipMemcpyHostToDevice, o->stream2));
   return TNSIM_OK;
 }
 
@@ -1061,17 +1091,28 @@ tnsim_status run_1q(tnsim_mps h, const std::vector<std::pair<int, const tnsim_c1
     for (int e = 0; e < 4; e++) d.u[e] = to_d2(gs[k].second[e]);
     maxe = std::max(maxe, d.chiL * d.chiR);
   }
+  // up to four launches with the descriptors as arguments, 4 us each, cost
+  // less than staging them (12 us and one launch)
+  const bool args = D.size() <= 128;
   Gate1Desc *ddev = h->at<Gate1Desc>(h->L.d1_off);
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  prof_drain(h);
-  memcpy(h->pin, D.data(), sizeof(Gate1Desc) * D.size());
-  HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(Gate1Desc) * D.size(), hipMemcpyHostToDevice,
-                           h->stream));
+  if (!args || h->prof) {
+    tnsim_status s = pin_free(h);
+    if (s != TNSIM_OK) return s;
+    prof_drain(h);
+  }
+  if (!args) {
+    memcpy(h->pin, D.data(), sizeof(Gate1Desc) * D.size());
+    tnsim_status s = pin_copy(h, ddev, sizeof(Gate1Desc) * D.size());
+    if (s != TNSIM_OK) return s;
+  }
   double by = 0.0;
   for (auto &d : D) by += 2.0 * (h->L.storage == 0 ? 16.0 : 8.0) * 2.0 * d.chiL * d.chiR;
   {
     ProfScope p(h, TNSIM_K_1Q, 0.0, by);
-    launch_apply_1q(h->stream, ddev, (int)D.size(), maxe);
+    if (args)
+      launch_apply_1q_args(h->stream, D.data(), (int)D.size(), maxe);
+    else
+      launch_apply_1q(h->stream, ddev, (int)D.size(), maxe);
   }
   LAUNCHCHK(h, "apply_1q");
   return TNSIM_OK;
@@ -1579,39 +1620,42 @@ GemmArgs gemm(int M, int N, int K, const void *A, long long sai, long long sak, 
 
 inline double2 cr(double x) { return make_double2(x, 0.0); }
 
+inline CopyItem copy_item(void *dst, const void *src, size_t bytes) {
+  return CopyItem{dst, src, (uint32_t)(bytes / 8), 1, 0, 0};
+}
+
+// The state to or from checkpoint memory, in the current dimensions.
+tnsim_status copy_ckpt(tnsim_mps h, char *base, bool save) {
+  GradState &G = h->grad;
+  const int n = h->L.n;
+  std::vector<CopyItem> items;
+  auto add = [&](void *state, char *ckpt, size_t bytes) {
+    items.push_back(save ? copy_item(ckpt, state, bytes) : copy_item(state, ckpt, bytes));
+  };
+  for (int q = 0; q < n; q++)
+    add(h->site(q), base + G.st_site[q], (size_t)h->dims[q] * 2 * h->dims[q + 1] * h->L.elem);
+  for (int b = 0; b < n - 1; b++)
+    add(h->lam(b), base + G.st_lam[b], sizeof(double) * h->dims[b + 1]);
+  launch_copy_list(h->stream, items.data(), (int)items.size());
+  LAUNCHCHK(h, "checkpoint");
+  return TNSIM_OK;
+}
+
 tnsim_status save_ckpt(tnsim_mps h, int idx) {
   GradState &G = h->grad;
-  char *base = G.ws + G.ckpt0 + G.state_bytes * idx;
-  const int n = h->L.n;
-  for (int q = 0; q < n; q++)
-    HIPCHK(h, hipMemcpyAsync(base + G.st_site[q], h->site(q),
-                             (size_t)h->dims[q] * 2 * h->dims[q + 1] * h->L.elem,
-                             hipMemcpyDeviceToDevice, h->stream));
-  for (int b = 0; b < n - 1; b++)
-    HIPCHK(h, hipMemcpyAsync(base + G.st_lam[b], h->lam(b), sizeof(double) * h->dims[b + 1],
-                             hipMemcpyDeviceToDevice, h->stream));
   G.ckpt_dims[idx] = h->dims;
-  return TNSIM_OK;
+  return copy_ckpt(h, G.ws + G.ckpt0 + G.state_bytes * idx, true);
 }
 
 tnsim_status restore_ckpt(tnsim_mps h, int idx) {
   GradState &G = h->grad;
-  const char *base = G.ws + G.ckpt0 + G.state_bytes * idx;
-  const int n = h->L.n;
   h->dims = G.ckpt_dims[idx];
-  for (int q = 0; q < n; q++)
-    HIPCHK(h, hipMemcpyAsync(h->site(q), base + G.st_site[q],
-                             (size_t)h->dims[q] * 2 * h->dims[q + 1] * h->L.elem,
-                             hipMemcpyDeviceToDevice, h->stream));
-  for (int b = 0; b < n - 1; b++)
-    HIPCHK(h, hipMemcpyAsync(h->lam(b), base + G.st_lam[b], sizeof(double) * h->dims[b + 1],
-                             hipMemcpyDeviceToDevice, h->stream));
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  memcpy(h->pin, h->dims.data(), sizeof(int32_t) * (n + 1));
-  HIPCHK(h, hipMemcpyAsync(h->dims_dev(), h->pin, sizeof(int32_t) * (n + 1),
-                           hipMemcpyHostToDevice, h->stream));
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  return TNSIM_OK;
+  tnsim_status s = copy_ckpt(h, G.ws + G.ckpt0 + G.state_bytes * idx, false);
+  if (s == TNSIM_OK) s = pin_free(h);
+  if (s != TNSIM_OK) return s;
+  const size_t bytes = sizeof(int32_t) * (h->L.n + 1);
+  memcpy(h->pin, h->dims.data(), bytes);
+  return pin_copy(h, h->dims_dev(), bytes);
 }
 
 // Apply gate g of the stored circuit (forward).  With rec != nullptr the
@@ -1635,9 +1679,10 @@ tnsim_status grad_apply(tnsim_mps h, int gi, GradRec *rec) {
       rec->param = G.param[gi];
       rec->axis = G.axis[gi];
       rec->u = u;
-      HIPCHK(h, hipMemcpyAsync(G.ws + rec->off + G.rec_a, h->site(q),
-                               (size_t)rec->chiL * 2 * rec->chiR * h->L.elem,
-                               hipMemcpyDeviceToDevice, st));
+      const CopyItem c = copy_item(G.ws + rec->off + G.rec_a, h->site(q),
+                                   (size_t)rec->chiL * 2 * rec->chiR * h->L.elem);
+      launch_copy_list(st, &c, 1);
+      LAUNCHCHK(h, "record");
     }
     tnsim_c128 um[4];
     for (int e = 0; e < 4; e++) um[e] = tnsim_c128{u.v[e].x, u.v[e].y};
@@ -1655,15 +1700,12 @@ tnsim_status grad_apply(tnsim_mps h, int gi, GradRec *rec) {
     rec->has_lam = (i + 1 <= n - 2);
     for (int e = 0; e < 16; e++) rec->g.v[e] = p.g[e];
     char *r = G.ws + rec->off;
-    HIPCHK(h, hipMemcpyAsync(r + G.rec_a, h->site(i),
-                             (size_t)rec->chiL * 2 * rec->chiM * h->L.elem,
-                             hipMemcpyDeviceToDevice, st));
-    HIPCHK(h, hipMemcpyAsync(r + G.rec_b, h->site(i + 1),
-                             (size_t)rec->chiM * 2 * rec->chiR * h->L.elem,
-                             hipMemcpyDeviceToDevice, st));
-    if (rec->has_lam)
-      HIPCHK(h, hipMemcpyAsync(r + G.rec_lam, h->lam(i + 1), sizeof(double) * rec->chiR,
-                               hipMemcpyDeviceToDevice, st));
+    CopyItem c[3] = {
+        copy_item(r + G.rec_a, h->site(i), (size_t)rec->chiL * 2 * rec->chiM * h->L.elem),
+        copy_item(r + G.rec_b, h->site(i + 1), (size_t)rec->chiM * 2 * rec->chiR * h->L.elem)};
+    if (rec->has_lam) c[2] = copy_item(r + G.rec_lam, h->lam(i + 1), sizeof(double) * rec->chiR);
+    launch_copy_list(st, c, rec->has_lam ? 3 : 2);
+    LAUNCHCHK(h, "record");
   }
   tnsim_status s = run_2q_batch(h, &p, 1, /*force_trans=*/true);
   if (s != TNSIM_OK) return s;
@@ -1674,13 +1716,12 @@ tnsim_status grad_apply(tnsim_mps h, int gi, GradRec *rec) {
     rec->N = sc_pin[0].N;
     const int m = 2 * rec->chiL, nn = 2 * rec->chiR, ldj = pad_to(m, 16);
     char *sl = h->slot(0), *r = G.ws + rec->off;
-    HIPCHK(h, hipMemcpyAsync(r + G.rec_T, sl + L.t_off, sizeof(double2) * (size_t)m * nn,
-                             hipMemcpyDeviceToDevice, st));
-    HIPCHK(h, hipMemcpy2DAsync(r + G.rec_J, sizeof(double2) * m, sl + L.j_off,
-                               sizeof(double2) * ldj, sizeof(double2) * m, m,
-                               hipMemcpyDeviceToDevice, st));
-    HIPCHK(h, hipMemcpyAsync(r + G.rec_sig, sl + L.sig_off, sizeof(double) * m,
-                             hipMemcpyDeviceToDevice, st));
+    const uint32_t w = 2 * m, ldw = 2 * ldj;
+    const CopyItem c[3] = {
+        copy_item(r + G.rec_T, sl + L.t_off, sizeof(double2) * (size_t)m * nn),
+        CopyItem{r + G.rec_J, sl + L.j_off, w, (uint32_t)m, w, ldw},
+        copy_item(r + G.rec_sig, sl + L.sig_off, sizeof(double) * m)};
+    launch_copy_list(st, c, 3);
     launch_sort_all(st, (const double *)(sl + L.sig_off), m, (int *)(r + G.rec_perm));
     LAUNCHCHK(h, "record");
   }
@@ -2242,6 +2283,7 @@ tnsim_status apply_propagate(tnsim_mps h, int q0, int q1, const tnsim_c128 *g) {
   for (int q = a + 1; q <= b; q++) h->dims[q] = rg * od[q];
   HIPCHK(h, hipStreamSynchronize(st));
   memcpy(h->pin, h->dims.data(), sizeof(int32_t) * (L.n + 1));
+  h->pin_copies++;
   HIPCHK(h, hipMemcpyAsync(h->dims_dev(), h->pin, sizeof(int32_t) * (L.n + 1),
                            hipMemcpyHostToDevice, st));
   auto step = [&](int j, int flags, void *a0i, void *a1i, void *a0o, void *a1o) {
@@ -2747,11 +2789,12 @@ tnsim_status tnsim_mps_copy(tnsim_mps dst, tnsim_mps src) {
   const int n = dst->L.n;
   for (int q = 1; q < n; q++)
     if (src->dims[q] > dst->L.dimcap[q]) return TNSIM_E_CAPACITY;
-  HIPCHK(src, hipStreamSynchronize(src->stream));
-  HIPCHK(dst, hipStreamSynchronize(dst->stream));  // the staging buffer is free
+  if (dst->stream != src->stream) HIPCHK(src, hipStreamSynchronize(src->stream));
+  s = pin_free(dst);
+  if (s != TNSIM_OK) return s;
   memcpy(dst->pin, src->dims.data(), sizeof(int32_t) * (n + 1));
-  HIPCHK(dst, hipMemcpyAsync(dst->dims_dev(), dst->pin, sizeof(int32_t) * (n + 1),
-                             hipMemcpyHostToDevice, dst->stream));
+  s = pin_copy(dst, dst->dims_dev(), sizeof(int32_t) * (n + 1));
+  if (s != TNSIM_OK) return s;
   size_t most = 1;
   for (int q = 0; q < n; q++)
     most = std::max(most, (size_t)src->dims[q] * 2 * src->dims[q + 1]);
@@ -3163,6 +3206,7 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
       const int rr = cand[ci];
       for (int g = 0; g < ng; g++) D[g].rotRows = rr;
       memcpy(h->pin, D.data(), sizeof(GateDesc) * ng);
+      h->pin_copies++;
       HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(GateDesc) * ng, hipMemcpyHostToDevice,
                                h->stream));
       launch_rot(h->stream, ddev, ng, 0, npairs, rows, 0, rr);  // warm-up
@@ -3190,6 +3234,7 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
       for (int g = 0; g < ng; g++)
         D[g].Gp = h->at<double2>(L.gp_off) + (size_t)g * ks * L.npairs_max * PW * PW;
       memcpy(h->pin, D.data(), sizeof(GateDesc) * ng);
+      h->pin_copies++;
       HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(GateDesc) * ng, hipMemcpyHostToDevice,
                                h->stream));
       launch_gram(h->stream, ddev, ng, 1 % (2 * npairs - 1), npairs, ks, !full, full);  // warm-up

@@ -115,6 +115,15 @@ void launch_put(hipStream_t st, double2 *dst, double2 value);
 // once, 3 = matrix cores (four-block 4x4x4); returns the flops launched
 double launch_probe(hipStream_t st, int unit, int groups, int iters, double *out);
 void launch_apply_1q(hipStream_t st, const Gate1Desc *d, int ng, int max_elems);
+// the same with the descriptors (host memory) as kernel arguments
+void launch_apply_1q_args(hipStream_t st, const Gate1Desc *d, int ng, int max_elems);
+// Copies on the device: `rows` rows of `words` 8-byte words, pitches in words.
+struct CopyItem {
+  void *dst;
+  const void *src;
+  uint32_t words, rows, dpitch, spitch;
+};
+void launch_copy_list(hipStream_t st, const CopyItem *items, int n);
 void launch_convert(hipStream_t st, const void *src, int src_storage, void *dst, int dst_storage,
                     size_t count);
 // Every site (storage converted) and Schmidt weight of a state in one launch;
