@@ -909,7 +909,8 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
 }
 
 constexpr int EIGF_THREADS = 512;  // 8 wavefronts; two pair solves share a CU
-constexpr int EIGF_VROWS = PW / (EIGF_THREADS / 64);  // rows of V held by each wavefront
+// rows of V held by each row of 16 lanes of the wavefronts 1, 2, 3, 5, 6, 7
+constexpr int EIGF_VROWS = (PW + 23) / 24;
 constexpr int EIGF_OFFD = (PW / 2) * (PW / 2 - 1) / 2;  // off-diagonal 2x2 blocks (i < j)
 
 // Order of the 2016 column pairs of a pair solve (columns 0-31 from block I,
@@ -955,14 +956,26 @@ __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b 
 // 2x2 blocks (rows of pair i x columns of pair j, i < j) are updated by one
 // thread each, and the 2x2 diagonal block of a rotating pair takes its
 // exact values (new diagonal entries, zero coupling) when the rotation is
-// computed.  V lives in registers: wavefront w holds rows 8w .. 8w + 7,
-// lane j column j, and a lane takes its rotation partner's entries by a
-// lane permute, so LDS holds only G and the rotation parameters (69 KB:
-// two solves per CU).  The rotations of round r + 1 are computed by the
-// first wavefront while the others apply round r to V (parameters double-
-// buffered), so a round costs two barriers (one if it rotates nothing).  At
-// most `inner_sweeps` sweeps; the outer sweeps finish what a capped inner
-// solve leaves.
+// computed.  At most `inner_sweeps` sweeps; the outer sweeps finish what a
+// capped inner solve leaves.
+//
+// V lies in registers, by slots of the tournament: a row of 16 lanes holds
+// EIGF_VROWS rows of V, lane l the p and q columns of slots l and 16 + l.  The
+// columns move between neighbouring slots from round to round, by row
+// rotations (DPP): between the blocks slot k takes the q column of slot k + 1
+// (mod 32); inside a block the columns r' + s move down and r' - s up by one
+// slot around the fixed column 31.  So V needs no LDS, which holds G and the
+// rotation parameters (69 KB: two solves per CU).
+//
+// A round takes two barriers: G's blocks on all wavefronts, then the next
+// rotations in the first one (into the other parameter buffer) while six
+// others rotate V and move its columns; one if it rotates nothing.  The
+// wavefronts 0 and 4, which share a SIMD, hold no rows of V, so that nothing
+// delays the parameters' chain.  Bound by that chain (1200 of 3200 clocks a
+// round) and by G's blocks through LDS (1300).  With eight wavefronts that
+// took the partners' entries of V by lane permutes (LDS) after the parameters,
+// a round was 4400 clocks: 124 -> 95 us for 64 pairs, one inner sweep; with V
+// in wavefronts 4 .. 7 99 us, with V rotated beside G 104.
 __global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
@@ -991,10 +1004,20 @@ __global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *de
     else
       dg[r] = x.x;
   });
-  const int lane = tid & 63, vrow0 = (tid >> 6) * EIGF_VROWS;
-  double2 vr[EIGF_VROWS];  // V[vrow0 + h][lane]
+  // rows of V (those from PW on do not exist), P and Q columns of slots l + 16 u
+  constexpr int H = PW / 2;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool hasV = wave & 3;
+  const int l = tid & 15, vrow0 = (((tid >> 4) & 3) + 4 * (wave - 1 - (wave > 4))) * EIGF_VROWS;
+  const bool at0 = l == 0, at15 = l == 15;
+  double2 P[EIGF_VROWS][2], Q[EIGF_VROWS][2];
 #pragma unroll
-  for (int h = 0; h < EIGF_VROWS; h++) vr[h] = make_double2(vrow0 + h == lane ? 1.0 : 0.0, 0.0);
+  for (int h = 0; h < EIGF_VROWS; h++)
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+      P[h][u] = make_double2(vrow0 + h == l + 16 * u ? 1.0 : 0.0, 0.0);
+      Q[h][u] = make_double2(vrow0 + h == H + l + 16 * u ? 1.0 : 0.0, 0.0);
+    }
   if (tid == 0) first_rot = 0;
   __syncthreads();
 
@@ -1038,102 +1061,171 @@ __global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *de
 
   // this thread's off-diagonal block: the upper triangle of 32 x 32 pair
   // indices folded into 16 rows of 31 (row a with row 31 - a)
-  int bi = 0, bj = 0;
+  int bi = 0, bj = 1;
   if (tid < EIGF_OFFD) {
-    const int a = tid / (PW / 2 - 1), col = tid - (PW / 2 - 1) * a;
-    if (col < PW / 2 - 1 - a) {
+    const int a = tid / (H - 1), col = tid - (H - 1) * a;
+    if (col < H - 1 - a) {
       bi = a;
       bj = a + 1 + col;
     } else {
-      bi = PW / 2 - 1 - a;
+      bi = H - 1 - a;
       bj = col + 1;
     }
   }
+  // entry (x, y) of G at its place in the upper triangle; its value or, from
+  // below the diagonal, the conjugate
+  auto place = [](int x, int y) { return min(x, y) * LDG + max(x, y); };
+  auto flip = [](double2 v, bool f) { return make_double2(v.x, f ? -v.y : v.y); };
+  // R = [[c, s e^{i phi}], [-s e^{-i phi}, c]] on columns (p, q); block (row
+  // pair i, column pair j): B <- R_i^H B R_j.  A pair that does not rotate has
+  // c = 1, s = 0, which leaves its entries exactly as they are, so every block
+  // is updated without branches.  The fused multiply-adds are written out:
+  // what complex64 gates store depends on how these round.
+  auto rotate_block = [&](int b, int o00, int o01, int o10, int o11, bool f00, bool f01, bool f10,
+                          bool f11) {
+    const double2 b00 = flip(Gs[o00], f00), b01 = flip(Gs[o01], f01), b10 = flip(Gs[o10], f10),
+                  b11 = flip(Gs[o11], f11);
+    double2 n00, n01, n10, n11;
+    {  // columns: [x_p x_q] R_j
+      const double c = rc[b][bj];
+      const double2 e = rse[b][bj];
+      n00.x = fma(b00.x, c, -fma(b01.x, e.x, b01.y * e.y));
+      n00.y = fma(b00.y, c, -fma(b01.y, e.x, -(b01.x * e.y)));
+      n01.x = fma(b01.x, c, fma(b00.x, e.x, -(b00.y * e.y)));
+      n01.y = fma(b01.y, c, fma(b00.y, e.x, b00.x * e.y));
+      n10.x = fma(b10.x, c, -fma(b11.x, e.x, b11.y * e.y));
+      n10.y = fma(b10.y, c, -fma(b11.y, e.x, -(b11.x * e.y)));
+      n11.x = fma(b11.x, c, fma(b10.x, e.x, -(b10.y * e.y)));
+      n11.y = fma(b11.y, c, fma(b10.y, e.x, b10.x * e.y));
+    }
+    {  // rows: R_i^H [row_p; row_q]
+      const double c = rc[b][bi];
+      const double2 e = rse[b][bi];
+      Gs[o00] = flip(make_double2(fma(c, n00.x, -fma(e.x, n10.x, -(e.y * n10.y))),
+                                  fma(c, n00.y, -fma(e.x, n10.y, e.y * n10.x))), f00);
+      Gs[o01] = flip(make_double2(fma(c, n01.x, -fma(e.x, n11.x, -(e.y * n11.y))),
+                                  fma(c, n01.y, -fma(e.x, n11.y, e.y * n11.x))), f01);
+      Gs[o10] = flip(make_double2(fma(c, n10.x, fma(e.x, n00.x, e.y * n00.y)),
+                                  fma(c, n10.y, fma(e.x, n00.y, -(e.y * n00.x)))), f10);
+      Gs[o11] = flip(make_double2(fma(c, n11.x, fma(e.x, n01.x, e.y * n01.y)),
+                                  fma(c, n11.y, fma(e.x, n01.y, -(e.y * n01.x)))), f11);
+    }
+  };
+  // V <- V R on this thread's slots: new x_p = c x_p - conj(e) x_q, new x_q =
+  // e x_p + c x_q
+  auto rotate_v = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+      const double c = rc[b][l + 16 * u];
+      const double2 e = rse[b][l + 16 * u];
+#pragma unroll
+      for (int h = 0; h < EIGF_VROWS; h++) {
+        const double2 x = P[h][u], y = Q[h][u];
+        P[h][u] = make_double2(fma(c, x.x, fma(-e.x, y.x, -(e.y * y.y))),
+                               fma(c, x.y, fma(e.y, y.x, -e.x * y.y)));
+        Q[h][u] = make_double2(fma(c, y.x, fma(e.x, x.x, -(e.y * x.y))),
+                               fma(c, y.y, fma(e.y, x.x, e.x * x.y)));
+      }
+    }
+  };
+  auto sel = [](bool c, double2 x, double2 y) {
+    return make_double2(c ? x.x : y.x, c ? x.y : y.y);
+  };
 
   for (int sweep = 0; sweep < d.innerSweeps; sweep++) {
     if (tid == 0) sweep_rot = 0;
     if (tid < 64) params(0, 0);
     __syncthreads();
-    for (int r = 0; r < PW - 1; r++) {
+#pragma nounroll
+    for (int r = 0; r < H; r++) {  // between the blocks
       const int b = r & 1;
       const bool any = anyr[b] != 0;
-      if (any && tid < EIGF_OFFD) {
-        // R = [[c, s e^{i phi}], [-s e^{-i phi}, c]] on columns (p, q);
-        // block (row pair i, column pair j): B <- R_i^H B R_j.  A pair that
-        // does not rotate has c = 1, s = 0, which leaves its entries exactly
-        // as they are, so every block is updated without branches.
-        int pi, qi, pj, qj;
-        eigf_pair(r, bi, pi, qi);
-        eigf_pair(r, bj, pj, qj);
-        const int s00 = gslot(pi, pj), s01 = gslot(pi, qj), s10 = gslot(qi, pj), s11 = gslot(qi, qj);
-        double2 b00 = Gs[s00], b01 = Gs[s01], b10 = Gs[s10], b11 = Gs[s11];
-        if (pi > pj) b00 = cconj(b00);
-        if (pi > qj) b01 = cconj(b01);
-        if (qi > pj) b10 = cconj(b10);
-        if (qi > qj) b11 = cconj(b11);
-        {  // columns: [x_p x_q] R_j
-          const double cj = rc[b][bj];
-          const double2 sej = rse[b][bj], secj = cconj(sej);
-          const double2 n00 = csub(cscale(b00, cj), cmul(secj, b01));
-          const double2 n01 = cadd(cmul(sej, b00), cscale(b01, cj));
-          const double2 n10 = csub(cscale(b10, cj), cmul(secj, b11));
-          const double2 n11 = cadd(cmul(sej, b10), cscale(b11, cj));
-          b00 = n00; b01 = n01; b10 = n10; b11 = n11;
-        }
-        {  // rows: R_i^H [row_p; row_q]
-          const double ci = rc[b][bi];
-          const double2 sei = rse[b][bi], seci = cconj(sei);
-          const double2 n00 = csub(cscale(b00, ci), cmul(sei, b10));
-          const double2 n01 = csub(cscale(b01, ci), cmul(sei, b11));
-          const double2 n10 = cadd(cmul(seci, b00), cscale(b10, ci));
-          const double2 n11 = cadd(cmul(seci, b01), cscale(b11, ci));
-          b00 = n00; b01 = n01; b10 = n10; b11 = n11;
-        }
-        Gs[s00] = pi < pj ? b00 : cconj(b00);
-        Gs[s01] = pi < qj ? b01 : cconj(b01);
-        Gs[s10] = qi < pj ? b10 : cconj(b10);
-        Gs[s11] = qi < qj ? b11 : cconj(b11);
-      }
-      // G after round r (a round without rotations leaves G as it was, and
-      // the next rotations go to the other buffer)
-      if (any) __syncthreads();
-      if (tid < 64 && r + 1 < PW - 1) params(r + 1, b ^ 1);
       if (any) {
-        // V <- V R on this lane's column j: the pair (p, q) holding j (slot
-        // k of the order above), new x_p = c x_p - conj(se) x_q, new x_q =
-        // se x_p + c x_q, the partner's entries by permute
-        constexpr int H = PW / 2;
-        int k, partner;
-        bool isp;
-        if (r < H) {
-          isp = lane < H;
-          k = isp ? lane : ((lane - H - r) & (H - 1));
-          partner = isp ? H + ((lane + r) & (H - 1)) : k;
-        } else {
-          const int rr = r - H, off = lane & H, jj = lane & (H - 1);
-          int d = jj - rr;
-          d += d < 0 ? H - 1 : 0;
-          int pt = 2 * rr - jj;
-          pt += pt < 0 ? H - 1 : (pt >= H - 1 ? 1 - H : 0);
-          const bool last = jj == H - 1, atr = jj == rr;
-          isp = last ? true : (atr ? false : d <= H / 2 - 1);
-          k = (last || atr) ? 0 : (d <= H / 2 - 1 ? d : H - 1 - d);
-          pt = last ? rr : (atr ? H - 1 : pt);
-          k += off >> 1;
-          partner = pt + off;
+        if (tid < EIGF_OFFD) {
+          const int qi = H + ((bi + r) & (H - 1)), qj = H + ((bj + r) & (H - 1));
+          rotate_block(b, bi * LDG + bj, bi * LDG + qj, bj * LDG + qi, place(qi, qj), false, false,
+                       true, qi > qj);
         }
-        const double c = rc[b][k];
-        const double2 se = rse[b][k];
-        const double2 kap = isp ? make_double2(-se.x, se.y) : se;
-#pragma unroll
-        for (int h = 0; h < EIGF_VROWS; h++) {
-          const double2 x = vr[h];
-          const double2 y = make_double2(__shfl(x.x, partner, 64), __shfl(x.y, partner, 64));
-          vr[h] = cadd(cscale(x, c), cmul(kap, y));
-        }
+        __syncthreads();  // G after round r
         if (tid == 0) sweep_rot = 1;
       }
+      // (a round without rotations leaves G as it was, and the next rotations
+      // go to the other buffer)
+      if (tid < 64) params(r + 1, b ^ 1);
+      if (hasV) {
+        if (any) rotate_v(b);
+#pragma unroll
+        for (int h = 0; h < EIGF_VROWS; h++) {  // slot k takes the q column of slot k + 1
+          const double2 x = row_next<1>(Q[h][0]), y = row_next<1>(Q[h][1]);
+          Q[h][0] = sel(at15, y, x);
+          Q[h][1] = sel(at15, x, y);
+        }
+      }
       __syncthreads();  // V after round r; rotations of round r + 1 ready
+    }
+    // P holds block I and Q block J again, column l + 16 u; to the slots of the
+    // rounds inside the blocks (u = block, slot l): s = 0 pairs 31 with 0, s >= 1
+    // pairs s with 31 - s
+    if (hasV) {
+#pragma unroll
+      for (int h = 0; h < EIGF_VROWS; h++) {
+        const double2 i0 = P[h][0], i1 = row_mirror(P[h][1]), j0 = Q[h][0],
+                      j1 = row_mirror(Q[h][1]);
+        P[h][0] = sel(at0, i1, i0);
+        Q[h][0] = sel(at0, i0, i1);
+        P[h][1] = sel(at0, j1, j0);
+        Q[h][1] = sel(at0, j0, j1);
+      }
+    }
+    // this thread's columns there, p and q of slot bi and of slot bj (slot 0's
+    // p stays, the others move on by one modulo 31)
+    const int si = bi & (H / 2 - 1), sj = bj & (H / 2 - 1);
+    const int oi = bi & (H / 2) ? H : 0, oj = bj & (H / 2) ? H : 0;
+    int ip = si ? si : H - 1, iq = si ? H - 1 - si : 0;
+    int jp = sj ? sj : H - 1, jq = sj ? H - 1 - sj : 0;
+    auto next = [](int x) { return x + 1 == H - 1 ? 0 : x + 1; };
+#pragma nounroll
+    for (int r = H; r < PW - 1; r++) {  // inside the blocks
+      const int b = r & 1;
+      const bool any = anyr[b] != 0;
+      if (any) {
+        if (tid < EIGF_OFFD) {
+          const int pi = ip + oi, qi = iq + oi, pj = jp + oj, qj = jq + oj;
+          rotate_block(b, place(pi, pj), place(pi, qj), place(qi, pj), place(qi, qj), pi > pj,
+                       pi > qj, qi > pj, qi > qj);
+        }
+        __syncthreads();
+        if (tid == 0) sweep_rot = 1;
+      }
+      ip = si ? next(ip) : ip;
+      jp = sj ? next(jp) : jp;
+      iq = next(iq);
+      jq = next(jq);
+      if (tid < 64 && r + 1 < PW - 1) params(r + 1, b ^ 1);
+      if (hasV) {
+        if (any) rotate_v(b);
+        // p columns move down by one slot, q columns up, around slot 0's p
+#pragma unroll
+        for (int h = 0; h < EIGF_VROWS; h++)
+#pragma unroll
+          for (int u = 0; u < 2; u++) {
+            const double2 x = row_next<1>(P[h][u]), y = row_next<15>(Q[h][u]);
+            P[h][u] = sel(at0, P[h][u], sel(at15, Q[h][u], x));
+            Q[h][u] = sel(at0, x, y);
+          }
+      }
+      __syncthreads();
+    }
+    if (hasV) {
+#pragma unroll
+      for (int h = 0; h < EIGF_VROWS; h++) {  // and back
+        const double2 i0 = sel(at0, Q[h][0], P[h][0]), i1 = sel(at0, P[h][0], Q[h][0]);
+        const double2 j0 = sel(at0, Q[h][1], P[h][1]), j1 = sel(at0, P[h][1], Q[h][1]);
+        P[h][0] = i0;
+        P[h][1] = row_mirror(i1);
+        Q[h][0] = j0;
+        Q[h][1] = row_mirror(j1);
+      }
     }
     const int cont = sweep_rot;  // every thread reads before anyone clears it
     if (sweep == 0 && tid == 0) first_rot = cont;
@@ -1161,8 +1253,16 @@ __global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *de
   }
   if (first_rot) {
     double2 *V = d.V + (size_t)pairIdx * (PW * PW);
+    if (hasV) {
 #pragma unroll
-    for (int h = 0; h < EIGF_VROWS; h++) V[(vrow0 + h) * PW + lane] = vr[h];
+      for (int h = 0; h < EIGF_VROWS; h++)
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+          if (vrow0 + h < PW) {
+            V[(vrow0 + h) * PW + l + 16 * u] = P[h][u];
+            V[(vrow0 + h) * PW + H + l + 16 * u] = Q[h][u];
+          }
+    }
   }
 }
 

@@ -70,12 +70,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 // divisions a column).  Against four barriers and a thread that computes for
 // all (one kernel for every height): 49 -> 12.4 us up to 256 rows, 49 -> 17.6 up
 // to 512.
-// Keeps the compiler from folding what x was computed from (signs, products)
-// into the expressions that use it, where another multiply-add would be fused.
-__device__ __forceinline__ void as_loaded(double2 &x) {
-  asm("" : "+v"(x.x), "+v"(x.y));
-}
-
 template <int THREADS, int RPT>
 __global__ __launch_bounds__(THREADS) void k_qr_panel(const GateDesc *descs, int stage, int panel) {
   static_assert(RPT == 1 || THREADS == 512, "a thread's rows are 512 apart");

@@ -35,6 +35,12 @@ __device__ __forceinline__ void cfmac(double2 &acc, double2 a, double2 b) {
   acc.y = fma(a.x, b.y, acc.y);
   acc.y = fma(-a.y, b.x, acc.y);
 }
+// Keeps the compiler from folding what x was computed from (signs, products)
+// into the expressions that use it, where another multiply-add would be fused.
+__device__ __forceinline__ void as_loaded(double2 &x) {
+  asm("" : "+v"(x.x), "+v"(x.y));
+}
+
 __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 
 __device__ __forceinline__ double2 f2d(float2 a) { return make_double2((double)a.x, (double)a.y); }

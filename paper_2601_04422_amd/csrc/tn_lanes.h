@@ -21,6 +21,16 @@ __device__ __forceinline__ double2 row_next(double2 x) {
   return make_double2(row_next<N>(x.x), row_next<N>(x.y));
 }
 
+// Value of lane 15 - l of the row of 16 lanes, in registers.
+__device__ __forceinline__ double row_mirror(double x) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x140, 0xF, 0xF, true),
+      __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x140, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double2 row_mirror(double2 x) {
+  return make_double2(row_mirror(x.x), row_mirror(x.y));
+}
+
 // Value of lane l ^ 16 (rows of 16 lanes exchanged in pairs), in registers.
 __device__ __forceinline__ double swap_rows(double x) {
   const bool odd = threadIdx.x & 16;
