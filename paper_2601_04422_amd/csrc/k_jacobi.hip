@@ -1335,7 +1335,8 @@ __global__ __launch_bounds__(256, 2) void k_rot_mfma3(const GateDesc *descs, int
   // flight are counted exactly: the products of a tile wait only for that
   // tile's data while the next tile's block I is still on its way.  Columns
   // are padded to whole 16-row tiles and chunks are whole tiles, so rows
-  // past the matrix land in the column's padding (never read).
+  // past the matrix land in the column's padding (never read).  (A wavefront
+  // with an odd number of tiles leaves before the empty one's products.)
   const BufRes rI = make_res(base + (size_t)I * BW * ld, BW * ld);
   const BufRes rJ = make_res(base + (size_t)J * BW * ld, BW * ld);
   const BufRes rZ = make_res(base, 0);
@@ -1397,9 +1398,87 @@ __global__ __launch_bounds__(256, 2) void k_rot_mfma3(const GateDesc *descs, int
     load_half(xj, 1, q);
     load_half(xi1, 0, q + 1);
     tile(xi0, xj, q);
+    if (q + 1 >= mytiles) break;
     load_half(xj, 1, q + 1);
     load_half(xi0, 0, q + 2);
     tile(xi1, xj, q + 1);
+  }
+}
+
+// The same rotation with the columns of the result split over the wavefronts:
+// each computes 16 of the 64 columns of every tile of its workgroup, its
+// columns of V in registers.  All four read a tile's X, so a barrier stands
+// between reading and overwriting it.  The products and their order are those
+// above, so the results are the same to the bit.
+// A tile's 192 matrix instructions take one SIMD 12000 clocks (5 us), which a
+// launch with fewer tiles than SIMDs cannot hide; here they take a quarter of
+// that.  chi 90 (3 pairs x 12 tiles) 13.8 -> 5.3 us, chi 300 (10 x 38) 18.3 ->
+// 9.5, chi 128 (up to 56 x 16) 25 -> 11.6, chi 256 in a batch of many gates 46 ->
+// 45 us, bound by the matrix cores there.
+__global__ __launch_bounds__(256, 2) void k_rot_cols(const GateDesc *descs, int round) {
+  const GateDesc &d = descs[blockIdx.y];
+  if (!d.sc->active || round >= d.nblk - 1) return;
+  const int npairs = d.nblk / 2;
+  const int RRW = d.rotRows;
+  const int xchunks = (d.rows + RRW - 1) / RRW;
+  const int jchunks = d.trans ? (d.m + RRW - 1) / RRW : 0;
+  const int per = xchunks + jchunks;
+  const int pairIdx = blockIdx.x / per, chunk = blockIdx.x % per;
+  if (pairIdx >= npairs) return;
+  if (!d.pairFlag[pairIdx]) return;
+  int I, J;
+  rr_pair(round, pairIdx, d.nblk, I, J);
+  const bool inX = chunk < xchunks;
+  double2 *base = inX ? d.X : d.J;
+  const int ld = inX ? d.ldx : d.ldj, nrows = inX ? d.rows : d.m;
+  const int r0 = (inX ? chunk : chunk - xchunks) * RRW;
+  const int r1 = min(nrows, r0 + RRW);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar)
+  const int l16 = lane & 15, lg = lane >> 4;
+  if (tid == 0 && d.ctr) {
+    unsigned long long nr = (unsigned long long)(r1 - r0);
+    atomicAdd(&d.ctr[CTR_ROT_FLOP], 8ull * nr * PW * PW);
+    atomicAdd(&d.ctr[CTR_ROT_BYTE], 32ull * nr * PW + 16ull * PW * PW);
+  }
+  const BufRes rI = make_res(base + (size_t)I * BW * ld, BW * ld);
+  const BufRes rJ = make_res(base + (size_t)J * BW * ld, BW * ld);
+  const BufRes rZ = make_res(base, 0);
+  const double2 *V = d.V + (size_t)pairIdx * (PW * PW) + lg * PW + 16 * wave + l16;
+  double2 a[PW / 4], x0[PW / 4], x1[PW / 4];  // lane: column l16 of V, row l16 of X; k = 4 s + lg
+  // a tile past the chunk reads zeros (and is not used)
+  auto load = [&](double2 *x, int rt) {
+    const BufRes bI = rt < r1 ? rI : rZ, bJ = rt < r1 ? rJ : rZ;
+    const int lo = lg * ld + rt + l16;
+#pragma unroll
+    for (int s = 0; s < PW / 4; s++)
+      x[s] = bload(s < BW / 4 ? bI : bJ, lo + 4 * (s % (BW / 4)) * ld);
+  };
+  auto tile = [&](const double2 *x, int rt) {
+    d4_t p1{0.0, 0.0, 0.0, 0.0}, p2 = p1, p3 = p1;
+#pragma unroll
+    for (int s = 0; s < PW / 4; s++) {
+      p1 = mfma64(a[s].x, x[s].x, p1);
+      p2 = mfma64(a[s].y, x[s].y, p2);
+      p3 = mfma64(a[s].x + a[s].y, x[s].x + x[s].y, p3);
+    }
+    __syncthreads();
+    const BufRes out = wave < 2 ? rI : rJ;
+    const int lo = (16 * (wave & 1) + lg) * ld + rt + l16;
+#pragma unroll
+    for (int v = 0; v < 4; v++)
+      bstore(out, lo + 4 * v * ld,
+             make_double2(p1[v] - p2[v], p3[v] - p1[v] - p2[v]));
+  };
+#pragma unroll
+  for (int s = 0; s < PW / 4; s++) a[s] = V[4 * s * PW];
+  load(x0, r0);
+  for (int rt = r0; rt < r1; rt += 32) {
+    load(x1, rt + 16);
+    tile(x0, rt);
+    if (rt + 16 >= r1) break;
+    load(x0, rt + 32);
+    tile(x1, rt + 16);
   }
 }
 
@@ -1426,10 +1505,13 @@ void launch_gather_sc(hipStream_t st, const GateDesc *d, int ng, SlotScalars *ou
 }
 
 void launch_rot(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs,
-                int max_rows, int max_m, int rot_rows) {
+                int max_rows, int max_m, int rot_rows, bool cols) {
   if (ng <= 0) return;
   const int per = (max_rows + rot_rows - 1) / rot_rows + (max_m + rot_rows - 1) / rot_rows;
-  hipLaunchKernelGGL(k_rot_mfma3, dim3(max_pairs * per, ng), dim3(256), 0, st, d, round);
+  if (cols)
+    hipLaunchKernelGGL(k_rot_cols, dim3(max_pairs * per, ng), dim3(256), 0, st, d, round);
+  else
+    hipLaunchKernelGGL(k_rot_mfma3, dim3(max_pairs * per, ng), dim3(256), 0, st, d, round);
 }
 
 // ---------------------------------------------------------------- sort + truncate

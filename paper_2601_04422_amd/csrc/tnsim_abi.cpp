@@ -685,6 +685,7 @@ struct SweepRunner {
   struct Plan {
     int na = 0, maxPairs = 0, maxNblk = 0, maxRows = 0, maxMtrans = 0, ksplit = 1, rotRows = 256;
     bool cross = false, full = false;  // gates without and with fullOrder
+    bool cols = false;                 // k_rot_cols
   } P;
 
   tnsim_status plan(const std::vector<const GateDesc *> &D, const std::vector<tnsim_mps> &hs) {
@@ -715,7 +716,17 @@ struct SweepRunner {
     P.ksplit = std::max(ks, 1);
     const int rchunks = std::max(1, P.maxRows + P.maxMtrans);
     const int tuned = o->tune_rot_rows[tune_bucket(pairs)];
-    if (tuned > 0) {
+    // Rotations with the columns split over the wavefronts (k_rot_cols) until
+    // X no longer fits the last-level cache (its four reads of a tile then
+    // cost more than they hide), at least about 512 workgroups where the tiles
+    // suffice.  us per launch, whole tiles per wavefront against split: 36
+    // tiles of 16 rows 13.8 / 5.3, 384 18.3 / 9.5, 1400 25 / 11.6, 7800 28.9 /
+    // 26.5, 10900 29.7 / 27.5, 18500 49.7 / 43.5; 46000 170 / 197.
+    const long long tiles = (long long)pairs * ((rchunks + 15) / 16);
+    P.cols = tiles <= 24576;
+    if (P.cols) {
+      P.rotRows = tiles <= 512 ? 16 : tiles <= 2048 ? 32 : 64;
+    } else if (tuned > 0) {
       P.rotRows = tuned;
     } else {
       while (P.rotRows > 64 && (long long)pairs * ((rchunks + P.rotRows - 1) / P.rotRows) < 1024)
@@ -752,7 +763,7 @@ struct SweepRunner {
       }
       {
         ProfScope p(h, TNSIM_K_ROT);
-        launch_rot(st, ddev, P.na, r, P.maxPairs, P.maxRows, P.maxMtrans, P.rotRows);
+        launch_rot(st, ddev, P.na, r, P.maxPairs, P.maxRows, P.maxMtrans, P.rotRows, P.cols);
       }
     }
     launch_gather_sc(st, ddev, P.na, o->at<SlotScalars>(o->L.scg_off));
@@ -764,7 +775,8 @@ struct SweepRunner {
     tnsim_mps h = o;
     hipStream_t st = o->stream;
     const long long key[8] = {P.na,      P.maxPairs,  P.ksplit,  P.maxNblk,
-                              P.maxRows, P.maxMtrans, P.rotRows, 2 * P.cross + P.full};
+                              P.maxRows, P.maxMtrans, P.rotRows,
+                              4 * P.cols + 2 * P.cross + P.full};
     if (h->sweep_exec && memcmp(key, h->sweep_key, sizeof key) == 0) return TNSIM_OK;
     if (h->sweep_exec) {
       hipGraphExecDestroy(h->sweep_exec);
@@ -3209,9 +3221,9 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
       h->pin_copies++;
       HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(GateDesc) * ng, hipMemcpyHostToDevice,
                                h->stream));
-      launch_rot(h->stream, ddev, ng, 0, npairs, rows, 0, rr);  // warm-up
+      launch_rot(h->stream, ddev, ng, 0, npairs, rows, 0, rr, false);  // warm-up
       HIPCHK(h, hipEventRecord(e0, h->stream));
-      for (int r = 0; r < 3; r++) launch_rot(h->stream, ddev, ng, r, npairs, rows, 0, rr);
+      for (int r = 0; r < 3; r++) launch_rot(h->stream, ddev, ng, r, npairs, rows, 0, rr, false);
       HIPCHK(h, hipEventRecord(e1, h->stream));
       LAUNCHCHK(h, "autotune");
       HIPCHK(h, hipEventSynchronize(e1));

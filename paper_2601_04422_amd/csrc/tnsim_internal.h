@@ -60,7 +60,7 @@ struct GateDesc {
   int maxSweeps;         // sweep cap (k_small; the host caps the block Jacobi's)
   int fullOrder;         // 1: every pair solve visits all 2016 column pairs of a Gram computed
                          // afresh (k_eig_full), 0: the passes of k_eig
-  int rotRows;           // rows of X (and J) per rotation workgroup, a multiple of 64
+  int rotRows;           // rows of X (and J) per rotation workgroup, a multiple of 16
   int *dimsDev;          // device bond dimensions of the gate's state (n+1)
   double tol;            // relative off-diagonal tolerance
   double cutoff;         // discarded-weight cutoff
@@ -154,7 +154,7 @@ void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pa
                 bool cross, bool full);
 void launch_gather_sc(hipStream_t st, const GateDesc *d, int ng, SlotScalars *out);
 void launch_rot(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs,
-                int max_rows, int max_m, int rot_rows);
+                int max_rows, int max_m, int rot_rows, bool cols);
 void launch_trunc(hipStream_t st, const GateDesc *d, int ng);
 // QR preconditioning (k_qr.hip).  stage 0 factors M (in Qm), stage 1 factors
 // R1^H (in X).  Panels of QNB columns are factored and applied inside their
