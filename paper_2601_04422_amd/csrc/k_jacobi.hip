@@ -501,16 +501,18 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
 // parameters, barrier: about 2000 clocks with rotations, 700 without), not by
 // the vector units, so G and V go to wavefronts of their own: one wavefront of
 // each per SIMD in place of one that does both in turn, and a V wavefront
-// never waits for the parameters.  The 16 half-pass relayouts through LDS cost
-// 8000 clocks.  Per launch, against 256 threads that hold both: chi 300
-// (10 pairs) 41.5 -> 34.8 us, chi 128 (layers of 4 .. 32 pairs) 57 -> 48 us,
-// chi 1024 (32 pairs, 9 gates at once) 46 -> 46 us, where two such workgroups
-// share a CU as three of the smaller ones did.
+// never waits for the parameters.  The relayouts between half-passes cost 8000
+// clocks each.  162 registers and so one workgroup per CU: with 128, where two
+// share a CU, the relayouts spill, which cost more than the second workgroup
+// gave even with 384 solves at once.  Per launch, 256 threads that hold both /
+// 512 with spills / 512: chi 300 (10 pairs) 41.5 / 34.8 / 31.5 us, chi 128
+// (layers of 4 .. 56 pairs) 57 / 48.1 / 43.5, chi 1024 (288 .. 384 pairs at
+// once) 46.2 / 45.8 / 40.9.
 constexpr int EIG_THREADS = 512;  // wavefronts 0 .. 3 hold G, 4 .. 7 hold V
 constexpr int EIG_ROWS = 16;      // rows of 16 lanes that hold G
 constexpr int EIG_VROWS = PW / 8; // rows of V held by each half-wavefront
 constexpr int EIG_EVERY = 4;  // tournament rounds between passes inside the blocks
-constexpr int EIG_UPPER = PW * (PW - 1) / 2;
+constexpr int EIG_UPPER = PW / 2 * (PW + 1);
 
 // Bits of the passes a solve makes in a round of a sweep of nr >= 3 rounds.
 __device__ __forceinline__ int eig_bits(int round, int nr) {
@@ -531,14 +533,19 @@ __device__ __forceinline__ int bit_del(int x, int b) {
   return ((x >> (b + 1)) << b) | (x & ((1 << b) - 1));
 }
 
-// Place of entry (a, b), a < b, of the packed strict upper triangle.
-__device__ __forceinline__ int gpack(int a, int b) { return a * (PW - 1) - a * (a - 1) / 2 + b - a - 1; }
+// Place of entry (a, b), a < b, of the strict upper triangle: the rows from 32
+// on turned round into the free halves of rows 31 .. 0.
+__device__ __forceinline__ int gpack(int a, int b) {
+  const int m = a & (PW / 2) ? PW - 1 : 0;
+  return (a ^ m) * (PW + 1) + (b ^ m);
+}
 
 __device__ __forceinline__ double2 gget(const double2 *Gs, int a, int b) {
-  return a < b ? Gs[gpack(a, b)] : cconj(Gs[gpack(b, a)]);
+  const double2 x = Gs[gpack(min(a, b), max(a, b))];
+  return make_double2(x.x, a < b ? x.y : -x.y);
 }
 __device__ __forceinline__ void gput(double2 *Gs, int a, int b, double2 x) {
-  Gs[a < b ? gpack(a, b) : gpack(b, a)] = a < b ? x : cconj(x);
+  Gs[gpack(min(a, b), max(a, b))] = make_double2(x.x, a < b ? x.y : -x.y);
 }
 
 // x - a y and x + a y
@@ -835,7 +842,7 @@ __device__ __forceinline__ int eig_solve_v(const GateDesc &d, EigShared &S, int 
   return first_rot;
 }
 
-__global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, int round,
+__global__ __launch_bounds__(EIG_THREADS, 2) void k_eig(const GateDesc *descs, int round,
                                                         int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
@@ -908,7 +915,7 @@ __global__ __launch_bounds__(EIG_THREADS, 4) void k_eig(const GateDesc *descs, i
   }
 }
 
-constexpr int EIGF_THREADS = 512;  // 8 wavefronts; two pair solves share a CU
+constexpr int EIGF_THREADS = 512;  // 8 wavefronts
 // rows of V held by each row of 16 lanes of the wavefronts 1, 2, 3, 5, 6, 7
 constexpr int EIGF_VROWS = (PW + 23) / 24;
 constexpr int EIGF_OFFD = (PW / 2) * (PW / 2 - 1) / 2;  // off-diagonal 2x2 blocks (i < j)
@@ -965,7 +972,7 @@ __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b 
 // rotations (DPP): between the blocks slot k takes the q column of slot k + 1
 // (mod 32); inside a block the columns r' + s move down and r' - s up by one
 // slot around the fixed column 31.  So V needs no LDS, which holds G and the
-// rotation parameters (69 KB: two solves per CU).
+// rotation parameters (69 KB).
 //
 // A round takes two barriers: G's blocks on all wavefronts, then the next
 // rotations in the first one (into the other parameter buffer) while six
@@ -975,8 +982,10 @@ __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b 
 // round) and by G's blocks through LDS (1300).  With eight wavefronts that
 // took the partners' entries of V by lane permutes (LDS) after the parameters,
 // a round was 4400 clocks: 124 -> 95 us for 64 pairs, one inner sweep; with V
-// in wavefronts 4 .. 7 99 us, with V rotated beside G 104.
-__global__ __launch_bounds__(EIGF_THREADS, 4) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
+// in wavefronts 4 .. 7 99 us, with V rotated beside G 104.  136 registers, one
+// solve per CU: limited to 128 for two it spilled, and batches of 60 to 500
+// solves took 3 % longer.
+__global__ __launch_bounds__(EIGF_THREADS, 2) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
   if (!d.fullOrder || !d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2)
