@@ -375,12 +375,13 @@ constexpr int QU_ROWS = 64;  // rows per LDS chunk
 //   apply = 0: B = A(j0:, first:last) <- (I - V T V^H)^H B  (factoring: the
 //              columns after the block, up to col_end)
 //   apply = 1: B = U(j0:, 0:k) <- (I - V T V^H) B          (U = Q1 [W; 0])
-// S = V^H B over all rows, Y = op(T) S, B -= V Y; V is staged in LDS.
-template <int NB, int COLS>
+// S = V^H B over all rows, Y = op(T) S, B -= V Y; V is staged in LDS, the next
+// rows loaded meanwhile.
+template <int NB, int COLS, int NT>
 __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const double2 *T,
                                 int apply, int col_end) {
-  static_assert((NB * COLS) % 256 == 0, "whole entries per thread");
-  constexpr int EPT = NB * COLS / 256;
+  static_assert((NB * COLS) % NT == 0 && NT % QU_ROWS == 0, "whole entries per thread");
+  constexpr int EPT = NB * COLS / NT;
   if (j0 >= q.cols) return;
   const int w = min(NB, q.cols - j0);
   double2 *B;
@@ -408,15 +409,31 @@ __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const
   __shared__ double2 Y[NB][COLS];
   __shared__ double2 Tl[NB][NB + 1];
   const int tid = threadIdx.x;
-  for (int e = tid; e < NB * NB; e += 256) Tl[e / NB][e % NB] = T[e];
+  for (int e = tid; e < NB * NB; e += NT) Tl[e / NB][e % NB] = T[e];
 
-  auto load_v = [&](int r0) {  // rows r0 .. r0+63 of V: 1 on the diagonal, stored below
-    for (int e = tid; e < QU_ROWS * NB; e += 256) {
-      const int r = e % QU_ROWS, p = e / QU_ROWS, gr = r0 + r, dr = gr - (j0 + p);
-      double2 v = make_double2(0.0, 0.0);
-      if (p < w && gr < rows && dr >= 0)
-        v = dr == 0 ? make_double2(1.0, 0.0) : V[(size_t)p * q.ld + gr];
-      Vs[r][p] = v;
+  // rows r0 .. r0+63 of V: 1 on the diagonal, stored below; and of B.  All loads
+  // of a chunk are under way before the first is waited for.
+  constexpr int VPT = QU_ROWS * NB / NT, BPT = QU_ROWS * COLS / NT;
+  auto get_v = [&](double2 (&x)[VPT], int r0) {
+#pragma unroll
+    for (int k = 0; k < VPT; k++) {
+      const int e = tid + NT * k, p = e / QU_ROWS, gr = r0 + e % QU_ROWS;
+      x[k] = p < w && gr < rows && gr > j0 + p ? V[(size_t)p * q.ld + gr]
+                                               : make_double2(gr == j0 + p && p < w ? 1.0 : 0.0, 0.0);
+    }
+  };
+  auto get_b = [&](double2 (&x)[BPT], int r0) {
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+      const int e = tid + NT * k, cc = e / QU_ROWS, gr = r0 + e % QU_ROWS;
+      x[k] = gr < rows && cc < nc ? B[(size_t)cc * ldb + gr] : make_double2(0.0, 0.0);
+    }
+  };
+  auto put_v = [&](const double2 (&x)[VPT]) {
+#pragma unroll
+    for (int k = 0; k < VPT; k++) {
+      const int e = tid + NT * k;
+      Vs[e % QU_ROWS][e / QU_ROWS] = x[k];
     }
   };
 
@@ -424,17 +441,22 @@ __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const
   double2 sacc[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; e++) sacc[e] = make_double2(0.0, 0.0);
+  double2 vx[VPT], bx[BPT];
+  get_v(vx, j0);
+  get_b(bx, j0);
   for (int r0 = j0; r0 < rows; r0 += QU_ROWS) {
-    load_v(r0);
-    for (int e = tid; e < QU_ROWS * COLS; e += 256) {
-      const int r = e % QU_ROWS, cc = e / QU_ROWS;
-      Bs[r][cc] = (r0 + r < rows && cc < nc) ? B[(size_t)cc * ldb + r0 + r]
-                                              : make_double2(0.0, 0.0);
+    put_v(vx);
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+      const int e = tid + NT * k;
+      Bs[e % QU_ROWS][e / QU_ROWS] = bx[k];
     }
     __syncthreads();
+    get_v(vx, r0 + QU_ROWS);  // the next chunk (zeros past the end)
+    get_b(bx, r0 + QU_ROWS);
 #pragma unroll
     for (int e = 0; e < EPT; e++) {
-      const int id = tid + 256 * e, p = id / COLS, cc = id % COLS;
+      const int id = tid + NT * e, p = id / COLS, cc = id % COLS;
 #pragma unroll 8
       for (int r = 0; r < QU_ROWS; r++) cfmac(sacc[e], Vs[r][p], Bs[r][cc]);
     }
@@ -442,14 +464,14 @@ __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const
   }
 #pragma unroll
   for (int e = 0; e < EPT; e++) {
-    const int id = tid + 256 * e;
+    const int id = tid + NT * e;
     S[id / COLS][id % COLS] = sacc[e];
   }
   __syncthreads();
   // phase 2: Y = T^H S (factor) or T S (apply)
 #pragma unroll
   for (int e = 0; e < EPT; e++) {
-    const int id = tid + 256 * e, p = id / COLS, cc = id % COLS;
+    const int id = tid + NT * e, p = id / COLS, cc = id % COLS;
     double2 y = make_double2(0.0, 0.0);
     for (int l = 0; l < NB; l++) {
       const double2 t = apply ? Tl[p][l] : cconj(Tl[l][p]);
@@ -459,33 +481,41 @@ __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const
   }
   __syncthreads();
   // phase 3: B -= V Y; lanes along rows
-  const int rl = tid % QU_ROWS, cg = tid / QU_ROWS;  // 64 rows x 4 column groups
+  const int rl = tid % QU_ROWS, cg = tid / QU_ROWS;  // 64 rows x column groups
+  get_v(vx, j0);
+  get_b(bx, j0);  // entry k: column cg + NT / QU_ROWS k of row rl
   for (int r0 = j0; r0 < rows; r0 += QU_ROWS) {
-    load_v(r0);
+    put_v(vx);
+    double2 old[BPT];
+#pragma unroll
+    for (int k = 0; k < BPT; k++) old[k] = bx[k];
     __syncthreads();
+    get_v(vx, r0 + QU_ROWS);
+    get_b(bx, r0 + QU_ROWS);
     const int r = r0 + rl;
-    if (r < rows) {
-      for (int cc = cg; cc < nc; cc += 4) {
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+      const int cc = cg + NT / QU_ROWS * k;
+      if (r < rows && cc < nc) {
         double2 acc = make_double2(0.0, 0.0);
-#pragma unroll 8
+#pragma unroll
         for (int p = 0; p < NB; p++) cfma(acc, Vs[rl][p], Y[p][cc]);
-        double2 *bp = B + (size_t)cc * ldb + r;
-        *bp = csub(*bp, acc);
+        B[(size_t)cc * ldb + r] = csub(old[k], acc);
       }
     }
     __syncthreads();
   }
 }
 
-constexpr int QU_COLS = 32;   // target columns per workgroup, panel updates
+constexpr int QU_COLS = 32;  // target columns per workgroup, panel updates
 
 // One panel's reflectors on the columns after it up to col_end (inside its
 // group while the group is being factored).
-__global__ __launch_bounds__(256) void k_qr_update(const GateDesc *descs, int stage, int panel,
+__global__ __launch_bounds__(QNB * QU_COLS) void k_qr_update(const GateDesc *descs, int stage, int panel,
                                                    int col_end) {
   const GateDesc &d = descs[blockIdx.y];
   if (!d.qr || d.storage == 0) return;
-  qr_block_update<QNB, QU_COLS>(d, qr_view(d, stage), panel * QNB, qr_tfac(d, stage, panel), 0,
+  qr_block_update<QNB, QU_COLS, QNB * QU_COLS>(d, qr_view(d, stage), panel * QNB, qr_tfac(d, stage, panel), 0,
                                 col_end);
 }
 
@@ -576,8 +606,8 @@ void launch_qr_update(hipStream_t st, const GateDesc *d, int ng, int stage, int 
                       int col_end, int max_cols, bool c128, bool c64) {
   if (ng <= 0 || max_cols <= 0) return;
   if (c64)
-    hipLaunchKernelGGL(k_qr_update, dim3((max_cols + QU_COLS - 1) / QU_COLS, ng), dim3(256), 0, st,
-                       d, stage, panel, col_end);
+    hipLaunchKernelGGL(k_qr_update, dim3((max_cols + QU_COLS - 1) / QU_COLS, ng),
+                       dim3(QNB * QU_COLS), 0, st, d, stage, panel, col_end);
   if (c128)
     hipLaunchKernelGGL(k_qr_update1, dim3((max_cols + QU1_COLS - 1) / QU1_COLS, ng), dim3(256), 0,
                        st, d, stage, panel, col_end);
@@ -915,66 +945,106 @@ void launch_qr_update_group(hipStream_t st, const GateDesc *d, int ng, int stage
 
 // T factor of a group of QG reflectors (compact WY, forward, columnwise):
 // T(i, i) = tau_i (from the panels' factors), T(0:i, i) = -tau_i T(0:i, 0:i)
-// (V(:, 0:i)^H v_i), with the Gram V^H V summed over the group's rows.  Gates
-// with complex128 sites take V^H V from k_qrg_s instead.
-__global__ __launch_bounds__(256) void k_qr_tgroup(const GateDesc *descs, int stage, int group) {
+// (V(:, 0:i)^H v_i), with the Gram V^H V summed over the group's rows in turn.
+// Gates with complex64 sites only; complex128 ones take V^H V from k_qrg_s.
+//
+// The Gram's columns first, QT_COLS per workgroup, one entry above the diagonal
+// per thread, into the place of T, the next rows' loads under way during the
+// sums; then T, row t in the registers of thread t (no barriers: G's column i
+// is the same for every row).  Bound by the chains of both.  One workgroup that
+// took the Gram, with loads and sums in turn, and a barrier per column of T:
+// 62 us at 512 rows, 51 at 256; now 16.3 + 16.6 and 13.5 + 16.6.
+constexpr int QT_COLS = 4;
+__global__ __launch_bounds__(QG * QT_COLS) void k_qr_tgram(const GateDesc *descs, int stage,
+                                                           int group) {
+  constexpr int NT = QG * QT_COLS;
+  const GateDesc &d = descs[blockIdx.y];
+  if (!d.qr || d.storage == 0) return;
+  const QrView q = qr_view(d, stage);
+  const int j0 = group * QG, l0 = blockIdx.x * QT_COLS;
+  if (j0 + l0 >= q.cols) return;
+  const int nv = min(l0 + QT_COLS, q.cols - j0);  // reflectors that count here
+  const double2 *V = q.A + (size_t)j0 * q.ld;
+  __shared__ double2 Vs[QU_ROWS][QG + 1];
+  const int tid = threadIdx.x, p = tid / QT_COLS, l = l0 + tid % QT_COLS;
+  double2 acc = make_double2(0.0, 0.0);
+  constexpr int VPT = QU_ROWS * QG / NT;
+  double2 x[VPT];
+  auto get = [&](int r0) {
+#pragma unroll
+    for (int k = 0; k < VPT; k++) {
+      const int e = tid + NT * k, c = e / QU_ROWS, gr = r0 + e % QU_ROWS;
+      x[k] = c < nv && gr < q.rows && gr > j0 + c
+                 ? V[(size_t)c * q.ld + gr]
+                 : make_double2(gr == j0 + c && c < nv ? 1.0 : 0.0, 0.0);
+    }
+  };
+  get(j0 + l0);
+  for (int r0 = j0 + l0; r0 < q.rows; r0 += QU_ROWS) {  // v_l starts at row l
+#pragma unroll
+    for (int k = 0; k < VPT; k++) {
+      const int e = tid + NT * k;
+      Vs[e % QU_ROWS][e / QU_ROWS] = x[k];
+    }
+    __syncthreads();
+    get(r0 + QU_ROWS);
+    if (p < l && l < nv) {
+#pragma unroll 8
+      for (int r = 0; r < QU_ROWS; r++) cfmac(acc, Vs[r][p], Vs[r][l]);
+    }
+    __syncthreads();
+  }
+  if (p < l && l < nv) qr_tgrp(d, stage, group)[p * QG + l] = acc;
+}
+
+__global__ __launch_bounds__(64) void k_qr_tgroup(const GateDesc *descs, int stage, int group) {
   const GateDesc &d = descs[blockIdx.x];
   if (!d.qr || d.storage == 0) return;
   const QrView q = qr_view(d, stage);
   const int j0 = group * QG;
   if (j0 >= q.cols) return;
   const int w = min(QG, q.cols - j0);
-  const double2 *V = q.A + (size_t)j0 * q.ld;
-  __shared__ double2 Vs[QU_ROWS][QG + 1];
-  __shared__ double2 G[QG][QG + 1];
-  __shared__ double2 Ts[QG][QG + 1];
-  const int tid = threadIdx.x;
-  constexpr int EPT = QG * QG / 256;
-  double2 acc[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; e++) acc[e] = make_double2(0.0, 0.0);
-  for (int r0 = j0; r0 < q.rows; r0 += QU_ROWS) {
-    for (int e = tid; e < QU_ROWS * QG; e += 256) {
-      const int r = e % QU_ROWS, p = e / QU_ROWS, gr = r0 + r, dr = gr - (j0 + p);
-      double2 v = make_double2(0.0, 0.0);
-      if (p < w && gr < q.rows && dr >= 0)
-        v = dr == 0 ? make_double2(1.0, 0.0) : V[(size_t)p * q.ld + gr];
-      Vs[r][p] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < EPT; e++) {
-      const int id = tid + 256 * e, p = id / QG, l = id % QG;
-#pragma unroll 8
-      for (int r = 0; r < QU_ROWS; r++) cfmac(acc[e], Vs[r][p], Vs[r][l]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int e = 0; e < EPT; e++) {
-    const int id = tid + 256 * e;
-    G[id / QG][id % QG] = acc[e];
-    Ts[id / QG][id % QG] = make_double2(0.0, 0.0);
-  }
-  __syncthreads();
-  for (int i = 0; i < w; i++) {
-    const double2 *Tp = qr_tfac(d, stage, (j0 + i) / QNB);
-    const double2 tau = Tp[(i % QNB) * QNB + (i % QNB)];
-    if (tid < i) {
-      double2 sum = make_double2(0.0, 0.0);
-      for (int l = tid; l < i; l++) sum = cadd(sum, cmul(Ts[tid][l], G[l][i]));
-      Ts[tid][i] = cmul(make_double2(-tau.x, -tau.y), sum);
-    }
-    if (tid == i) Ts[i][i] = tau;
-    __syncthreads();
-  }
   double2 *Tg = qr_tgrp(d, stage, group);
-  for (int e = tid; e < QG * QG; e += 256) Tg[e] = Ts[e / QG][e % QG];
+  __shared__ double2 G[QG][QG];
+  __shared__ double2 taus[QG];
+  const int tid = threadIdx.x;
+  double2 g[QG * QG / 64];
+#pragma unroll
+  for (int k = 0; k < QG * QG / 64; k++) {  // (what lies on and below the diagonal is not used)
+    const int p = (tid + 64 * k) / QG, l = tid % QG;
+    g[k] = p < l && l < w ? Tg[tid + 64 * k] : make_double2(0.0, 0.0);
+  }
+  if (tid < QG)
+    taus[tid] = tid < w ? qr_tfac(d, stage, (j0 + tid) / QNB)[(tid % QNB) * (QNB + 1)]
+                        : make_double2(0.0, 0.0);
+#pragma unroll
+  for (int k = 0; k < QG * QG / 64; k++) (&G[0][0])[tid + 64 * k] = g[k];
+  __syncthreads();
+  if (tid >= QG) return;
+  double2 T[QG];  // row tid
+#pragma unroll
+  for (int i = 0; i < QG; i++) {
+    const double2 tau = taus[i];
+    double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int l = 0; l < i; l++) {  // (T(tid, l) = 0 before the diagonal)
+      const double2 t = T[l], x = G[l][i];
+      s.x += fma(t.x, x.x, -(t.y * x.y));
+      s.y += fma(t.y, x.x, t.x * x.y);
+    }
+    const bool before = tid < i, at = tid == i;
+    T[i].x = before ? fma(tau.y, s.y, -(tau.x * s.x)) : (at ? tau.x : 0.0);
+    T[i].y = before ? fma(-tau.y, s.x, -(tau.x * s.y)) : (at ? tau.y : 0.0);
+  }
+#pragma unroll
+  for (int i = 0; i < QG; i++) Tg[tid * QG + i] = T[i];
 }
 
 void launch_qr_tgroup(hipStream_t st, const GateDesc *d, int ng, int stage, int group) {
   if (ng <= 0) return;
-  hipLaunchKernelGGL(k_qr_tgroup, dim3(ng), dim3(256), 0, st, d, stage, group);
+  hipLaunchKernelGGL(k_qr_tgram, dim3(QG / QT_COLS, ng), dim3(QG * QT_COLS), 0, st, d, stage,
+                     group);
+  hipLaunchKernelGGL(k_qr_tgroup, dim3(ng), dim3(64), 0, st, d, stage, group);
 }
 
 // ---------------------------------------------------------------- triangular transposes
