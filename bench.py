@@ -44,8 +44,8 @@ HBM_PEAK_GBS = 8000.0
 # kernel class -> (bound, device kernel name): the Gram and rotation kernels
 # are float64 matrix-core contractions, the pair solve and the Householder
 # panels float64 vector arithmetic
-KERNEL_BOUND = {"rot": ("mfma", "k_rot_mfma3"), "gram": ("mfma", "k_gram_mfma2"),
-                "eig": ("alu", "k_eig"), "qr": ("alu", "k_qr_update")}
+KERNEL_BOUND = {"rot": ("mfma", "k_rot_mfma3"), "gram": ("mfma", "k_gram_cross"),
+                "eig": ("alu", "k_eig"), "qr": ("alu", "k_qrg_b")}
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "jacobi_traffic_chi1024_batched.md")
 JACOBI_SRC = os.path.join(ROOT, "paper_2601_04422_amd", "csrc", "k_jacobi.hip")
 
@@ -789,9 +789,9 @@ def bench_fidelity(args):
 
 def bench_calib(args):
     """Copy kernel of known size, for scaling hardware byte counters: the
-    library's storage-conversion kernel (the one tnsim_mps_copy launches) on
-    complex128 sites of a synthetic state; each launch on a 1024 x 2 x 1024
-    site reads and writes exactly 32 MiB."""
+    library's state copy (tnsim_mps_copy, one launch of k_copy_state) on a
+    synthetic state with complex128 sites; each launch reads and writes the
+    sites and Schmidt weights once."""
     import torch
 
     from paper_2601_04422_amd import tnsim as T
@@ -811,13 +811,13 @@ def bench_calib(args):
     dt = (time.perf_counter() - t0) / 3
     big = [q for q in range(n) if dims[q] == chi and dims[q + 1] == chi]
     moved = 2 * 16 * sum(dims[q] * 2 * dims[q + 1] for q in range(n))
-    return {"metric": "counter calibration: storage-conversion copy of complex128 sites",
+    return {"metric": "counter calibration: state copy of complex128 sites",
             "value": moved / dt / 1e9, "unit": "GB/s", "n_gpus": 1, "steps": 3, "warmup": 0,
             "ms_per_step": 1e3 * dt, "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": "c128", "data": "synthetic",
-            "config": {"workload": f"copy of an n={n}, chi={chi} state; sites {big} are "
-                                   f"{chi}x2x{chi}: {16 * chi * 2 * chi // 1024} KiB read and "
-                                   f"written per launch"}}
+            "config": {"workload": f"copy of an n={n}, chi={chi} state ({len(big)} sites of "
+                                   f"{chi}x2x{chi}): {(moved // 2 + 8 * sum(dims[1:-1])) / 1024} "
+                                   f"KiB read and written per launch"}}
 
 
 def bench_peak(args):

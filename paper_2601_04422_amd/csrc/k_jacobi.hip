@@ -502,13 +502,15 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
 // the vector units, so G and V go to wavefronts of their own: one wavefront of
 // each per SIMD in place of one that does both in turn, and a V wavefront
 // never waits for the parameters.  The relayouts between half-passes cost 8000
-// clocks each.  162 registers and so one workgroup per CU: with 128, where two
-// share a CU, the relayouts spill, which cost more than the second workgroup
-// gave even with 384 solves at once.  Per launch, 256 threads that hold both /
-// 512 with spills / 512: chi 300 (10 pairs) 41.5 / 34.8 / 31.5 us, chi 128
-// (layers of 4 .. 56 pairs) 57 / 48.1 / 43.5, chi 1024 (288 .. 384 pairs at
-// once) 46.2 / 45.8 / 40.9.
+// clocks each; with 162 registers (one workgroup per CU) they do not spill, with
+// 128 (two) they do, which is worth it only when every CU has two (EIG_PACKED).
+// Per launch, 256 threads that hold both / 512 with 128 registers / with 162:
+// chi 300 (10 pairs) 41.5 / 34.8 / 31.5 us, chi 128 (layers of 4 .. 56 pairs)
+// 57 / 48.1 / 43.5, chi 1024 (288 .. 384 pairs at once) 46.2 / 45.8 / 40.9;
+// 1600 pairs at once (two layers of a 100-qubit circuit) - / 219 / 257 ms.
 constexpr int EIG_THREADS = 512;  // wavefronts 0 .. 3 hold G, 4 .. 7 hold V
+// solves in a launch from which two workgroups share a CU (256 CUs)
+constexpr int EIG_PACKED = 512;
 constexpr int EIG_ROWS = 16;      // rows of 16 lanes that hold G
 constexpr int EIG_VROWS = PW / 8; // rows of V held by each half-wavefront
 constexpr int EIG_EVERY = 4;  // tournament rounds between passes inside the blocks
@@ -842,7 +844,8 @@ __device__ __forceinline__ int eig_solve_v(const GateDesc &d, EigShared &S, int 
   return first_rot;
 }
 
-__global__ __launch_bounds__(EIG_THREADS, 2) void k_eig(const GateDesc *descs, int round,
+template <int WAVES>
+__global__ __launch_bounds__(EIG_THREADS, WAVES) void k_eig(const GateDesc *descs, int round,
                                                         int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
@@ -983,9 +986,10 @@ __device__ __forceinline__ int gslot(int a, int b) { return a < b ? a * LDG + b 
 // took the partners' entries of V by lane permutes (LDS) after the parameters,
 // a round was 4400 clocks: 124 -> 95 us for 64 pairs, one inner sweep; with V
 // in wavefronts 4 .. 7 99 us, with V rotated beside G 104.  136 registers, one
-// solve per CU: limited to 128 for two it spilled, and batches of 60 to 500
-// solves took 3 % longer.
-__global__ __launch_bounds__(EIGF_THREADS, 2) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
+// solve per CU: limited to 128 for two it spills, and batches of 60 to 500
+// solves took 3 % longer; above EIG_PACKED two share a CU, as for k_eig.
+template <int WAVES>
+__global__ __launch_bounds__(EIGF_THREADS, WAVES) void k_eig_full(const GateDesc *descs, int round, int ksplit) {
   const GateDesc &d = descs[blockIdx.y];
   const int pairIdx = blockIdx.x;
   if (!d.fullOrder || !d.sc->active || round >= d.nblk - 1 || pairIdx >= d.nblk / 2)
@@ -1278,11 +1282,13 @@ __global__ __launch_bounds__(EIGF_THREADS, 2) void k_eig_full(const GateDesc *de
 void launch_eig(hipStream_t st, const GateDesc *d, int ng, int round, int max_pairs, int ksplit,
                 bool cross, bool full) {
   if (ng <= 0) return;
+  const bool packed = (long long)max_pairs * ng > EIG_PACKED;
   if (cross)
-    hipLaunchKernelGGL(k_eig, dim3(max_pairs, ng), dim3(EIG_THREADS), 0, st, d, round, ksplit);
+    hipLaunchKernelGGL(packed ? k_eig<4> : k_eig<2>, dim3(max_pairs, ng), dim3(EIG_THREADS), 0, st,
+                       d, round, ksplit);
   if (full)
-    hipLaunchKernelGGL(k_eig_full, dim3(max_pairs, ng), dim3(EIGF_THREADS), 0, st, d, round,
-                       ksplit);
+    hipLaunchKernelGGL(packed ? k_eig_full<4> : k_eig_full<2>, dim3(max_pairs, ng),
+                       dim3(EIGF_THREADS), 0, st, d, round, ksplit);
 }
 
 // ---------------------------------------------------------------- apply a pair rotation
