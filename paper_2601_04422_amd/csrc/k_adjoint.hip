@@ -12,11 +12,18 @@ namespace tn {
 // C[i][j] (+)= alpha * sum_k opA(i,k) opB(k,j), with element strides and an
 // optional conjugation of each operand.  Used for the contractions of the
 // adjoint and of the loss environments.  Float64 matrix cores
-// (v_mfma_f64_16x16x4f64, three real products per complex one): a 64x64 tile
-// of C per workgroup, K in steps of 16 through LDS with the next step loaded
-// into registers during the products; wavefront w owns the 32x32 quarter
-// (rows 32 (w&1), columns 32 (w>>1)), lane l supplies A[l%16][k + l/16] and
-// B[k + l/16][l%16] and holds D[l/16 + 4v][l%16] of each 16x16 tile.
+// (v_mfma_f64_16x16x4f64, three real products per complex one): a 32x32 tile
+// of C per workgroup, K in steps of 64 through LDS with the next step loaded
+// into registers during the products; wavefront w owns one 16x16 quarter (row
+// half w & 1, column half w >> 1), lane l supplies A[l%16][k + l/16] and
+// B[k + l/16][l%16] and holds D[l/16 + 4v][l%16].
+//
+// Bound by latency up to a few hundred columns: one wait for memory and 3000
+// clocks of matrix instructions per 64 of K.  With 64x64 tiles and steps of 16 a
+// wavefront had four times the products, padding included, and four waits.
+// M = N = K = 16: 5.3 -> 4.1 us, 64: 14.7 -> 6.7, 128: 26.9 -> 10.9, 256: 50.8 ->
+// 19.2, 512: 130 -> 60, 1024: 237 -> 239, 1536: 1144 -> 865.
+constexpr int GG_T = 32, GG_K = 64;
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f64x4_t adj_mfma(double a, double b, f64x4_t c) {
@@ -25,17 +32,18 @@ __device__ __forceinline__ f64x4_t adj_mfma(double a, double b, f64x4_t c) {
 
 template <class SA, class SB>
 __global__ __launch_bounds__(256) void k_gemm_gen(GemmArgs g) {
-  __shared__ double2 As[16 * 64], Bs[16 * 64];
+  constexpr int T = GG_T, KS = GG_K, PT = KS * T / 256;  // PT elements per thread
+  __shared__ double2 As[KS * T], Bs[KS * T];
   const int tid = threadIdx.x;
-  const int i0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
+  const int i0 = blockIdx.x * T, j0 = blockIdx.y * T;
   const SA *A = (const SA *)g.A;
   const SB *B = (const SB *)g.B;
-  double2 ra[4], rb[4];
-  // element e = tid + 256 q of the 16 x 64 step: k = e / 64, row/column e % 64
+  double2 ra[PT], rb[PT];
+  // element e = tid + 256 q of the KS x T step: k = e / T, row/column e % T
   auto load = [&](int k0) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int e = tid + 256 * q, kk = e >> 6, ii = e & 63;
+    for (int q = 0; q < PT; q++) {
+      const int e = tid + 256 * q, kk = e / T, ii = e % T;
       const int gi = i0 + ii, gj = j0 + ii, gk = k0 + kk;
       double2 v = make_double2(0.0, 0.0);
       if (gi < g.M && gk < g.K) {
@@ -52,64 +60,42 @@ __global__ __launch_bounds__(256) void k_gemm_gen(GemmArgs g) {
     }
   };
   const int wv = tid >> 6, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
-  const int wm = (wv & 1) * 32, wn = (wv >> 1) * 32;
-  f64x4_t c1[2][2], c2[2][2], c3[2][2];  // Gauss: a c, b d, (a + b)(c + d)
-#pragma unroll
-  for (int x = 0; x < 2; x++)
-#pragma unroll
-    for (int y = 0; y < 2; y++) {
-      c1[x][y] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-      c2[x][y] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-      c3[x][y] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-    }
+  const int wm = (wv & 1) * (T / 2), wn = (wv >> 1) * (T / 2);
+  f64x4_t c1{0.0, 0.0, 0.0, 0.0}, c2 = c1, c3 = c1;  // Gauss: a c, b d, (a + b)(c + d)
   load(0);
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
+  for (int k0 = 0; k0 < g.K; k0 += KS) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
+    for (int q = 0; q < PT; q++) {
       As[tid + 256 * q] = ra[q];
       Bs[tid + 256 * q] = rb[q];
     }
     __syncthreads();
-    if (k0 + 16 < g.K) load(k0 + 16);
+    if (k0 + KS < g.K) load(k0 + KS);
 #pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-      double2 a[2], b[2];
-#pragma unroll
-      for (int x = 0; x < 2; x++) {
-        a[x] = As[(kk + lg) * 64 + wm + 16 * x + l16];
-        b[x] = Bs[(kk + lg) * 64 + wn + 16 * x + l16];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; x++)
-#pragma unroll
-        for (int y = 0; y < 2; y++) {
-          c1[x][y] = adj_mfma(a[x].x, b[y].x, c1[x][y]);
-          c2[x][y] = adj_mfma(a[x].y, b[y].y, c2[x][y]);
-          c3[x][y] = adj_mfma(a[x].x + a[x].y, b[y].x + b[y].y, c3[x][y]);
-        }
+    for (int kk = 0; kk < KS; kk += 4) {
+      if (kk % 16 == 0 && kk > 0 && k0 + kk >= g.K) break;  // (uniform)
+      const double2 a = As[(kk + lg) * T + wm + l16], b = Bs[(kk + lg) * T + wn + l16];
+      c1 = adj_mfma(a.x, b.x, c1);
+      c2 = adj_mfma(a.y, b.y, c2);
+      c3 = adj_mfma(a.x + a.y, b.x + b.y, c3);
     }
     __syncthreads();
   }
+  const int gj = j0 + wn + l16;
 #pragma unroll
-  for (int x = 0; x < 2; x++)
-#pragma unroll
-    for (int y = 0; y < 2; y++) {
-      const int gj = j0 + wn + 16 * y + l16;
-#pragma unroll
-      for (int v = 0; v < 4; v++) {
-        const int gi = i0 + wm + 16 * x + lg + 4 * v;
-        if (gi < g.M && gj < g.N) {
-          double2 *c = g.C + gi * g.sc_i + gj * g.sc_j;
-          const double2 val = cmul(g.alpha, make_double2((c1[x][y][v] - c2[x][y][v]), (c3[x][y][v] - c1[x][y][v] - c2[x][y][v])));
-          *c = g.accumulate ? cadd(*c, val) : val;
-        }
-      }
+  for (int v = 0; v < 4; v++) {
+    const int gi = i0 + wm + lg + 4 * v;
+    if (gi < g.M && gj < g.N) {
+      double2 *c = g.C + gi * g.sc_i + gj * g.sc_j;
+      const double2 val = cmul(g.alpha, make_double2(c1[v] - c2[v], c3[v] - c1[v] - c2[v]));
+      *c = g.accumulate ? cadd(*c, val) : val;
     }
+  }
 }
 
 void launch_gemm_gen(hipStream_t st, const GemmArgs &g) {
   if (g.M <= 0 || g.N <= 0) return;
-  dim3 grid((g.M + 63) / 64, (g.N + 63) / 64);
+  dim3 grid((g.M + GG_T - 1) / GG_T, (g.N + GG_T - 1) / GG_T);
   if (g.a_storage == 0 && g.b_storage == 0)
     hipLaunchKernelGGL((k_gemm_gen<double2, double2>), grid, dim3(256), 0, st, g);
   else if (g.a_storage == 0)
