@@ -6,12 +6,13 @@
 // blocks of 32.  A sweep runs the round-robin tournament over the blocks; in
 // one round every block is paired with one other block, and for every pair:
 //
-//   k_gram_mfma2 : G = X_IJ^H X_IJ (64x64 Hermitian), split over row chunks;
-//   k_eig        : G = V D V^H by cyclic two-sided Jacobi in LDS; a pair whose
+//   k_gram_mfma2, k_gram_cross : G = X_IJ^H X_IJ (64x64 Hermitian), split over
+//                  row chunks; whole, or only the block between I and J;
+//   k_eig, k_eig_full : G = V D V^H by cyclic two-sided Jacobi; a pair whose
 //                  columns are already orthogonal to tolerance is left alone;
-//   k_rot_mfma3  : X_IJ <- X_IJ V (and J_IJ <- J_IJ V).
+//   k_rot_cols, k_rot_mfma3 : X_IJ <- X_IJ V (and J_IJ <- J_IJ V).
 //
-// All pairs of all gates of a batch run in the same launches.  The sweep
+// Matrices of up to 64 columns that fit in LDS take k_small instead.  All pairs of all gates of a batch run in the same launches.  The sweep
 // ends the rounds; a gate converges after a sweep in which no pair rotated.
 // Then k_colnorm gives sigma_j^2 = ||x_j||^2 and k_trunc sorts them and
 // applies the truncation rule.

@@ -47,11 +47,6 @@ __device__ __forceinline__ double2 *qr_tgrp(const GateDesc &d, int stage, int gr
   return d.Tq + (size_t)2 * np * (QNB * QNB) + ((size_t)stage * ngp + group) * (QG * QG);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-
 // ---------------------------------------------------------------- panel
 
 // Factor columns j0 .. j0+w-1 (rows j0 ..) of one gate's matrix: one
@@ -370,33 +365,19 @@ void launch_qr_panel(hipStream_t st, const GateDesc *d, int ng, int stage, int p
 
 constexpr int QU_ROWS = 64;  // rows per LDS chunk
 
-// Apply a block reflector of NB Householder vectors (a panel, NB = QNB, or a
-// group of panels, NB = QG) to COLS target columns per workgroup:
-//   apply = 0: B = A(j0:, first:last) <- (I - V T V^H)^H B  (factoring: the
-//              columns after the block, up to col_end)
-//   apply = 1: B = U(j0:, 0:k) <- (I - V T V^H) B          (U = Q1 [W; 0])
-// S = V^H B over all rows, Y = op(T) S, B -= V Y; V is staged in LDS, the next
-// rows loaded meanwhile.
+// Apply a block reflector of NB Householder vectors to COLS target columns per
+// workgroup: B = A(j0:, first:last) <- (I - V T V^H)^H B, the columns after the
+// block up to col_end.  S = V^H B over all rows, Y = T^H S, B -= V Y; V is staged
+// in LDS, the next rows loaded meanwhile.
 template <int NB, int COLS, int NT>
 __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const double2 *T,
-                                int apply, int col_end) {
+                                int col_end) {
   static_assert((NB * COLS) % NT == 0 && NT % QU_ROWS == 0, "whole entries per thread");
   constexpr int EPT = NB * COLS / NT;
   if (j0 >= q.cols) return;
   const int w = min(NB, q.cols - j0);
-  double2 *B;
-  int ldb, rows, ncols;
-  if (apply) {
-    B = d.U;
-    ldb = d.ldu;
-    rows = d.m;
-    ncols = d.sc->k;
-  } else {
-    B = q.A + (size_t)(j0 + w) * q.ld;
-    ldb = q.ld;
-    rows = q.rows;
-    ncols = min(col_end, q.cols) - j0 - w;
-  }
+  const int ldb = q.ld, rows = q.rows, ncols = min(col_end, q.cols) - j0 - w;
+  double2 *B = q.A + (size_t)(j0 + w) * ldb;
   const int c0 = blockIdx.x * COLS;
   if (c0 >= ncols) return;
   const int nc = min(COLS, ncols - c0);
@@ -468,13 +449,13 @@ __device__ void qr_block_update(const GateDesc &d, const QrView q, int j0, const
     S[id / COLS][id % COLS] = sacc[e];
   }
   __syncthreads();
-  // phase 2: Y = T^H S (factor) or T S (apply)
+  // phase 2: Y = T^H S
 #pragma unroll
   for (int e = 0; e < EPT; e++) {
     const int id = tid + NT * e, p = id / COLS, cc = id % COLS;
     double2 y = make_double2(0.0, 0.0);
     for (int l = 0; l < NB; l++) {
-      const double2 t = apply ? Tl[p][l] : cconj(Tl[l][p]);
+      const double2 t = cconj(Tl[l][p]);
       y = cadd(y, cmul(t, S[l][cc]));
     }
     Y[p][cc] = y;
@@ -515,7 +496,7 @@ __global__ __launch_bounds__(QNB * QU_COLS) void k_qr_update(const GateDesc *des
                                                    int col_end) {
   const GateDesc &d = descs[blockIdx.y];
   if (!d.qr || d.storage == 0) return;
-  qr_block_update<QNB, QU_COLS, QNB * QU_COLS>(d, qr_view(d, stage), panel * QNB, qr_tfac(d, stage, panel), 0,
+  qr_block_update<QNB, QU_COLS, QNB * QU_COLS>(d, qr_view(d, stage), panel * QNB, qr_tfac(d, stage, panel),
                                 col_end);
 }
 
