@@ -491,6 +491,23 @@ tnsim_status pin_copy(tnsim_mps h, void *dev, size_t bytes) {
   return TNSIM_OK;
 }
 
+// Device memory to the caller's array, after everything on the handle's
+// stream.  What fits goes through the pinned staging buffer on that stream
+// (a direct copy to pageable memory took 24 us, whatever its size); larger
+// reads are copied directly.
+tnsim_status read_back(tnsim_mps h, void *host, const void *dev, size_t bytes) {
+  if (bytes <= h->pin_flag_off) {
+    tnsim_status s = fetch(h, h->stream, h->pin, dev, bytes);
+    if (s == TNSIM_OK) s = fetched(h, h->stream);
+    if (s != TNSIM_OK) return s;
+    memcpy(host, h->pin, bytes);
+    return TNSIM_OK;
+  }
+  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, hipMemcpy(host, dev, bytes, hipMemcpyDeviceToHost));
+  return TNSIM_OK;
+}
+
 // Descriptor of one two-qubit gate from its handle's current bond dimensions.
 // `o` owns the launches (profiling counters, the inner-sweep cap).
 GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
@@ -2870,23 +2887,6 @@ tnsim_status tnsim_last_batch(tnsim_mps h, int32_t *out, int32_t max_gates, int3
   return TNSIM_OK;
 }
 
-// Device memory to the caller's array, after everything on the handle's
-// stream.  What fits goes through the pinned staging buffer on that stream
-// (a direct copy to pageable memory took 24 us, whatever its size); larger
-// reads are copied directly.
-static tnsim_status read_back(tnsim_mps h, void *host, const void *dev, size_t bytes) {
-  if (bytes <= h->pin_flag_off) {
-    tnsim_status s = fetch(h, h->stream, h->pin, dev, bytes);
-    if (s == TNSIM_OK) s = fetched(h, h->stream);
-    if (s != TNSIM_OK) return s;
-    memcpy(host, h->pin, bytes);
-    return TNSIM_OK;
-  }
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  HIPCHK(h, hipMemcpy(host, dev, bytes, hipMemcpyDeviceToHost));
-  return TNSIM_OK;
-}
-
 tnsim_status tnsim_export_site(tnsim_mps h, int32_t q, tnsim_c128 *host, int32_t *chiL,
                                int32_t *chiR) {
   tnsim_status s = check_handle(h);
@@ -3084,9 +3084,12 @@ tnsim_status tnsim_backward(tnsim_mps h, double dloss, double *grad_angles) {
   }
   s = restore_ckpt(h, G.n_seg);
   if (s != TNSIM_OK) return s;
+  // The gradient comes through the handle's stream, after its adjoints (a
+  // blocking copy is not ordered after a stream of the caller's own), and after
+  // the restore: the caller may free the workspace now.
   if (G.n_params > 0)
-    HIPCHK(h, hipMemcpy(grad_angles, G.ws + G.grad, sizeof(double) * G.n_params,
-                        hipMemcpyDeviceToHost));
+    return read_back(h, grad_angles, G.ws + G.grad, sizeof(double) * G.n_params);
+  HIPCHK(h, hipStreamSynchronize(st));
   return TNSIM_OK;
 }
 
