@@ -286,6 +286,14 @@ struct tnsim_mps_s {
   int tune_rot_rows[TNSIM_TUNE_BUCKETS] = {0, 0, 0, 0};  // autotuned, 0 = built-in rule
   int tune_gram_ks[TNSIM_TUNE_BUCKETS] = {0, 0, 0, 0};   // autotuned, 0 = built-in rule
   hipGraphExec_t sweep_exec = nullptr;
+  // Executables that another plan has replaced, with the number of the last
+  // sweep launched before that: it may still be running them.
+  struct Retired {
+    hipGraphExec_t exec;
+    uint64_t last;
+  };
+  std::vector<Retired> retired;
+  uint64_t sweep_no = 0, sweep_at[2] = {0, 0};  // sweeps launched; the last one of each buffer
   long long sweep_key[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
   int64_t sw_gates = 0, sw_sum = 0;
   int sw_max = 0;
@@ -796,7 +804,7 @@ struct SweepRunner {
                               4 * P.cols + 2 * P.cross + P.full};
     if (h->sweep_exec && memcmp(key, h->sweep_key, sizeof key) == 0) return TNSIM_OK;
     if (h->sweep_exec) {
-      hipGraphExecDestroy(h->sweep_exec);
+      h->retired.push_back({h->sweep_exec, h->sweep_no});
       h->sweep_exec = nullptr;
     }
     hipGraph_t g = nullptr;
@@ -835,6 +843,7 @@ struct SweepRunner {
                             sizeof(SlotScalars) * P.na, 1 + buf);
     if (fs != TNSIM_OK) return fs;
     HIPCHK(h, hipEventRecord(h->ev_sw[buf], st));
+    h->sweep_at[buf] = ++h->sweep_no;
     return TNSIM_OK;
   }
 
@@ -844,6 +853,15 @@ struct SweepRunner {
     tnsim_mps h = o;
     tnsim_status fs = fetched(h, o->stream, 1 + buf, h->ev_sw[buf]);
     if (fs != TNSIM_OK) return fs;
+    if (!h->retired.empty()) {  // this sweep and those before it are done
+      HIPCHK(h, hipEventSynchronize(h->ev_sw[buf]));
+      auto &r = h->retired;
+      for (size_t k = r.size(); k-- > 0;)
+        if (r[k].last <= h->sweep_at[buf]) {
+          hipGraphExecDestroy(r[k].exec);
+          r.erase(r.begin() + k);
+        }
+    }
     if (h->prof) {  // only one sweep is ever in flight while profiling
       HIPCHK(h, hipStreamSynchronize(o->stream));
       prof_drain(h);
@@ -2138,6 +2156,7 @@ tnsim_status tnsim_mps_destroy(tnsim_mps h) {
   if (h->pin2) hipHostFree(h->pin2);
   prof_drain(h);
   if (h->sweep_exec) hipGraphExecDestroy(h->sweep_exec);
+  for (auto &r : h->retired) hipGraphExecDestroy(r.exec);
   for (hipEvent_t e : h->evpool) hipEventDestroy(e);
   if (h->pin) hipHostFree(h->pin);
   delete h;

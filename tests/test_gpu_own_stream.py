@@ -47,3 +47,34 @@ def test_gradient(T):
     for loss, grad in got[1:]:
         assert abs(loss - got[0][0]) < 1e-12
         assert np.max(np.abs(grad - got[0][1])) < 2.0 ** -53 * 2 ** 14
+
+
+def _state(T, n, chi, seed, **kw):
+    m = T.MPS(n, chi, 0.0, **kw)
+    m.import_state(*W.random_canonical_mps(n, W.saturated_dims(n, chi), seed))
+    return m
+
+
+@pytest.mark.parametrize("precision,storage,qr", [("fp64", "c128", False), ("fp64", "c128", True),
+                                                  ("bf16x6", "c64", True)])
+def test_layers_of_block_gates(T, precision, storage, qr):
+    """Bonds of 2 to 100: gates of one workgroup and gates of two to eight
+    column blocks in one batch, which converge at different sweeps, so that the
+    sweep's graph is replaced while one of its replays is in flight.  The
+    captured launches are the eager ones: equal bit for bit."""
+    import torch
+
+    n, kw = 20, dict(precision=precision, storage=storage, svd_precondition=qr)
+    e = _state(T, n, 100, 5, **kw)
+    own = _state(T, n, 100, 5, stream=torch.cuda.Stream(), **kw)
+    for layer in W.brickwork_haar(n, 4, 6):
+        assert e.apply_layer(layer) == T.OK and own.apply_layer(layer) == T.OK
+        rec = e.last_batch()
+        block = rec[np.minimum(rec[:, 1], rec[:, 3]) > 32]
+        assert len(block) >= 3 and block[:, 5].min() >= 2  # swept, not decomposed in one launch
+        assert np.array_equal(rec, own.last_batch())
+    assert len(set(rec[:, 5])) > 1
+    for q in range(n):
+        assert np.array_equal(own.site(q), e.site(q))
+    for b in range(n - 1):
+        assert np.array_equal(own.lam(b), e.lam(b))

@@ -35,3 +35,7 @@ def _run(exe, scenario):
 
 def test_gradient_is_read_after_its_adjoints(exe):
     _run(exe, "gradient")
+
+
+def test_a_replaced_graph_stays_until_its_sweep_is_done(exe):
+    _run(exe, "replan")
