@@ -78,3 +78,28 @@ def test_layers_of_block_gates(T, precision, storage, qr):
         assert np.array_equal(own.site(q), e.site(q))
     for b in range(n - 1):
         assert np.array_equal(own.lam(b), e.lam(b))
+
+
+def test_batch_of_handles_with_block_gates(T):
+    """Handles of uneven sizes in shared launches on a stream of their own
+    against each one by itself.  Another K-split adds a Gram's rows in another
+    order: equal to rounding."""
+    import torch
+
+    sizes = [(20, 100), (14, 70), (17, 40), (9, 100)]
+    s = torch.cuda.Stream()
+    own = [_state(T, n, chi, 7 + n, stream=s, max_layer_gates=(40 if k == 0 else 0))
+           for k, (n, chi) in enumerate(sizes)]
+    alone = [_state(T, n, chi, 7 + n) for n, chi in sizes]
+    circuits = [W.brickwork_haar(n, 3, 50 + n) for n, _ in sizes]
+    for l in range(3):
+        assert T.apply_layer_multi(own, [c[l] for c in circuits]) == T.OK
+        for m, c in zip(alone, circuits):
+            assert m.apply_layer(c[l]) == T.OK
+    for (n, chi), a, b in zip(sizes, alone, own):
+        assert list(a.bond_dims()) == list(b.bond_dims())
+        for k in range(n - 1):
+            assert np.max(np.abs(a.lam(k) - b.lam(k))) < 1e-12
+        c = T.MPS(n, chi)
+        c.copy_from(b)  # to the stream of `a`
+        assert abs(1 - abs(a.overlap(c)) ** 2 / (a.norm2() * c.norm2())) < 1e-12
