@@ -17,6 +17,8 @@
 // Then k_colnorm gives sigma_j^2 = ||x_j||^2 and k_trunc sorts them and
 // applies the truncation rule.
 
+#include <cfloat>
+
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 #include "tn_buffer.h"
@@ -662,9 +664,10 @@ __device__ __forceinline__ int eig_solve_g(const GateDesc &d, EigShared &S, int 
         gres = gc;
         if (!m) return;
         if (tid == 0) S.sweep_rot = 1;
-        const double delta = dq - dp;
+        const double delta = dq - dp, s2 = fma(delta, delta, 4.0 * h);
+        // (an infinite s2 gives no rotation, as 2 / inf does, and so E_NOCONV)
         const double tw = copysign(
-            2.0 * fast_rcp(fabs(delta) + fast_sqrt(fma(delta, delta, 4.0 * h))), delta);
+            s2 <= DBL_MAX ? 2.0 * fast_rcp(fabs(delta) + fast_sqrt(s2)) : 0.0, delta);
         const double wq = act ? tw * s2q : 0.0, wp = act ? tw * s2p : 0.0;
         if (param) {
           S.prm[w][0][si] = make_double2(wq * gc.x, -wq * gc.y);

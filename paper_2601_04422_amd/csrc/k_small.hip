@@ -22,6 +22,7 @@
 #include "tn_lanes.h"
 #include "tn_fast.h"
 
+#include <cfloat>
 #include <type_traits>
 
 namespace tn {
@@ -92,7 +93,8 @@ __device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotate
           // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
           // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
           const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
-          const double w = copysign(2.0 * fast_rcp(fabs(delta) + s2 * fast_rsqrt(s2)), delta);
+          const double w = copysign(
+              s2 <= DBL_MAX ? 2.0 * fast_rcp(fabs(delta) + s2 * fast_rsqrt(s2)) : 0.0, delta);
           const double wh = w * h, c = fast_rsqrt(fma(w, wh, 1.0)), cw = c * w;
           const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
 #pragma unroll
