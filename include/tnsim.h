@@ -95,7 +95,9 @@ typedef struct {
   double cutoff;             /* discarded-weight cutoff, >= 0 */
   int32_t precision;         /* tnsim_precision */
   int32_t storage;           /* tnsim_storage */
-  int32_t jacobi_max_sweeps; /* <= 0 selects 60 */
+  int32_t jacobi_max_sweeps; /* <= 0 selects 60; with a cap below 60 a complex128 gate that
+                                exceeds it is decomposed once more, its column pairs in the
+                                order that complex64 gates take, before it is refused */
   double jacobi_tol;         /* <= 0 selects max(rows, 16) * 2^-53 with complex128 sites,
                                 2^-30 with complex64 sites (64 times below their rounding) */
   int32_t max_layer_gates;   /* two-qubit gates processed together; <= 0 selects n/2 */

@@ -424,8 +424,9 @@ struct BatchItem {
 // Pair-count class of a launch, for the autotuned rotation shape.
 int tune_bucket(int pairs) { return pairs <= 32 ? 0 : pairs <= 128 ? 1 : pairs <= 512 ? 2 : 3; }
 
+constexpr int MAX_SWEEPS = 60;  // four times what the largest matrices take
 int max_sweeps(tnsim_mps o) {
-  return o->cfg.jacobi_max_sweeps > 0 ? o->cfg.jacobi_max_sweeps : 60;
+  return o->cfg.jacobi_max_sweeps > 0 ? o->cfg.jacobi_max_sweeps : MAX_SWEEPS;
 }
 
 SlotScalars *pin_scalars(tnsim_mps o, int buf = 0) {
@@ -517,8 +518,18 @@ tnsim_status read_back(tnsim_mps h, void *host, const void *dev, size_t bytes) {
 }
 
 // Descriptor of one two-qubit gate from its handle's current bond dimensions.
-// `o` owns the launches (profiling counters, the inner-sweep cap).
-GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
+// `o` owns the launches (profiling counters, the inner-sweep cap).  With
+// `full`, the block Jacobi in the order of all column pairs, whatever the size:
+// what a gate falls back to that another order, or k_small without the QR
+// preconditioner, did not finish within the sweep cap.  The counts differ by a
+// sweep or two, with the preconditioner and up to 64 columns by a factor of two
+// (7 or 8 sweeps against 14 or 15 at chi = 32), so a cap that was enough stays
+// enough.  Where the default cap is not enough, no order converges: no second
+// attempt.
+bool second_attempt(tnsim_mps o, const GateDesc &d) {
+  return (d.small || !d.fullOrder) && max_sweeps(o) < MAX_SWEEPS;
+}
+GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans, bool full = false) {
   GateDesc d;
   memset(&d, 0, sizeof d);
   const tnsim_mps h = it.h;
@@ -536,7 +547,7 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   // QR-preconditioned SVD for square or tall M that fits one panel workgroup
   // a matrix that one workgroup holds in LDS is decomposed there; with
   // complex64 sites the block Jacobi keeps such gates too (see fullOrder)
-  if (o->cfg.precision == TNSIM_FP64 && h->cfg.storage == TNSIM_STORE_C128)
+  if (!full && o->cfg.precision == TNSIM_FP64 && h->cfg.storage == TNSIM_STORE_C128)
     d.small = d.trans ? small_class(d.n, d.m, d.m) : small_class(d.m, d.n, 0);
   d.maxSweeps = max_sweeps(o);
   d.qr = h->cfg.svd_precondition && !d.trans && !d.small && d.m <= QR_MAX_ROWS;
@@ -556,7 +567,7 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans) {
   // phases; stored in complex64 these round differently, which moves the
   // state's norm by 1e-7, so such handles keep the order, and with it the
   // states they store bit for bit.  In complex128 the same change is 1e-15.
-  d.fullOrder = d.nblk == 2 || d.storage != TNSIM_STORE_C128;
+  d.fullOrder = full || d.nblk == 2 || d.storage != TNSIM_STORE_C128;
   d.innerSweeps = o->inner_sweeps;
   // default Jacobi tolerance: float64 level for complex128 sites; for
   // complex64 sites 2^-30, a factor 64 below the rounding of the stored
@@ -893,8 +904,10 @@ void record_gate(const BatchItem &it, const GateDesc &d, int k, int sweeps) {
 // Everything after convergence: norms, sort and truncation, U_k, the
 // write-back; updates each handle's bond dimensions and statistics.  With
 // `staged`, the descriptors of exactly these gates are in place already.
+// TNSIM_E_NOCONV: the small gates marked in `failed` ran out of sweeps; none of
+// the gates has been written back or recorded.
 tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D,
-                          const int *sweeps, int ng, bool staged = false) {
+                          const int *sweeps, int ng, bool staged, std::vector<char> &failed) {
   tnsim_mps h = o;
   hipStream_t st = o->stream;
   int maxM = 0, maxN = 0, maxColsPad = 0, qrN = 0;
@@ -930,14 +943,10 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
   prof_drain(h);
   // a small gate that ran out of sweeps: nothing was cut (k_trunc), nothing
   // is written back
-  bool failed = false;
-  for (int g = 0; g < ng; g++) failed |= D[g].small && sc_pin[g].rot;
-  if (failed) {
-    for (int g = 0; g < ng; g++)
-      record_gate(items[g], D[g], 0, D[g].small ? sc_pin[g].sweeps : sweeps[g]);
-    o->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
-    return TNSIM_E_NOCONV;
-  }
+  failed.assign(ng, 0);
+  bool any = false;
+  for (int g = 0; g < ng; g++) any |= failed[g] = D[g].small && sc_pin[g].rot;
+  if (any) return TNSIM_E_NOCONV;
   int maxK = 0, qrK = 0, qrM = 0;
   double wbl_byte = 0.0, wbr_flop = 0.0, wbr_byte = 0.0, qa_flop = 0.0;
   for (int g = 0; g < ng; g++) {
@@ -989,9 +998,28 @@ tnsim_status gates_finish(tnsim_mps o, const BatchItem *items, const GateDesc *D
 // Run a batch of two-qubit gates (possibly of several handles) through the
 // whole path in the same launches.  `o` owns the descriptors, the stream and
 // the profiling; every gate works in its own handle's state and slot.
-tnsim_status run_2q_items(tnsim_mps o, const BatchItem *items, int ng, bool force_trans) {
+tnsim_status run_2q_items(tnsim_mps o, const BatchItem *items, int ng, bool force_trans,
+                          bool full = false) {
   std::vector<GateDesc> D(ng);
-  for (int g = 0; g < ng; g++) D[g] = make_desc(o, items[g], force_trans);
+  for (int g = 0; g < ng; g++) D[g] = make_desc(o, items[g], force_trans, full);
+  // nothing of a batch that ran out of sweeps is written: it can start again
+  // in the order of all pairs (see make_desc)
+  auto unfinished = [&](const std::vector<int> &swp) -> tnsim_status {
+    for (const GateDesc &d : D)
+      if (second_attempt(o, d)) return run_2q_items(o, items, ng, force_trans, true);
+    for (int g = 0; g < ng; g++) record_gate(items[g], D[g], 0, swp[g]);
+    o->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
+    return TNSIM_E_NOCONV;
+  };
+  auto finish = [&](const std::vector<int> &swp, bool staged) -> tnsim_status {
+    std::vector<char> failed;
+    tnsim_status f = gates_finish(o, items, D.data(), swp.data(), ng, staged, failed);
+    if (f != TNSIM_E_NOCONV) return f;
+    std::vector<int> taken = swp;
+    for (int g = 0; g < ng; g++)
+      if (D[g].small) taken[g] = pin_scalars(o)[g].sweeps;
+    return unfinished(taken);
+  };
   tnsim_status s = gates_prepare(o, D.data(), ng);
   if (s != TNSIM_OK) return s;
 
@@ -999,8 +1027,7 @@ tnsim_status run_2q_items(tnsim_mps o, const BatchItem *items, int ng, bool forc
   std::vector<int> done_at(ng, 0), act;
   for (int g = 0; g < ng; g++)
     if (!D[g].small) act.push_back(g);
-  if (act.empty())
-    return gates_finish(o, items, D.data(), done_at.data(), ng, /*staged=*/true);
+  if (act.empty()) return finish(done_at, /*staged=*/true);
   SweepRunner sw{o};
   auto replan = [&]() {
     std::vector<const GateDesc *> pd;
@@ -1067,12 +1094,7 @@ tnsim_status run_2q_items(tnsim_mps o, const BatchItem *items, int ng, bool forc
   }
   std::vector<int> swp(ng);
   for (int g = 0; g < ng; g++) swp[g] = done_at[g] ? done_at[g] : sweeps;
-  if (!converged) {
-    for (int g = 0; g < ng; g++) record_gate(items[g], D[g], 0, swp[g]);
-    o->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
-    return TNSIM_E_NOCONV;
-  }
-  return gates_finish(o, items, D.data(), swp.data(), ng);
+  return converged ? finish(swp, /*staged=*/false) : unfinished(swp);
 }
 
 
@@ -1288,6 +1310,7 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
     const tnsim_c128 *m = nullptr;
     int npred = 0;
     std::vector<int> succ;
+    bool full = false;  // second attempt (see make_desc)
   };
   const int n = h->L.n;
   std::vector<Op> ops(ng);
@@ -1321,12 +1344,13 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
   std::vector<int> ready1, ready2;  // kept in circuit order
   for (int k = 0; k < ng; k++)
     if (ops[k].npred == 0) (ops[k].kind == 1 ? ready1 : ready2).push_back(k);
+  auto set_ready = [&](int k) {
+    auto &r = ops[k].kind == 1 ? ready1 : ready2;
+    r.insert(std::upper_bound(r.begin(), r.end(), k), k);
+  };
   auto release = [&](int k) {
     for (int j : ops[k].succ)
-      if (--ops[j].npred == 0) {
-        auto &r = ops[j].kind == 1 ? ready1 : ready2;
-        r.insert(std::upper_bound(r.begin(), r.end(), j), j);
-      }
+      if (--ops[j].npred == 0) set_ready(j);
   };
 
   struct Flight {
@@ -1379,7 +1403,7 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
       const int k = ready2[taken];
       BatchItem it{h, free_slots.back(), &ops[k].p};
       free_slots.pop_back();
-      nd.push_back(make_desc(h, it, false));
+      nd.push_back(make_desc(h, it, false, ops[k].full));
       nf.push_back(Flight{it, nd.back(), k, 0});
     }
     ready2.erase(ready2.begin(), ready2.begin() + taken);
@@ -1409,21 +1433,51 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
       if (ready1.empty() && ready2.empty()) break;
       continue;
     }
+    // a gate that ran out of sweeps takes its second attempt from the start
+    auto again = [&](const Flight &f) {
+      ops[f.op].full = true;
+      free_slots.push_back(f.it.slot);
+      set_ready(f.op);
+      dirty = true;
+    };
+    auto unfinished = [&](const Flight &f, int sweeps) {
+      record_gate(f.it, f.d, 0, sweeps);
+      h->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
+      return TNSIM_E_NOCONV;
+    };
     // write back the gates of `fin` and release their successors
-    auto finish = [&](const std::vector<Flight> &fin, bool staged) -> tnsim_status {
-      std::vector<BatchItem> fi;
-      std::vector<GateDesc> fd;
-      std::vector<int> fs;
-      for (const Flight &f : fin) {
-        fi.push_back(f.it);
-        fd.push_back(f.d);
-        fs.push_back(f.sweeps);
-      }
-      tnsim_status s = gates_finish(h, fi.data(), fd.data(), fs.data(), (int)fin.size(), staged);
-      if (s != TNSIM_OK) return s;
-      for (const Flight &f : fin) {
-        free_slots.push_back(f.it.slot);
-        release(f.op);
+    auto finish = [&](std::vector<Flight> fin, bool staged) -> tnsim_status {
+      while (!fin.empty()) {
+        std::vector<BatchItem> fi;
+        std::vector<GateDesc> fd;
+        std::vector<int> fs;
+        for (const Flight &f : fin) {
+          fi.push_back(f.it);
+          fd.push_back(f.d);
+          fs.push_back(f.sweeps);
+        }
+        std::vector<char> failed;
+        tnsim_status s = gates_finish(h, fi.data(), fd.data(), fs.data(), (int)fin.size(), staged,
+                                      failed);
+        if (s == TNSIM_E_NOCONV) {  // the others without them
+          std::vector<Flight> rest;
+          for (size_t a = 0; a < fin.size(); a++)
+            if (!failed[a])
+              rest.push_back(fin[a]);
+            else if (second_attempt(h, fin[a].d))
+              again(fin[a]);
+            else
+              return unfinished(fin[a], max_sweeps);
+          fin.swap(rest);
+          staged = false;
+          continue;
+        }
+        if (s != TNSIM_OK) return s;
+        for (const Flight &f : fin) {
+          free_slots.push_back(f.it.slot);
+          release(f.op);
+        }
+        fin.clear();
       }
       dirty = true;
       return TNSIM_OK;
@@ -1464,14 +1518,14 @@ tnsim_status run_circuit_impl(tnsim_mps h, const tnsim_gate *gates, int ng) {
       fl[a].sweeps++;
       if (!rot[a])
         fin.push_back(fl[a]);
-      else if (fl[a].sweeps >= max_sweeps) {
-        record_gate(fl[a].it, fl[a].d, 0, fl[a].sweeps);
-        h->err = "Jacobi SVD did not converge within jacobi_max_sweeps";
-        return TNSIM_E_NOCONV;
-      } else
+      else if (fl[a].sweeps < max_sweeps)
         keep.push_back(fl[a]);
+      else if (second_attempt(h, fl[a].d))
+        again(fl[a]);
+      else
+        return unfinished(fl[a], fl[a].sweeps);
     }
-    if (!fin.empty()) {
+    if (keep.size() < fl.size()) {
       fl.swap(keep);
       s = finish(fin, false);
       if (s != TNSIM_OK) return s;
