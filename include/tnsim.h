@@ -386,7 +386,10 @@ tnsim_status tnsim_probe_fp64(tnsim_mps mps, int32_t unit, int32_t iters, double
    more pairs per launch, largest gate the handle can hold) and keeps the
    fastest shape of each; later sweeps use the table instead of the built-in
    rules:
-     - the rotation: rows per workgroup, one of 64, 128, 256, 512;
+     - the rotation: rows per workgroup, one of 64, 128, 256, 512 (a launch of
+       up to 24576 tiles of 64 columns x 16 rows, whose workgroups split the
+       columns over their wavefronts, takes a quarter of that), timed with
+       the kernel that a launch of that class takes;
      - the pair Grams: K-split, the number of row chunks (1, 2, 4, 8, 16)
        whose partial Grams the pair solve adds up, within the handle's pool
        of partials (room for a K-split of 4 with every slot in use).

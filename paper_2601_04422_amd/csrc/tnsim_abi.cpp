@@ -424,6 +424,17 @@ struct BatchItem {
 // Pair-count class of a launch, for the autotuned rotation shape.
 int tune_bucket(int pairs) { return pairs <= 32 ? 0 : pairs <= 128 ? 1 : pairs <= 512 ? 2 : 3; }
 
+// Rotations with the columns split over the wavefronts (k_rot_cols) until
+// X no longer fits the last-level cache (its four reads of a tile then
+// cost more than they hide).  us per launch, whole tiles per wavefront against
+// split: 36 tiles of 16 rows 13.8 / 5.3, 384 18.3 / 9.5, 1400 25 / 11.6, 7800
+// 28.9 / 26.5, 10900 29.7 / 27.5, 18500 49.7 / 43.5; 46000 170 / 197.  Their four
+// wavefronts all pass over a workgroup's rows instead of a quarter each, so
+// an entry of the launch table stands for a quarter of its rows there.
+constexpr long long ROT_COLS_TILES = 24576;
+constexpr int ROT_COLS_SHARE = 4;
+long long rot_tiles(int pairs, int rows) { return (long long)pairs * ((rows + 15) / 16); }
+
 constexpr int MAX_SWEEPS = 60;  // four times what the largest matrices take
 int max_sweeps(tnsim_mps o) {
   return o->cfg.jacobi_max_sweeps > 0 ? o->cfg.jacobi_max_sweeps : MAX_SWEEPS;
@@ -752,18 +763,13 @@ struct SweepRunner {
     P.ksplit = std::max(ks, 1);
     const int rchunks = std::max(1, P.maxRows + P.maxMtrans);
     const int tuned = o->tune_rot_rows[tune_bucket(pairs)];
-    // Rotations with the columns split over the wavefronts (k_rot_cols) until
-    // X no longer fits the last-level cache (its four reads of a tile then
-    // cost more than they hide), at least about 512 workgroups where the tiles
-    // suffice.  us per launch, whole tiles per wavefront against split: 36
-    // tiles of 16 rows 13.8 / 5.3, 384 18.3 / 9.5, 1400 25 / 11.6, 7800 28.9 /
-    // 26.5, 10900 29.7 / 27.5, 18500 49.7 / 43.5; 46000 170 / 197.
-    const long long tiles = (long long)pairs * ((rchunks + 15) / 16);
-    P.cols = tiles <= 24576;
-    if (P.cols) {
+    // k_rot_cols: at least about 512 workgroups where the tiles suffice
+    const long long tiles = rot_tiles(pairs, rchunks);
+    P.cols = tiles <= ROT_COLS_TILES;
+    if (tuned > 0) {
+      P.rotRows = P.cols ? tuned / ROT_COLS_SHARE : tuned;
+    } else if (P.cols) {
       P.rotRows = tiles <= 512 ? 16 : tiles <= 2048 ? 32 : 64;
-    } else if (tuned > 0) {
-      P.rotRows = tuned;
     } else {
       while (P.rotRows > 64 && (long long)pairs * ((rchunks + P.rotRows - 1) / P.rotRows) < 1024)
         P.rotRows /= 2;
@@ -3288,25 +3294,26 @@ tnsim_status tnsim_autotune(tnsim_mps h, int32_t *table_out) {
   HIPCHK(h, hipEventCreate(&e1));
   for (int bk = 0; bk < TNSIM_TUNE_BUCKETS; bk++) {
     const int ng = std::max(1, std::min(L.nslots, (want[bk] + npairs - 1) / npairs));
+    const bool rcols = rot_tiles(ng * npairs, rows) <= ROT_COLS_TILES;
     int best = 0;
     float best_ms = 0.0f;
     for (int ci = 0; ci < 4; ci++) {
-      const int rr = cand[ci];
+      const int rr = rcols ? cand[ci] / ROT_COLS_SHARE : cand[ci];
       for (int g = 0; g < ng; g++) D[g].rotRows = rr;
       memcpy(h->pin, D.data(), sizeof(GateDesc) * ng);
       h->pin_copies++;
       HIPCHK(h, hipMemcpyAsync(ddev, h->pin, sizeof(GateDesc) * ng, hipMemcpyHostToDevice,
                                h->stream));
-      launch_rot(h->stream, ddev, ng, 0, npairs, rows, 0, rr, false);  // warm-up
+      launch_rot(h->stream, ddev, ng, 0, npairs, rows, 0, rr, rcols);  // warm-up
       HIPCHK(h, hipEventRecord(e0, h->stream));
-      for (int r = 0; r < 3; r++) launch_rot(h->stream, ddev, ng, r, npairs, rows, 0, rr, false);
+      for (int r = 0; r < 3; r++) launch_rot(h->stream, ddev, ng, r, npairs, rows, 0, rr, rcols);
       HIPCHK(h, hipEventRecord(e1, h->stream));
       LAUNCHCHK(h, "autotune");
       HIPCHK(h, hipEventSynchronize(e1));
       float ms = 0.0f;
       HIPCHK(h, hipEventElapsedTime(&ms, e0, e1));
       if (best == 0 || ms < best_ms) {
-        best = rr;
+        best = cand[ci];
         best_ms = ms;
       }
     }
