@@ -60,3 +60,46 @@ def test_autotuned_table_is_taken(T):
     for layer in W.brickwork_haar(n, 2, 8):
         assert a.apply_layer(layer) == T.OK and b.apply_layer(layer) == T.OK
     _equal(a, b)
+
+
+@pytest.mark.parametrize("precision,storage", [("fp64", "c128"), ("bf16x6", "c64")])
+def test_launches_of_many_pairs(T, precision, storage):
+    """Four handles of 40 gates, up to eight column pairs each: 1056 pairs and
+    more than 24576 tiles in a launch, which takes the pair solves that share a CU
+    and the rotation by whole tiles, against each handle by itself, which takes
+    neither.  One K-split, so every sum has the same order: equal bit for bit
+    with complex64 sites; the pair solve by passes is compiled anew for two to a
+    CU, which may contract its products otherwise: equal to rounding."""
+    n, chi = 80, 256
+    kw = dict(precision=precision, storage=storage, svd_precondition=True)
+    one = W.random_canonical_mps(16, W.saturated_dims(16, chi), 9)
+    rng = np.random.default_rng(10)
+    bulk = [W.random_isometry(rng, 2 * chi, chi).reshape(chi, 2, chi) for _ in range(3)]
+    sites = one[0][:8] + [bulk[q % 3] for q in range(n - 16)] + one[0][8:]
+    lams = one[1][:8] + [one[1][7]] * (n - 16) + one[1][8:]
+    circuits = [W.brickwork_haar(n, 1, 20 + k)[0] for k in range(4)]
+
+    def handle(k):
+        m = T.MPS(n, chi, 1e-12, max_layer_gates=(160 if k == 0 else 0), **kw)
+        m.import_state(sites, lams)
+        m.set_autotune([0, 0, 0, 0, 1, 1, 1, 1])
+        return m
+
+    batch = [handle(k) for k in range(4)]
+    big = sum(1 for q in range(0, n - 1, 2) if min(q, n - 2 - q) >= 8) * 4
+    assert big * 8 > 512 and big * 8 * (2 * chi // 16) > 24576
+    assert T.apply_layer_multi(batch, circuits) == T.OK
+    for k in range(4):
+        alone = T.MPS(n, chi, 1e-12, **kw)
+        alone.import_state(sites, lams)
+        alone.set_autotune([0, 0, 0, 0, 1, 1, 1, 1])
+        assert alone.apply_layer(circuits[k]) == T.OK
+        if storage == "c64":
+            _equal(alone, batch[k])
+        else:
+            assert list(alone.bond_dims()) == list(batch[k].bond_dims())
+            for b in range(n - 1):
+                assert np.max(np.abs(alone.lam(b) - batch[k].lam(b))) < 1e-12
+            f = abs(alone.overlap(batch[k])) ** 2 / (alone.norm2() * batch[k].norm2())
+            assert abs(1 - f) < 1e-12
+        alone.close()
