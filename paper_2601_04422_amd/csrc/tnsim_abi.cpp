@@ -1646,19 +1646,10 @@ GradState grad_layout(const Layout &L, int n_seg, int max_seg, int n_params) {
   off += G.env_stride * (n + 1);
   G.envR = off;
   off += G.env_stride * (n + 1);
-  G.envLS = off;
-  off += G.env_stride * (n + 1);
-  G.envRS = off;
-  off += G.env_stride * (n + 1);
-  G.envT = off;
-  off += G.env_stride * (n + 3);
   G.envF = off;
   off = align_up(off + sizeof(double2) * (size_t)maxbond * 2 * maxbond);
   G.envF2 = off;
   off = align_up(off + sizeof(double2) * (size_t)maxbond * 2 * maxbond);
-  G.tmp_stride = align_up(sizeof(double2) * cmax * cmax);
-  G.tmp0 = off;
-  off += G.tmp_stride * 12;
   G.lam2 = off;
   off = align_up(off + sizeof(double) * cmax);
   G.sbar = off;
@@ -1669,6 +1660,17 @@ GradState grad_layout(const Layout &L, int n_seg, int max_seg, int n_params) {
   off = align_up(off + 64);
   G.grad = off;
   off = align_up(off + sizeof(double) * std::max(n_params, 1));
+  // The environments that the terms of the loss share, of use before the first
+  // record only, lie where the adjoint's matrices and the records do (48 and
+  // 10 or more matrices of their size); segments of a gate or two on a long
+  // chain leave too little there, and the workspace is larger for it.
+  G.envLS = off;
+  G.envRS = G.envLS + G.env_stride * (n + 1);
+  G.envT = G.envRS + G.env_stride * (n + 1);
+  const size_t env_end = G.envT + G.env_stride * (n + 3);
+  G.tmp_stride = align_up(sizeof(double2) * cmax * cmax);
+  G.tmp0 = off;
+  off += G.tmp_stride * 12;
   // per-gate records
   const size_t site_max = (size_t)maxbond * 2 * maxbond;
   size_t r = 0;
@@ -1689,7 +1691,7 @@ GradState grad_layout(const Layout &L, int n_seg, int max_seg, int n_params) {
   G.rec_stride = r;
   G.rec0 = off;
   off = align_up(off + r * std::max(max_seg, 1));
-  G.total = off;
+  G.total = std::max(off, env_end);
   G.n = n;
   G.n_seg = n_seg;
   G.max_seg = max_seg;

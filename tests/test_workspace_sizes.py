@@ -1,0 +1,25 @@
+"""Device memory that callers hand in: sizes as programs have them from earlier
+versions of the library must go on to be accepted.  Host only."""
+import ctypes as C
+
+import pytest
+
+from paper_2601_04422_amd import tnsim as T
+
+
+def _cfg(n, chi, storage=0, precondition=0, layer_gates=0):
+    return T.Config(n, chi, 0.0, 0, storage, 0, 0.0, layer_gates, precondition)
+
+
+# (n, chi, storage, segments, gates per segment, parameters, bytes)
+GRADIENT = [(2, 1, 0, 1, 1, 1, 10496), (10, 32, 0, 4, 10, 40, 3468800),
+            (14, 64, 0, 4, 14, 56, 19063808), (14, 64, 0, 42, 1, 14, 25584384),
+            (16, 24, 1, 8, 48, 256, 6117376), (20, 90, 0, 4, 20, 80, 56017664),
+            (40, 128, 0, 8, 120, 640, 556737024), (32, 16, 0, 4, 32, 128, 3377664),
+            (100, 1024, 0, 4, 100, 400, 40776039168), (100, 1024, 0, 8, 300, 1600, 91967023104)]
+
+
+@pytest.mark.parametrize("n,chi,storage,segments,gates,params,known", GRADIENT)
+def test_gradient_workspace(n, chi, storage, segments, gates, params, known):
+    cfg = _cfg(n, chi, storage)
+    assert T.lib().tnsim_grad_workspace_bytes(C.byref(cfg), segments, gates, params) <= known
