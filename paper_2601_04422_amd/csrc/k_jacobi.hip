@@ -424,11 +424,16 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
       int o[4];
       double2 x[4];
 #pragma unroll
-      for (int k = 0; k < 4; k++) o[k] = e0 + k * THREADS;
-      sums(o, x);  // entries below the stored tiles are read and dropped
+      for (int k = 0; k < 4; k++) {  // entries below the diagonal: any other is read and dropped
+        const int e = e0 + k * THREADS;
+        o[k] = e / PW <= e % PW ? e : 0;
+      }
+      sums(o, x);
 #pragma unroll
-      for (int k = 0; k < 4; k++)
-        if (o[k] / PW <= o[k] % PW) put(o[k] / PW, o[k] % PW, x[k]);
+      for (int k = 0; k < 4; k++) {
+        const int e = e0 + k * THREADS;
+        if (e / PW <= e % PW) put(e / PW, e % PW, x[k]);
+      }
     }
     return;
   }
@@ -437,8 +442,9 @@ __device__ __forceinline__ void pair_gram(const GateDesc &d, int I, int J, int r
   double2 dI[CE], dJ[CE];
 #pragma unroll
   for (int k = 0; k < CE; k++) {
-    dI[k] = d.Dg[(size_t)I * (BW * BW) + tid + k * THREADS];
-    dJ[k] = d.Dg[(size_t)J * (BW * BW) + tid + k * THREADS];
+    const int e = tid + k * THREADS, o = e / BW * PW + e % BW;
+    dI[k] = d.Dg[(size_t)I * (PW * PW) + o];
+    dJ[k] = d.Dg[(size_t)J * (PW * PW) + o];
   }
   int o[4];
   double2 x[4];
@@ -903,7 +909,7 @@ __global__ __launch_bounds__(EIG_THREADS, WAVES) void k_eig(const GateDesc *desc
     for (int e = tid; e < 2 * BW * BW; e += EIG_THREADS) {
       const int blk = e / (BW * BW), r = (e / BW) % BW, c = e % BW, o = blk * BW;
       if (r <= c)
-        d.Dg[(size_t)(blk ? J : I) * (BW * BW) + r * BW + c] =
+        d.Dg[(size_t)(blk ? J : I) * (PW * PW) + r * PW + c] =
             r < c ? S.Gs[gpack(o + r, o + c)] : make_double2(S.dg[o + r], 0.0);
     }
   }

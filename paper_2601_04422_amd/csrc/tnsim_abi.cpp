@@ -24,6 +24,11 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t x, size_t a = ALIGN) { return (x + a - 1) / a * a; }
 inline int pad_to(int x, int a) { return (x + a - 1) / a * a; }
 
+// One-qubit gates of a layer above which their descriptors are staged: up to
+// four launches with the descriptors as arguments, 4 us each, cost less (12 us
+// and one launch).
+constexpr int GATE1_STAGED = 128;
+
 struct Layout {
   int n = 0, chi_max = 0, storage = 0, nslots = 0, desc_cap = 0;
   size_t elem = 16;                 // site element bytes
@@ -33,11 +38,11 @@ struct Layout {
   size_t dims_off = 0, site_tab_off = 0, lam_tab_off = 0;
   int cmax = 0, ldx_max = 0, cols_pad_max = 0, npairs_max = 0, gp_blocks = 0;
   size_t slot_bytes = 0, slot0_off = 0;
-  size_t x_off = 0, j_off = 0, t_off = 0, v_off = 0, dg_off = 0, pf_off = 0, ver_off = 0, seen_off = 0,
+  size_t x_off = 0, j_off = 0, t_off = 0, v_off = 0, pf_off = 0, ver_off = 0, seen_off = 0,
          sig_off = 0, perm_off = 0, sc_off = 0, u_off = 0, tq_off = 0;  // within a slot
   size_t gp_off = 0;  // pooled pair-Gram partials
   size_t desc_off = 0, desc2_off = 0, d1_off = 0, ctr_off = 0, scg_off = 0;
-  size_t e0_off = 0, e1_off = 0, f_off = 0, f2_off = 0, va_off = 0, vb_off = 0;
+  size_t va_off = 0, vb_off = 0;
   size_t total = 0;
 };
 
@@ -114,8 +119,6 @@ Layout make_layout(const tnsim_config &c) {
   s = align_up(s + sizeof(double2) * (size_t)L.cmax * L.cmax);
   L.v_off = s;
   s = align_up(s + sizeof(double2) * (size_t)L.npairs_max * PW * PW);
-  L.dg_off = s;
-  s = align_up(s + sizeof(double2) * 2 * (size_t)L.npairs_max * BW * BW);
   L.pf_off = s;
   s = align_up(s + sizeof(int) * L.npairs_max);
   L.ver_off = s;
@@ -149,21 +152,10 @@ Layout make_layout(const tnsim_config &c) {
   off = align_up(off + sizeof(GateDesc) * L.desc_cap);
   L.scg_off = off;
   off = align_up(off + sizeof(SlotScalars) * L.desc_cap);
-  L.d1_off = off;
-  off = align_up(off + sizeof(Gate1Desc) * n);
+  L.d1_off = off;  // one-qubit gates that do not fit a launch's arguments
+  if (n > GATE1_STAGED) off = align_up(off + sizeof(Gate1Desc) * n);
   L.ctr_off = off;
   off = align_up(off + sizeof(unsigned long long) * CTR_COUNT);
-  const size_t ee = sizeof(double2) * (size_t)maxbond * maxbond;
-  const size_t ff = sizeof(double2) * (size_t)maxbond * 2 * maxbond;
-  // E and F hold two contractions side by side (transfer())
-  L.e0_off = off;
-  off = align_up(off + 2 * ee);
-  L.e1_off = off;
-  off = align_up(off + 2 * ee);
-  L.f_off = off;
-  off = align_up(off + 2 * ff);
-  L.f2_off = off;
-  off = align_up(off + ff);
   L.va_off = off;
   off = align_up(off + sizeof(double2) * maxbond);
   L.vb_off = off;
@@ -608,7 +600,9 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans, bool full
   }
   d.T = sl + L.t_off;
   d.V = (double2 *)(sl + L.v_off);
-  d.Dg = (double2 *)(sl + L.dg_off);
+  static_assert(GP_PER_SLOT >= 2, "a quadrant for every column block");
+  d.Dg = h->at<double2>(L.gp_off) + (size_t)GP_PER_SLOT * it.slot * L.npairs_max * PW * PW +
+         BW * PW;
   d.pairFlag = (int *)(sl + L.pf_off);
   d.blkVer = o->pair_skip ? (int *)(sl + L.ver_off) : nullptr;
   d.pairSeen = o->pair_skip ? (int2 *)(sl + L.seen_off) : nullptr;
@@ -1166,9 +1160,7 @@ tnsim_status run_1q(tnsim_mps h, const std::vector<std::pair<int, const tnsim_c1
     for (int e = 0; e < 4; e++) d.u[e] = to_d2(gs[k].second[e]);
     maxe = std::max(maxe, d.chiL * d.chiR);
   }
-  // up to four launches with the descriptors as arguments, 4 us each, cost
-  // less than staging them (12 us and one launch)
-  const bool args = D.size() <= 128;
+  const bool args = D.size() <= GATE1_STAGED;
   Gate1Desc *ddev = h->at<Gate1Desc>(h->L.d1_off);
   if (!args || h->prof) {
     tnsim_status s = pin_free(h);
@@ -1558,8 +1550,10 @@ tnsim_status transfer(tnsim_mps h, tnsim_mps bra, tnsim_mps ket, const double2 *
                       const char *isI, double2 *out) {
   const Layout &L = h->L;
   hipStream_t st = h->stream;
-  double2 *E = h->at<double2>(L.e0_off), *E2 = h->at<double2>(L.e1_off);
-  double2 *F = h->at<double2>(L.f_off), *F2 = h->at<double2>(L.f2_off);
+  // two E of 2 chi^2 entries, F of 4 and F2 of 2, in the first slot (X, J and T
+  // hold 4 chi^2 each), which no gate is using
+  double2 *E = (double2 *)(h->slot(0) + L.x_off), *E2 = E + (size_t)L.cmax * L.cmax / 2;
+  double2 *F = (double2 *)(h->slot(0) + L.j_off), *F2 = (double2 *)(h->slot(0) + L.t_off);
   launch_put(st, E, make_double2(1.0, 0.0));
   const int n = L.n;
   int nb = 1;  // 1, then 2 from the first operator on: without, with operators
@@ -2619,9 +2613,10 @@ tnsim_status tnsim_amplitude(tnsim_mps h, const uint8_t *bits, tnsim_c128 *out) 
     if (bits[q] > 1) return TNSIM_E_ARG;
   hipStream_t st = h->stream;
   double2 *v = h->at<double2>(h->L.va_off), *w = h->at<double2>(h->L.vb_off);
+  double2 *part = (double2 *)(h->slot(0) + h->L.j_off);
   launch_put(st, v, make_double2(1.0, 0.0));
   for (int q = 0; q < n; q++) {
-    launch_amp_step(st, v, w, h->at<double2>(h->L.f_off), h->site(q), h->L.storage, h->dims[q],
+    launch_amp_step(st, v, w, part, h->site(q), h->L.storage, h->dims[q],
                     h->dims[q + 1], bits[q]);
     LAUNCHCHK(h, "amplitude");
     std::swap(v, w);

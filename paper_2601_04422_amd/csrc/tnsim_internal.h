@@ -72,8 +72,10 @@ struct GateDesc {
   double2 *X, *J;        // Jacobi matrix, accumulated left vectors (trans only)
   void *T;               // theta' (m x n, row-major)
   double2 *Gp, *V;       // pair Gram partials, pair rotations
-  double2 *Dg;           // per column block: its own Gram (upper triangle of 32x32) as its
-                         // last pair solve left it
+  double2 *Dg;           // per column block b: its own Gram (upper triangle of 32x32) as its last
+                         // pair solve left it, entry (r, c) at Dg[b * 64 * 64 + r * 64 + c]: the
+                         // quadrant below the diagonal of the slot's part of the pool of Gram
+                         // partials, which no partial fills
   int *pairFlag;         // pair rotated in this round
   int *blkVer;           // per column block: number of rotations applied to it so far
   int2 *pairSeen;        // per block pair (I * nblk + J): block versions when the pair

@@ -23,3 +23,18 @@ GRADIENT = [(2, 1, 0, 1, 1, 1, 10496), (10, 32, 0, 4, 10, 40, 3468800),
 def test_gradient_workspace(n, chi, storage, segments, gates, params, known):
     cfg = _cfg(n, chi, storage)
     assert T.lib().tnsim_grad_workspace_bytes(C.byref(cfg), segments, gates, params) <= known
+
+
+# (n, chi, storage, preconditioned, layer gates, bytes)
+ARENA = [(2, 1, 0, 0, 0, 1154304), (10, 32, 0, 0, 0, 2784000), (14, 64, 0, 0, 0, 10957824),
+         (16, 24, 1, 1, 0, 5173504), (20, 90, 0, 1, 0, 38107392), (40, 128, 0, 1, 0, 132708608),
+         (64, 256, 1, 1, 0, 700195584), (36, 1024, 0, 1, 0, 5751303680),
+         (100, 1024, 0, 1, 0, 16910579968), (100, 1024, 0, 0, 1, 3067522304),
+         (28, 500, 0, 0, 1, 181942528), (50, 2048, 1, 1, 8, 11172870912),
+         (100, 33, 0, 0, 0, 56197376), (100, 3, 0, 0, 0, 18297856)]
+
+
+@pytest.mark.parametrize("n,chi,storage,precondition,layer_gates,known", ARENA)
+def test_arena(n, chi, storage, precondition, layer_gates, known):
+    cfg = _cfg(n, chi, storage, precondition, layer_gates)
+    assert T.lib().tnsim_mps_arena_bytes(C.byref(cfg)) <= known
