@@ -44,11 +44,15 @@ __device__ __forceinline__ double row_sum(double x) {
 
 // Sweeps over the columns of X (rows of the dot products, then J's rows, NT
 // rows of 16 lanes in all) until one rotates nothing; returns whether the last
-// sweep still rotated, with the sweeps taken in `sweep`.
-template <int NT, int GROUPS>
+// sweep still rotated, with the sweeps taken in `sweep`.  RARE: rotations are
+// counted in `nrot`, and one from an infinite radicand vanishes, as 2 / inf
+// does (so that the gate ends in E_NOCONV).  Both cost every gate 3 % (75.0 ->
+// 77.5 us a launch in ten layers of a 10-qubit circuit), so that the sweeps of
+// gates that need neither are compiled without them.
+template <int NT, int GROUPS, bool RARE>
 __device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotated, int rows,
                                             int cols, int maxSweeps, double tol2, double small,
-                                            int &sweep) {
+                                            int &sweep, unsigned &nrot) {
   constexpr int ld = 16 * NT;
   const int tid = threadIdx.x, l = tid & 15, grp = tid >> 4;
   const int P = (cols + 1) & ~1;  // players of the circle method
@@ -93,8 +97,8 @@ __device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotate
           // as in the pair solve: w = 2 sign(delta) / (|delta| + sqrt(delta^2
           // + 4h)), cosine 1 / sqrt(1 + w^2 h), s e^{i phi} = c w g
           const double delta = b - a, s2 = fma(delta, delta, 4.0 * h);
-          const double w = copysign(
-              s2 <= DBL_MAX ? 2.0 * fast_rcp(fabs(delta) + s2 * fast_rsqrt(s2)) : 0.0, delta);
+          double w = copysign(2.0 * fast_rcp(fabs(delta) + s2 * fast_rsqrt(s2)), delta);
+          if (RARE && !(s2 <= DBL_MAX)) w = 0.0;
           const double wh = w * h, c = fast_rsqrt(fma(w, wh, 1.0)), cw = c * w;
           const double2 se = make_double2(cw * g.x, cw * g.y), sec = cconj(se);
 #pragma unroll
@@ -102,6 +106,7 @@ __device__ __forceinline__ int small_sweeps(double2 *X, double *nrm, int &rotate
             xp[16 * i] = csub(cscale(x[i], c), cmul(sec, y[i]));
             yp[16 * i] = cadd(cmul(se, x[i]), cscale(y[i], c));
           }
+          if (RARE) nrot++;
           if (l == 0) {
             nrm[p] = a - wh;
             nrm[q] = b + wh;
@@ -181,21 +186,29 @@ __global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
   __syncthreads();
   const double eps_r = rows * 0x1p-53, small = fro2 * eps_r * eps_r, tol2 = d.tol * d.tol;
   int sweep = 0, rot = 0;
-  auto run = [&](auto nt) {
-    rot = small_sweeps<decltype(nt)::value, GROUPS>(X, nrm, rotated, rows, cols, d.maxSweeps,
-                                                    tol2, small, sweep);
+  unsigned nrot = 0;  // rotations of this group of lanes (profiling)
+  auto sweeps = [&](auto rare) {
+    auto run = [&](auto nt) {
+      rot = small_sweeps<decltype(nt)::value, GROUPS, decltype(rare)::value>(
+          X, nrm, rotated, rows, cols, d.maxSweeps, tol2, small, sweep, nrot);
+    };
+    switch (ld / 16) {
+      case 1: run(std::integral_constant<int, 1>()); break;
+      case 2: run(std::integral_constant<int, 2>()); break;
+      case 3: run(std::integral_constant<int, 3>()); break;
+      case 4: run(std::integral_constant<int, 4>()); break;
+      case 5:
+      case 6: run(std::integral_constant<int, 6>()); break;
+      case 7:
+      case 8: run(std::integral_constant<int, 8>()); break;
+      default: run(std::integral_constant<int, SMALL_ROWS / 16>()); break;
+    }
   };
-  switch (ld / 16) {
-    case 1: run(std::integral_constant<int, 1>()); break;
-    case 2: run(std::integral_constant<int, 2>()); break;
-    case 3: run(std::integral_constant<int, 3>()); break;
-    case 4: run(std::integral_constant<int, 4>()); break;
-    case 5:
-    case 6: run(std::integral_constant<int, 6>()); break;
-    case 7:
-    case 8: run(std::integral_constant<int, 8>()); break;
-    default: run(std::integral_constant<int, SMALL_ROWS / 16>()); break;
-  }
+  // (norms below 2^510 have finite squares)
+  if (__builtin_amdgcn_readfirstlane(d.ctr || !(fro2 < 0x1p510)))
+    sweeps(std::true_type());
+  else
+    sweeps(std::false_type());
   // left vectors and squared norms where the truncation and the write-back
   // (and the adjoint) look for them
   for (int e = tid; e < cols * ld; e += THREADS) {
@@ -204,6 +217,12 @@ __global__ __launch_bounds__(THREADS) void k_small(const GateDesc *descs) {
     if (d.trans && r >= rows && r < tot) d.J[(size_t)c * d.ldj + r - rows] = X[e];
   }
   for (int c = tid; c < cols; c += THREADS) d.sig2[c] = nrm[c];
+  // 8 flops a row for the dot product of every pair of columns, 32 a row (J's
+  // included) for a rotation of two columns
+  if (d.ctr && l == 0) {
+    const unsigned dots = tid == 0 ? sweep * (cols * (cols - 1) / 2) : 0;
+    atomicAdd(&d.ctr[CTR_SMALL_FLOP], 8ull * dots * rows + 32ull * nrot * tot);
+  }
   if (tid == 0) {
     d.sc->fro2 = fro2;
     d.sc->rot = rot;  // 1: not converged

@@ -616,6 +616,9 @@ GateDesc make_desc(tnsim_mps o, const BatchItem &it, bool force_trans, bool full
   return d;
 }
 
+// Merge of two sites and the gate on it.
+double merge_flops(const GateDesc &d) { return 8.0 * d.m * d.chiM * d.n + 32.0 * d.m * d.n; }
+
 // Copy descriptors into the owner's descriptor array, once the pinned staging
 // buffer feeds no earlier copy.  With `second`, the second stream, its staging
 // buffer and descriptor region.
@@ -642,16 +645,19 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
   tnsim_mps h = o;
   int maxM = 0, maxColsPad = 0, maxChiR = 0, qrN = 0, qrMr = 0;
   bool small1 = false, small2 = false, block = false, qr128 = false, qr64 = false;
-  double theta_flop = 0.0, theta_byte = 0.0, colnorm_byte = 0.0, qr_flop = 0.0;
+  double theta_flop = 0.0, theta_byte = 0.0, colnorm_byte = 0.0, qr_flop = 0.0, small_flop = 0.0;
   for (int g = 0; g < ng; g++) {
     const GateDesc &d = D[g];
     (d.small == 0 ? block : d.small == 1 ? small1 : small2) = true;
-    if (d.small) continue;
+    if (d.small) {
+      small_flop += merge_flops(d);
+      continue;
+    }
     maxM = std::max(maxM, d.m);
     maxColsPad = std::max(maxColsPad, d.colsPad);
     maxChiR = std::max(maxChiR, d.chiR);
     const double eb = d.storage == 0 ? 16.0 : 8.0, tb = d.tfp32 ? 8.0 : 16.0;
-    theta_flop += 8.0 * d.m * d.chiM * d.n + 32.0 * d.m * d.n;
+    theta_flop += merge_flops(d);
     theta_byte += eb * ((double)d.m * d.chiM + (double)d.chiM * d.n) + (tb + 16.0) * d.m * d.n;
     colnorm_byte += 16.0 * d.rows * d.cols;
     if (d.qr) {
@@ -668,7 +674,7 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
   hipStream_t st = second ? o->stream2 : o->stream;
   // small gates: merge and SVD in one launch (they take no sweeps)
   if (small1 || small2) {
-    ProfScope p(h, TNSIM_K_EIG, 0.0, 0.0, second);
+    ProfScope p(h, TNSIM_K_EIG, small_flop, 0.0, second);
     launch_small(st, ddev, ng, small1, small2);
     LAUNCHCHK(h, "small gates");
   }
@@ -3250,7 +3256,9 @@ tnsim_status tnsim_profile_read(tnsim_mps h, tnsim_kernel_stat *out) {
   out[TNSIM_K_GRAM].bytes = (double)ctr[CTR_GRAM_BYTE];
   // one 2x2 rotation updates two columns and two rows of G and two columns of
   // V (64 entries each); an entry update is 2 complex multiply-adds = 16 flops
-  out[TNSIM_K_EIG].flops = (double)ctr[CTR_EIG_ROT] * 6.0 * PW * 16.0;
+  // (as many as the method takes; k_eig's rotations without scales execute half).
+  // Small gates: their merges, and what k_small counted.
+  out[TNSIM_K_EIG].flops += (double)ctr[CTR_EIG_ROT] * 6.0 * PW * 16.0 + (double)ctr[CTR_SMALL_FLOP];
   out[TNSIM_K_EIG].bytes = 0.0;
   out[TNSIM_K_ROT].flops = (double)ctr[CTR_ROT_FLOP];
   out[TNSIM_K_ROT].bytes = (double)ctr[CTR_ROT_BYTE];

@@ -94,7 +94,8 @@ struct GateDesc {
 
 // Device work counters, accumulated by the Jacobi kernels (one atomic per
 // workgroup): algorithmic flops and bytes of what each launch really did.
-enum { CTR_GRAM_FLOP = 0, CTR_GRAM_BYTE, CTR_EIG_ROT, CTR_ROT_FLOP, CTR_ROT_BYTE, CTR_COUNT };
+enum { CTR_GRAM_FLOP = 0, CTR_GRAM_BYTE, CTR_EIG_ROT, CTR_ROT_FLOP, CTR_ROT_BYTE,
+       CTR_SMALL_FLOP, CTR_COUNT };
 
 struct Gate1Desc {
   void *A;
