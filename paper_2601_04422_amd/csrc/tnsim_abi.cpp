@@ -705,7 +705,9 @@ tnsim_status gates_prepare(tnsim_mps o, const GateDesc *D, int ng, bool second =
                            qr128, qr64);
         }
         if (qr64) launch_qr_tgroup(st, ddev, ng, stage, grp);
-        launch_qr_update_group(st, ddev, ng, stage, grp, 0, qrN - gend, rows, qr128);
+        // (stage 0's T also serves U = Q1 [W; 0], Q2 is never applied)
+        if (stage == 0 || gend < qrN)
+          launch_qr_update_group(st, ddev, ng, stage, grp, 0, qrN - gend, rows, qr128);
       }
       if (stage == 0) launch_qr_r1h(st, ddev, ng, qrN);
     }

@@ -6,7 +6,7 @@
 // enough for the host code to go its way: a gate's Jacobi takes the number of
 // sweeps that the scenario sets, a gradient entry counts its adjoint launches.
 //
-// usage: fake_hip gradient | replan; prints "ok" or what went wrong.
+// usage: fake_hip gradient | replan | qr; prints "ok" or what went wrong.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -189,6 +189,8 @@ hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t st) {
 // sweeps that the gate on sites (i, i + 1) takes
 static int sweeps_of(int i) { return i % 4 == 0 ? 2 : 6; }
 
+static int group_updates = 0, empty_updates = 0;
+
 namespace tn {
 int small_class(int, int, int) { return 0; }
 void launch_fetch(hipStream_t st, void *host, const void *dev, size_t n, uint32_t *flag, uint32_t v) {
@@ -264,7 +266,11 @@ NOOP(launch_rot, D, int, int, int, int, int, int, bool)
 NOOP(launch_qr_panel, D, int, int, int, int, bool, bool)
 NOOP(launch_qr_update, D, int, int, int, int, int, bool, bool)
 NOOP(launch_qr_tgroup, D, int, int, int)
-NOOP(launch_qr_update_group, D, int, int, int, int, int, int, bool)
+void launch_qr_update_group(hipStream_t st, D, int, int stage, int, int, int max_cols, int, bool) {
+  group_updates++;
+  empty_updates += stage == 1 && max_cols <= 0;
+  noop(st);
+}
 NOOP(launch_qr_r1h, D, int, int)
 NOOP(launch_qr_r2h, D, int, int)
 NOOP(launch_qr_gather, D, int, int, int)
@@ -355,11 +361,21 @@ static int replan(tnsim_mps h, const tnsim_config &cfg) {
   return destroyed_in_flight ? bad("a graph in flight was destroyed") : 0;
 }
 
+// Preconditioned gates of one group of reflectors: Q1's T factor is computed,
+// nothing is launched for Q2, which is not applied.
+static int qr(tnsim_mps h) {
+  const tnsim_gate g = gate2(2);
+  if (tnsim_apply_layer(h, &g, 1)) return bad("layer failed");
+  if (group_updates == 0) return bad("no factors for U");
+  return empty_updates ? bad("a factor of Q2 that nothing reads") : 0;
+}
+
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   tnsim_config cfg{};
   cfg.n_qubits = 8;
   cfg.chi_max = 8;
+  cfg.svd_precondition = what == "qr";
   Stream st;
   const size_t bytes = tnsim_mps_arena_bytes(&cfg);
   void *arena = dev_alloc(bytes);
@@ -368,7 +384,8 @@ int main(int argc, char **argv) {
   if (tnsim_mps_create(&cfg, arena, bytes, &st, &h)) return bad("create failed");
   const int r = what == "gradient" ? gradient(h, cfg, st)
                 : what == "replan" ? replan(h, cfg)
-                                   : bad("usage: fake_hip gradient | replan");
+                : what == "qr"     ? qr(h)
+                                   : bad("usage: fake_hip gradient | replan | qr");
   tnsim_mps_destroy(h);
   free(arena);
   if (!r) printf("ok\n");

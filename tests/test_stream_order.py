@@ -1,7 +1,8 @@
 """Ordering of the library's host side (csrc/tnsim_abi.cpp) on a stream of its
 own, against a stand-in for the HIP runtime whose streams are slow queues
 (tests/fake_hip.cpp): what a call hands back has been computed by then, and
-nothing is freed that work in flight still uses.  No GPU."""
+nothing is freed that work in flight still uses, nothing is launched whose
+result is not read.  No GPU."""
 import os
 import shutil
 import subprocess
@@ -39,3 +40,7 @@ def test_gradient_is_read_after_its_adjoints(exe):
 
 def test_a_replaced_graph_stays_until_its_sweep_is_done(exe):
     _run(exe, "replan")
+
+
+def test_no_factors_of_the_second_q(exe):
+    _run(exe, "qr")
