@@ -14,11 +14,14 @@
 // a chain of K / 16 staged steps of 2 us) most CUs stood idle.  Three
 // expectations, an overlap, a norm and four amplitudes at chi = 500, n = 28:
 // 35.5 -> 9.1 ms; 1000 shots at chi = 256, n = 48: 8.7 -> 3.85 ms.  Large
-// products gain nothing from larger tiles either (the four wavefronts' loads
-// of a tile meet in L1 and L2): an expectation value at chi = 1024 5.8 -> 5.7
-// ms, at 2048 42.0 -> 41.3 (65 TFLOP/s), 2048 shots at 1024 8.5 -> 7.8.
+// products of the transfer chains gain nothing from larger tiles either (the
+// four wavefronts' loads of a tile meet in L1 and L2): an expectation value at
+// chi = 1024 5.8 -> 5.7 ms, at 2048 42.0 -> 41.3 (65 TFLOP/s), 2048 shots at 1024
+// 8.5 -> 7.8.  Products over very many columns do: see k_zgemm_cols.
 // Bound by the matrix cores: their rate when the chip is full, the chain of
 // K / (4 NW) steps of 16 products when it is not.
+#include <algorithm>
+
 #include "tnsim_internal.h"
 #include "tn_complex.h"
 
@@ -154,6 +157,121 @@ __global__ __launch_bounds__(64 * NW, 2) void k_zgemm(ZgemmArgs g) {
   }
 }
 
+// The same for the columns of many shots (A k-contiguous, B and C
+// column-major): 64 x 64 tiles, each wavefront a 32 x 32 quarter, K advances 16
+// at a time through LDS with the next step's loads issued before the current
+// step's products.  A tile's four wavefronts share what they load, and the tiles
+// of an XCD are a contiguous run along A's rows, so that those rows stay in its
+// L2: 2048 x 32768 x 1024 7.9 ms (69 TFLOP/s) against 9.7 in 32 x 32 tiles, 512 x
+// 32768 x 256 545 us against 587, 128 x 32768 x 64 52 against 66.  Bound by the
+// matrix cores.
+constexpr int ZW = 64, ZWK = 16;
+template <class TA, class TB, bool GA>
+__global__ __launch_bounds__(256, 4) void k_zgemm_cols(ZgemmArgs g) {
+  // workgroup L runs on XCD L % 8
+  const int nx = gridDim.x, ntile = gridDim.x * gridDim.y;
+  const int L = blockIdx.x + nx * blockIdx.y, xcd = L & 7, slot = L >> 3;
+  const int per = ntile >> 3, extra = ntile & 7;
+  const int t_lin = xcd * per + min(xcd, extra) + slot;
+  const int tx = t_lin % nx, ty = t_lin / nx;
+  int N = g.N, j0 = tx * ZW, A_off_tile = 0;
+  if (GA) {
+    const int lo = *g.clo;
+    N = *g.chi;
+    j0 += lo;
+    if (g.asplit && j0 >= *g.asplit) A_off_tile = 1;
+  } else if (g.mcount) {
+    N = min(N, g.mult * *g.mcount);
+  }
+  const int i0 = ty * ZW;
+  if (j0 >= N) return;
+  const int M = g.M, K = g.K, z = blockIdx.z;
+  const TA *A = (const TA *)g.A + (z + A_off_tile) * g.za;
+  const TB *B = (const TB *)g.B + z * g.zb;
+  double2 *C = g.C + z * g.zc;
+  __shared__ double2 As[ZWK][ZW], Bs[ZWK][ZW];
+  const int t = threadIdx.x;
+  // this thread's share of a K step: 4 elements of a row of A and of a column of B
+  const int row = t >> 2, k4 = (t & 3) * 4, gi = i0 + row, gj = j0 + row;
+  const TA *pa = A + (long long)min(gi, M - 1) * g.sa;
+  const TB *pb = B + (GA ? (long long)g.bmap[min(gj, N - 1)] : min(gj, N - 1)) * g.sb;
+  double2 ra[4], rb[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int gk = k0 + k4 + q;
+      ra[q] = gi < M && gk < K ? cload(pa + gk) : make_double2(0.0, 0.0);
+      rb[q] = gj < N && gk < K ? cload(pb + gk) : make_double2(0.0, 0.0);
+    }
+  };
+  const int w = t >> 6, lane = t & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
+  zd4_t cr[2][2], ci[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++) {
+      cr[x][y] = zd4_t{0.0, 0.0, 0.0, 0.0};
+      ci[x][y] = zd4_t{0.0, 0.0, 0.0, 0.0};
+    }
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += ZWK) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      As[k4 + q][row] = ra[q];
+      Bs[k4 + q][row] = rb[q];
+    }
+    __syncthreads();
+    if (k0 + ZWK < K) load(k0 + ZWK);
+#pragma unroll
+    for (int kk = 0; kk < ZWK; kk += 4) {
+      double2 a[2], b[2];
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        a[x] = As[kk + lg][wm + 16 * x + l16];
+        b[x] = Bs[kk + lg][wn + 16 * x + l16];
+      }
+#pragma unroll
+      for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+          cr[x][y] = zmfma(a[x].x, b[y].x, cr[x][y]);
+          cr[x][y] = zmfma(-a[x].y, b[y].y, cr[x][y]);
+          ci[x][y] = zmfma(a[x].x, b[y].y, ci[x][y]);
+          ci[x][y] = zmfma(a[x].y, b[y].x, ci[x][y]);
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++) {
+      const int j = j0 + wn + 16 * y + l16;
+      if (j >= N) continue;
+      const double sc = GA ? g.cscale[j] : 1.0;
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        const int i = i0 + wm + 16 * x + lg + 4 * v;
+        if (i < M) C[(long long)j * g.sc + i] = make_double2(sc * cr[x][y][v], sc * ci[x][y][v]);
+      }
+    }
+}
+
+// Whether the 64 x 64 tiles are the better ones.  They need about four of them
+// for every row of K, up to the 1024 that the chip holds at once, and past that a
+// last round of tiles that is not nearly empty; K of up to 16 leaves the 32 x 32
+// kernel's wavefronts without work.  us in 32 x 32 / 64 x 64 tiles: K = 32, 128
+// tiles 6.5 / 9.1, 256 tiles 10.1 / 9.7; K = 128, 376 tiles 38 / 45, 512 tiles 49 /
+// 46; K = 256, 376 tiles 61 / 79, 1024 tiles 152 / 146; K = 384, 1128 tiles 247 / 267,
+// 1536 tiles 329 / 312; K = 16, 64 tiles 6.0 / 5.4.
+static bool zgemm_cols(const ZgemmArgs &g) {
+  const long long tiles = (long long)((g.M + ZW - 1) / ZW) * ((g.N + ZW - 1) / ZW) * g.batch;
+  const long long rounds = (tiles + 1023) / 1024;
+  return g.K <= 16 || (tiles >= std::max(180, std::min(4 * g.K, 1024)) &&
+                       (rounds == 1 || 10 * tiles >= 7 * 1024 * rounds));
+}
+
 // f(TA(), TB()) with the operands' element types
 template <class F>
 static void zgemm_types(int a_storage, int b_storage, F f) {
@@ -169,12 +287,21 @@ static void zgemm_types(int a_storage, int b_storage, F f) {
 
 template <bool AK, bool AC, bool BK, bool CM, bool GA = false>
 static void zgemm_dispatch(hipStream_t st, const ZgemmArgs &g, int a_storage, int b_storage) {
+  static_assert(!CM || (AK && !AC && BK), "column-major products take k_zgemm_cols");
   const dim3 grid((g.N + ZT - 1) / ZT, (g.M + ZT - 1) / ZT, g.batch);
   // fewer tiles than CUs and a K to split: twice the wavefronts on each
   const bool few = (size_t)grid.x * grid.y * grid.z <= 256 && g.K >= 64;
   zgemm_types(a_storage, b_storage, [&](auto ta, auto tb) {
     using TA = decltype(ta);
     using TB = decltype(tb);
+    if constexpr (CM) {
+      if (zgemm_cols(g)) {
+        hipLaunchKernelGGL((k_zgemm_cols<TA, TB, GA>),
+                           dim3((g.N + ZW - 1) / ZW, (g.M + ZW - 1) / ZW, g.batch), dim3(256), 0,
+                           st, g);
+        return;
+      }
+    }
     if (few)
       hipLaunchKernelGGL((k_zgemm<TA, TB, AK, AC, BK, CM, GA, 8>), grid, dim3(512), 0, st, g);
     else
