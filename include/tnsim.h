@@ -339,7 +339,7 @@ tnsim_status tnsim_backward(tnsim_mps mps, double dloss, double *grad_angles);
 typedef enum {
   TNSIM_K_THETA = 0, /* two-site merge + gate epilogue */
   TNSIM_K_GRAM,      /* pair Gram blocks */
-  TNSIM_K_EIG,       /* 64x64 Hermitian Jacobi */
+  TNSIM_K_EIG,       /* 64x64 Hermitian Jacobi; gates decomposed whole by one workgroup */
   TNSIM_K_ROT,       /* pair rotations */
   TNSIM_K_COLNORM,   /* column norms */
   TNSIM_K_TRUNC,     /* sort + truncation rule */

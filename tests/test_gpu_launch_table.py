@@ -62,6 +62,24 @@ def test_autotuned_table_is_taken(T):
     _equal(a, b)
 
 
+@pytest.mark.parametrize("split", [1, 4, 16])
+def test_gram_splits_agree_to_rounding(T, split):
+    """Matrices of up to eight column blocks, whose Grams the table splits over
+    1, 4 or 16 row chunks (what their rows allow) against the built-in rule."""
+    n = 16
+    a, b = (T.MPS(n, 100, 0.0) for _ in range(2))
+    for m in (a, b):
+        m.import_state(*W.random_canonical_mps(n, W.saturated_dims(n, 100), 2))
+    a.set_autotune([0] * 4 + [split] * 4)
+    a.profile(True)
+    for layer in W.brickwork_haar(n, 2, 8):
+        assert a.apply_layer(layer) == T.OK and b.apply_layer(layer) == T.OK
+    assert a.profile_read()["gram"]["launches"] > 0
+    assert list(a.bond_dims()) == list(b.bond_dims())
+    for k in range(n - 1):
+        assert np.max(np.abs(a.lam(k) - b.lam(k))) < 1e-12
+
+
 @pytest.mark.parametrize("precision,storage", [("fp64", "c128"), ("bf16x6", "c64")])
 def test_launches_of_many_pairs(T, precision, storage):
     """Four handles of 40 gates, up to eight column pairs each: 1056 pairs and
